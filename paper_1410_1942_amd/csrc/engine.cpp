@@ -45,6 +45,12 @@ hipError_t launch_divnorm(const Slot *slot, double inv_h, const double *u,
                           const double *v, const double *w, double *part, int blocks,
                           hipStream_t st);
 hipError_t static_scratch(void **ptr, size_t *bytes);
+// The resident kernel (resident.hip); weak, so that the host engine also
+// links without its device side (then no solve is resident).
+__attribute__((weak)) int resident_shapes(int family, ResidentShape *out, int cap);
+__attribute__((weak)) hipError_t launch_resident(int family, int shape, int blocks, unsigned lds,
+                                                 const Slot *slots, int s0, int s1, int budget,
+                                                 hipStream_t s);
 }  // namespace pcgmi
 
 using namespace pcgmi;
@@ -350,6 +356,58 @@ bool one_sweep(const Geometry &G, int prec, int flags)
     return !(flags & PCG_TWO_SWEEPS) && G.tx > 0;
 }
 
+// How a grid runs in the resident kernel: shape (index into the kernel's
+// shapes, -1: not at all), rows and planes a brick, bricks along y and z,
+// LDS a brick.
+struct ResidentPlan {
+    int shape = -1;
+    int rby = 0, rbz = 0, rnby = 0, rnbz = 0;
+    unsigned lds = 0;
+    int bricks() const { return rnby * rnbz; }
+};
+
+// One brick a CU, all at once.
+constexpr int kResMaxBricks = 256;
+
+// The resident form of a grid: single solves with no tile form asked for,
+// where the bricks' registers and LDS hold the whole grid.  Of the shapes
+// that do, the one of the least estimated time an iteration.
+ResidentPlan resident_plan(const pcg_grid_t &g, int prec, const pcg_opts_t &o, bool batch)
+{
+    ResidentPlan best;
+    if (!resident_shapes || batch || o.tz > 0 || o.grid_blocks > 0) return best;
+    if (o.flags & (PCG_FRACTIONS | PCG_FLAT_TILES | PCG_PLANE_TILES | PCG_TWO_SWEEPS |
+                   PCG_NARROW_TILES))
+        return best;
+    ResidentShape sh[32];
+    const int n = std::min(32, resident_shapes(prec, sh, 32));
+    const size_t es = prec == PCG_PREC_FP32_IR ? 4 : 8;
+    double cost = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const int64_t cols = (int64_t)sh[i].cols * kResThreads;
+        if (g.nx > cols) continue;
+        ResidentPlan p;
+        p.shape = i;
+        p.rbz = sh[i].planes;
+        p.rnbz = (g.nz + p.rbz - 1) / p.rbz;
+        p.rby = (int)std::min<int64_t>(g.ny, cols / g.nx);
+        p.rnby = (g.ny + p.rby - 1) / p.rby;
+        p.rby = (g.ny + p.rnby - 1) / p.rnby;      // bricks of even height
+        p.rnby = (g.ny + p.rby - 1) / p.rby;
+        if ((int64_t)p.rnby * p.rnbz > kResMaxBricks) continue;
+        if ((int64_t)2 * p.rbz * g.nx > kResHalo * kResThreads) continue;
+        // the exchange words live in the second direction buffer
+        if ((size_t)p.bricks() * kResWords * 8 > es * g.nx * g.ny * g.nz) continue;
+        const size_t lds = (size_t)p.rbz * (p.rby + 2) * (g.nx + 2) * es;
+        if (lds > kResLds) continue;
+        p.lds = (unsigned)align_up(lds, 16);
+        const double c = (p.bricks() > 1 ? 3.5 + 0.006 * p.bricks() : 0.0) +
+                         0.1 * sh[i].cols * sh[i].planes;
+        if (best.shape < 0 || c < cost) { best = p; cost = c; }
+    }
+    return best;
+}
+
 size_t slot_bytes(const Geometry &G, int prec, bool frac = false, bool sweep = false)
 {
     const size_t n = (size_t)G.n;
@@ -592,6 +650,10 @@ struct SlotHost {
     int nclasses = 0;            // fluid classes when coded
     double *ax = nullptr, *ay = nullptr, *az = nullptr, *vol = nullptr;  // arena, if reserved
     bool has_frac = false;       // cut-cell fractions in use (coefficient mode 2)
+    ResidentPlan res;            // resident form, if the grid has one
+    unsigned long long *rsync = nullptr;   // its exchange words
+    bool resident = false;       // the running solve takes it
+    int rsteps = 0;              // polling steps of the running solve
     const double *rhs = nullptr;
     double *x = nullptr;
     Clock::time_point t0;
@@ -658,6 +720,9 @@ struct Engine {
     int graph_modes = -1;   // modes the captured graph was built for
     bool k2only = false;    // second-half launches only (every solve in one sweep)
     int graph_k2only = -1;  // the same for the captured graph
+    pcg_opts_t opts{};      // as given (zero: defaults)
+    int cus = 0;            // compute units of the device
+    int nresident = 0;      // running solves in the resident kernel
     int fail_after = 0;     // test hook: the step call that reports a failure
     HostMirror *mirror = nullptr;  // caller-owned host mirrors: no pinned memory,
                                    // no capture stream, launches without graphs
@@ -699,6 +764,7 @@ struct Engine {
         int st = check_opts(o);
         if (st) return st;
         if (o) {
+            opts = *o;
             prec = o->precision;
             if (o->check_every > 0) check_every = o->check_every;
             inner_maxit = o->inner_maxit;
@@ -746,6 +812,9 @@ struct Engine {
         HIP_TRY(hipMemcpyAsync(d_hdr, h_hdr, sizeof(BatchHeader), hipMemcpyHostToDevice, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         if (!mirror) HIP_TRY(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
+        int dev = 0;
+        HIP_TRY(hipGetDevice(&dev));
+        HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
         return PCG_OK;
     }
 
@@ -844,6 +913,9 @@ struct Engine {
                                            plane_group(*grid_, prec, flags | this->flags, bc,
                                                        batch_mode()));
         const bool sweep = one_sweep(geo, prec, flags | this->flags);
+        pcg_opts_t ro = opts;
+        ro.flags |= flags;
+        const ResidentPlan res = resident_plan(*grid_, prec, ro, batch_mode());
         const size_t need = slot_bytes(geo, prec, frac_space, sweep);
         size_t off = 0;
         if (!alloc.alloc(need, &off)) return max_slots == 1 ? PCG_ENOMEM : PCG_EBUSY;
@@ -880,6 +952,12 @@ struct Engine {
             S.ay = (double *)p; p += align_up(8 * nx * (ny + 1) * nz, kAlign);
             S.az = (double *)p; p += align_up(8 * nx * ny * (nz + 1), kAlign);
             S.vol = (double *)p;
+        }
+        // the resident kernel uses one direction buffer; its exchange words
+        // live in the next, which every solve's set-up action zeroes
+        if (res.shape >= 0 && res.bricks() <= cus) {
+            S.res = res;
+            S.rsync = (unsigned long long *)S.dir1;
         }
 
         st = encode_slot(S, rho, mask, flags);
@@ -1035,7 +1113,11 @@ struct Engine {
         h.inner_maxit = inner_maxit > 0 ? inner_maxit : INT32_MAX;
         h.inner_tol2 = inner_tol * inner_tol;
         h.warm = (flags & PCG_WARM_START) ? 1 : 0;
-        h.fused = S.z2 ? 1 : 0;
+        // classes on grids with a resident form, unless each launch is timed
+        S.resident = S.res.shape >= 0 && S.classes && !S.has_frac && !timing;
+        S.rsteps = 0;
+        h.resident = S.resident ? 1 : 0;
+        h.fused = S.z2 && !S.resident ? 1 : 0;
         h.scale = 1.0;
         HIP_TRY(hipMemcpyAsync(d_states + id, &h, sizeof(SlotState), hipMemcpyHostToDevice, stream));
         S.running = true;
@@ -1062,6 +1144,7 @@ struct Engine {
         int ns = 0;
         int m = 0;
         bool all_fused = true;
+        int nres = 0, rblk = 0;
         for (int id = 0; id < max_slots; ++id) {
             SlotHost &S = slots[id];
             if (!S.used || !S.running) continue;
@@ -1096,6 +1179,17 @@ struct Engine {
             set_frac(d, S);
             d.tab64 = S.tab64;
             d.tab32 = S.tab32;
+            d.rblk = rblk;
+            if (S.resident) {
+                d.resident = 1;
+                d.rby = S.res.rby;
+                d.rbz = S.res.rbz;
+                d.rnby = S.res.rnby;
+                d.rnbz = S.res.rnbz;
+                d.rsync = S.rsync;
+                rblk += S.res.bricks();
+                ++nres;
+            }
             m |= 1 << slot_mode(S);
             tb += S.geo.ntiles;
             all_fused = all_fused && S.z2 != nullptr;
@@ -1109,6 +1203,7 @@ struct Engine {
         h_hdr->k2only = k2only ? 1 : 0;
         total_tiles = tb;
         nrunning = ns;
+        nresident = nres;
         modes = m;
         view_id = -1;
         if (ns) HIP_TRY(hipMemcpyAsync(d_slots, h_slots, sizeof(Slot) * ns, hipMemcpyHostToDevice, stream));
@@ -1233,6 +1328,48 @@ struct Engine {
         table_dirty = true;
     }
 
+    // The set-up, residual and update actions of resident solves: n launches,
+    // each taking every solve's next one.
+    hipError_t launch_actions(int n)
+    {
+        hipError_t e = hipSuccess;
+        for (int i = 0; i < n && e == hipSuccess; ++i)
+            e = k2only ? launch_position(2, stream) : launch_iteration(stream);
+        return e;
+    }
+
+    // One polling step of a single resident solve: the actions it is waiting
+    // for, its iterations, and the actions after them.  A solve takes
+    // check_every iterations in the first step, twice that in the second and
+    // then up to kResBudget (FP32 + refinement: to the end of its inner solve,
+    // one trip a step).  A step costs about 40 us beside its iterations (the
+    // cooperative launch 20), which 32 iterations of a small grid (130 us)
+    // would not hide.
+    static constexpr int kResBudget = 4096;
+    int resident_step()
+    {
+        int id = 0;
+        while (!slots[id].resident || !slots[id].running) ++id;
+        SlotHost &S = slots[id];
+        const bool ir = prec == PCG_PREC_FP32_IR;
+        int pre = 0;
+        switch (h_states[id].phase) {
+        case K1_MEAN_B: pre = ir ? 4 : 2; break;
+        case K1_INIT64: pre = 1; break;
+        case K1_IR_INIT: pre = 3; break;
+        case K1_CG_A: case K1_IR_A: break;
+        default: pre = 3;
+        }
+        int budget = kResBudget;
+        if (S.rsteps < 2) budget = std::min(budget, check_every << S.rsteps);
+        ++S.rsteps;
+        HIP_TRY(launch_actions(pre));
+        HIP_TRY(launch_resident(prec, S.res.shape, S.res.bricks(), S.res.lds, d_slots, 0, nrunning,
+                                budget, stream));
+        HIP_TRY(launch_actions((ir ? 2 : 1) + (S.singular ? 2 : 0)));
+        return PCG_OK;
+    }
+
     // Run `replays` graphs (or timed chunks), then refresh the status mirror.
     int step(int replays)
     {
@@ -1243,14 +1380,17 @@ struct Engine {
         int st = upload_table();
         if (st) return st;
         if (nrunning == 0) return PCG_OK;
-        if (mirror) {
+        if (mirror || nresident) {
             grid = choose_grid();    // launched directly: no graph to capture
         } else {
             st = capture();
             if (st) return st;
         }
         for (int r = 0; r < replays; ++r) {
-            if (timing) {
+            if (nresident) {
+                st = resident_step();
+                if (st) return st;
+            } else if (timing) {
                 st = timed_chunk();
                 if (st) return st;
             } else if (mirror) {
@@ -1265,6 +1405,10 @@ struct Engine {
         for (int id = 0; id < max_slots; ++id) {
             SlotHost &S = slots[id];
             if (!S.used || !S.running) continue;
+            if (h_states[id].rfail) {
+                g_hip_err = "resident kernel: an exchange between workgroups timed out";
+                return PCG_EHIP;
+            }
             if (h_states[id].phase == PH_DONE) {
                 S.running = false;
                 S.finished = true;

@@ -2263,6 +2263,17 @@ __device__ __forceinline__ void note_x_update(SlotState &st)
     st.xpend += 1;
 }
 
+// From one first-half action to the next (or to the end): launches of the
+// two halves alternate, so by way of an empty second half; a resident
+// solve's iterations need no such alternation, and its launches take the
+// actions as they come.
+__device__ __forceinline__ void go_on(SlotState &st, int next)
+{
+    if (st.resident) { st.phase = next; return; }
+    st.phase = K2_NONE;
+    st.after = next;
+}
+
 __device__ void advance(SlotState &st, int phase, const double (&tot)[3])
 {
     switch (phase) {
@@ -2279,8 +2290,7 @@ __device__ void advance(SlotState &st, int phase, const double (&tot)[3])
         st.rz = tot[1];
         st.rr = tot[2];
         st.first = 1;
-        st.phase = K2_NONE;
-        st.after = (st.rr <= st.tol2 || st.maxit == 0) ? K1_CHECK64 : K1_CG_A;
+        go_on(st, (st.rr <= st.tol2 || st.maxit == 0) ? K1_CHECK64 : K1_CG_A);
         break;
     }
     case K1_CG_A: {
@@ -2355,20 +2365,20 @@ __device__ void advance(SlotState &st, int phase, const double (&tot)[3])
     case K1_CHECK64: {
         st.rr_true = tot[0];
         const int end = st.singular ? K1_MEAN_X : PH_DONE;
-        if (tot[0] <= st.tol2) { st.phase = K2_NONE; st.after = end; st.status = PCG_OK; }
-        else if (st.iter >= st.maxit) { st.phase = K2_NONE; st.after = end; st.status = PCG_MAXIT; }
+        if (tot[0] <= st.tol2) { go_on(st, end); st.status = PCG_OK; }
+        else if (st.iter >= st.maxit) { go_on(st, end); st.status = PCG_MAXIT; }
         else if (st.fused && st.iter > 0) {
             // the last sweep left alpha and beta for the next one
             if (st.pap > 0.0 && isfinite(st.pap)) st.phase = K2_CG_F;
             else finish(st, PCG_EBREAKDOWN);
-        } else { st.phase = K2_NONE; st.after = K1_CG_A; }
+        } else { go_on(st, K1_CG_A); }
         break;
     }
     case K1_MEAN_B: {
         st.nfluid = tot[1];
         st.bshift = tot[1] > 0.0 ? tot[0] / tot[1] : 0.0;
         if (!isfinite(st.bshift)) { finish(st, PCG_EDOMAIN); break; }
-        st.phase = K2_NONE;   // then the initialisation held in `after`
+        go_on(st, st.after);   // the initialisation
         break;
     }
     case K1_MEAN_X: {
@@ -2402,8 +2412,7 @@ __device__ void advance(SlotState &st, int phase, const double (&tot)[3])
         st.rr_true = tot[0];
         st.upd_s = 0.0;
         st.scale = pow2_scale(sqrt(tot[0]));
-        st.phase = K2_NONE;
-        st.after = K1_IR_RESID;
+        go_on(st, K1_IR_RESID);
         break;
     }
     case K1_IR_RESID: {
@@ -2741,10 +2750,12 @@ __device__ __forceinline__ bool serves(const Slot &S, int ph, bool k2only)
     if (WHICH == 0) return k0_phase(ph);
     if (WHICH == 3 && k0_phase(ph)) return true;
     if (slot_mode(S) != MODE) return false;
-    if (WHICH == 1 || WHICH == 3) return ph == K1_CG_A || ph == K1_IR_A;
+    // (a resident solve's iterations belong to the resident kernel)
+    const bool passA = (ph == K1_CG_A || ph == K1_IR_A) && !S.resident;
+    if (WHICH == 1 || WHICH == 3) return passA;
     // second-half launches alone (one-sweep solves on plane tiles): also
     // the first-half actions of this mode's slots
-    if (MODE >= 3 && k2only && (k0_phase(ph) || ph == K1_CG_A || ph == K1_IR_A)) return true;
+    if (MODE >= 3 && k2only && (k0_phase(ph) || passA)) return true;
     return ph >= 11 && ph <= 19;
 }
 

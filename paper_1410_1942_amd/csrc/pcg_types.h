@@ -20,6 +20,20 @@ constexpr int kTileY = 4;
 // Bytes of the device array behind the allocation-free entry point.
 constexpr unsigned long long kStaticScratchBytes = 64ull << 20;
 
+// Resident form: threads of a workgroup, the most y-halo cells of a brick a
+// thread carries, 8-byte words a brick exchanges through (four for the sums
+// after the update, two for p.A p, each half a double beside a 32-bit tag),
+// and the most LDS a brick may take (of 160 KiB a CU, less the kernel's tables).
+constexpr int kResThreads = 512;
+constexpr int kResHalo = 8;
+constexpr int kResWords = 6;
+constexpr unsigned kResLds = 160u * 1024u - 4096u;
+
+// A shape of the resident kernel: cols columns of planes cells a thread.
+struct ResidentShape {
+    int cols, planes;
+};
+
 // Density classes: up to kMaxFluidClasses distinct fluid densities get a
 // one-byte class; kClsWallD stands for a Dirichlet wall (density 0 in the
 // face formula), kClsSolid for hull cells and Neumann walls (density +inf).
@@ -91,6 +105,9 @@ struct alignas(128) SlotState {
     int32_t xpend;    // earlier iterations whose x (FP64) or d (IR) update is pending: 0..2
     int32_t fused;    // iterations run as one sweep (K2_CG_F, K2_IR_F)
     int32_t zsel;     // one-sweep iterations: z is in Slot::z2 (1) or Slot::z (0)
+    int32_t resident; // iterations run in the resident kernel (resident.hip)
+    int32_t rfail;    // resident kernel: an exchange between workgroups timed out
+    uint32_t repoch;  // resident kernel: tag of this solve's last exchange
 };
 
 // Read-only description of a slot (rewritten by the host between replays).
@@ -131,6 +148,11 @@ struct Slot {
     // (ax [nz][ny][nx+1], ay [nz][ny+1][nx], az [nz+1][ny][nx]) and volume
     // fractions per cell
     const double *ax, *ay, *az, *vol;
+    // resident form (resident.hip): bricks of rby whole rows x rbz planes,
+    // rnby x rnbz of them, one workgroup each from workgroup rblk of the
+    // launch; rsync: kResWords words a brick.  resident 0: not in use
+    int32_t resident, rby, rbz, rnby, rnbz, rblk;
+    unsigned long long *rsync;
 };
 
 struct BatchHeader {

@@ -1,0 +1,570 @@
+// The CG iteration of solves that fit on the chip (gfx950, wave64).
+//
+// A grid is cut into bricks of whole rows (rby rows x rbz planes), one
+// workgroup each and all of them resident at once (a cooperative launch).  A
+// workgroup keeps its brick's z = D^-1 r and x (FP32 + refinement: the
+// correction d) in registers and its direction p in LDS from one iteration
+// to the next, so an iteration moves only the bricks' faces and three sums:
+//   p = z + beta p (own cells, and the rows and planes around the brick from
+//   the neighbours' z), q = A p, p.A p                        -> exchange 1
+//   x += alpha p, z -= alpha q / diag, r.z, r.r, faces of z   -> exchange 2
+// This is the textbook order of the two-pass iteration.  It ends where the
+// two-pass state machine would leave the loop (convergence, iteration cap,
+// breakdown) or after `budget` iterations, with z, x and p back in the slot's
+// vectors.
+//
+// What bounds it: the two exchanges, about 1.5 us each across the eight XCDs
+// (a store that reaches memory, a load that sees it), and for bricks of many
+// cells their LDS traffic, 56 to 96 B a cell.  A launch per iteration instead
+// waits for memory plane after plane and streams 41 B a cell.  Measured per
+// iteration, launches against this: FP64 32^3 15.9 -> 6.8 us, 64^3 22.3 -> 8.1,
+// 101 x 77 x 59 32.5 -> 10.1, 128^3 45.0 -> 15.4, 320 x 128 x 96 90.0 -> 34.9;
+// FP32 32^3 16.0 -> 7.0, 64^3 21.4 -> 7.7, 128^3 48.5 -> 12.9.
+//
+// Exchange: a workgroup's sums go out as words of half a double beside a
+// 32-bit tag, the number of the exchange, written and read with relaxed
+// device-scope atomics (which reach the memory all XCDs share); a reader
+// polls until every workgroup's words bear the tag, so no flag, fence or
+// counter is needed.  The face values are written the same way before the
+// sums (s_waitcnt between them), so whoever has seen the sums may read the
+// faces.  All workgroups add the sums in the same order and so take the same
+// decisions.  A word is rewritten only after an exchange that its readers
+// have all passed.
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+#include <type_traits>
+
+#include "pcg_types.h"
+#include "pcg.h"
+
+namespace pcgmi {
+
+namespace {
+
+#define GLB __attribute__((address_space(1)))
+template <typename T>
+__device__ __forceinline__ GLB T *gp(T *p) { return (GLB T *)p; }
+template <typename T>
+__device__ __forceinline__ const GLB T *gp(const T *p) { return (const GLB T *)p; }
+
+typedef unsigned long long u64;
+
+// Polls of one exchange before a workgroup gives up (seconds: only a lost
+// workgroup reaches it).
+constexpr int kSpin = 1 << 21;
+
+template <typename T>
+__device__ __forceinline__ T dev_load(const GLB T *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void dev_store(GLB T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ double wave_sum(double v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+__device__ __forceinline__ double recip(double d)
+{
+    double y = __builtin_amdgcn_rcp(d);
+    double e = fma(-d, y, 1.0);
+    y = fma(y, e, y);
+    e = fma(-d, y, 1.0);
+    return fma(y, e, y);
+}
+__device__ __forceinline__ float recip(float d) { return __builtin_amdgcn_rcpf(d); }
+
+__device__ __forceinline__ void *dir_buf(const Slot &S, int b)
+{
+    return b == 0 ? S.dir0 : (b == 1 ? S.dir1 : S.dir2);
+}
+
+__device__ double pow2_scale(double norm)
+{
+    if (!(norm > 0.0) || !isfinite(norm)) return 1.0;
+    return ldexp(1.0, -ilogb(norm));
+}
+
+// Holds the compiler to the value in a register: what is derived from it in
+// the iteration loop (coefficient addresses, lane masks) is formed there
+// again instead of being kept in registers of its own, several a cell.
+template <typename V>
+__device__ __forceinline__ void keep_here(V &v) { asm volatile("" : "+v"(v)); }
+
+// Sum NV values over the workgroups of a solve: every thread brings its part
+// and leaves with the total, added in an order fixed by the bricks.  False
+// when a workgroup did not answer.
+template <int NV>
+__device__ __forceinline__ bool all_sum(double (&v)[NV], GLB u64 *area, int G, int g, uint32_t tag,
+                                        double (*red)[2 * (kResThreads / 64)], int *fail)
+{
+    constexpr int W = kResThreads / 64;
+    const int t = (int)threadIdx.x, w = t >> 6;
+    // a lone workgroup passes one barrier a call: calls alternate the halves
+    const int r0 = G == 1 && (tag & 1) ? W : 0;
+#pragma unroll
+    for (int m = 0; m < NV; ++m) v[m] = wave_sum(v[m]);
+    if ((t & 63) == 0) {
+#pragma unroll
+        for (int m = 0; m < NV; ++m) red[m][r0 + w] = v[m];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < NV; ++m) {
+        double s = red[m][r0];
+#pragma unroll
+        for (int x = 1; x < W; ++x) s += red[m][r0 + x];
+        v[m] = s;
+    }
+    if (G == 1) return true;
+    if (t < 2 * NV) {
+        double mine = v[0];
+#pragma unroll
+        for (int m = 1; m < NV; ++m) mine = (t >> 1) == m ? v[m] : mine;
+        const u64 bits = (u64)__double_as_longlong(mine);
+        const u64 half = (t & 1) ? bits >> 32 : bits & 0xffffffffull;
+        dev_store(area + (size_t)g * 2 * NV + t, ((u64)tag << 32) | half);
+    }
+#pragma unroll
+    for (int m = 0; m < NV; ++m) v[m] = 0.0;
+    bool ok = true;
+    // value m of brick b: pair b NV + m of words
+    for (int e = t; e < G * NV; e += kResThreads) {
+        const GLB u64 *src = area + 2 * (size_t)e;
+        u64 lo, hi;
+        for (int n = 0;; ++n) {
+            lo = dev_load(src);
+            hi = dev_load(src + 1);
+            if ((uint32_t)(lo >> 32) == tag && (uint32_t)(hi >> 32) == tag) break;
+            if (n >= kSpin) { ok = false; break; }
+        }
+        const double d = __longlong_as_double((long long)((lo & 0xffffffffull) | (hi << 32)));
+#pragma unroll
+        for (int m = 0; m < NV; ++m)
+            if (e % NV == m) v[m] += d;
+    }
+    if (!ok) *fail = 1;
+#pragma unroll
+    for (int m = 0; m < NV; ++m) v[m] = wave_sum(v[m]);
+    if ((t & 63) == 0) {
+#pragma unroll
+        for (int m = 0; m < NV; ++m) red[m][W + w] = v[m];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < NV; ++m) {
+        double s = red[m][W];
+#pragma unroll
+        for (int x = 1; x < W; ++x) s += red[m][W + x];
+        v[m] = s;
+    }
+    return *fail == 0;
+}
+
+// The operator row of one cell of a column: coefficients from the class
+// nibbles of its code (own, x-, x+, y-, y+, z-, z+), or one coefficient for
+// the whole wave where every cell of the column and its neighbours are of
+// one class (UNI; the x walls of a row then scale it by 0 or 2).
+template <typename T>
+struct Row {
+    T q, dg, s;
+};
+
+template <typename T, bool UNI, bool SUM>
+__device__ __forceinline__ Row<T> cell_row(uint32_t code, const T *tab, T bu, T fxm, T fxp, T &bzm,
+                                           T pc, T xm, T xp, T ym, T yp, T zm, T zp)
+{
+    T bxm, bxp, bym, byp, bzp;
+    if (UNI) {
+        bxm = bu * fxm;
+        bxp = bu * fxp;
+        bym = byp = bzp = bzm = bu;
+    } else {
+        const T *row = tab + (code & 15u) * kClasses;
+        bxm = row[(code >> 4) & 15u];
+        bxp = row[(code >> 8) & 15u];
+        bym = row[(code >> 12) & 15u];
+        byp = row[(code >> 16) & 15u];
+        bzp = row[(code >> 24) & 15u];
+    }
+    const T dxm = pc - xm, dxp = pc - xp, dym = pc - ym, dyp = pc - yp, dzm = pc - zm, dzp = pc - zp;
+    const T txm = bxm * dxm, txp = bxp * dxp, tym = bym * dym, typ = byp * dyp, tzm = bzm * dzm,
+            tzp = bzp * dzp;
+    Row<T> r;
+    r.q = ((txm + txp) + (tym + typ)) + (tzm + tzp);
+    r.dg = ((bxm + bxp) + (bym + byp)) + (bzm + bzp);
+    r.s = T(0);
+    if (SUM) {
+        // each face from its upper cell, and the p = 0 walls above a cell
+        r.s = (txm * dxm + tym * dym) + tzm * dzm;
+        if (UNI) {
+            r.s += fxp == T(2) ? txp * dxp : T(0);
+        } else {
+            r.s += ((code >> 8) & 15u) == (uint32_t)kClsWallD ? txp * dxp : T(0);
+            r.s += ((code >> 16) & 15u) == (uint32_t)kClsWallD ? typ * dyp : T(0);
+            r.s += ((code >> 24) & 15u) == (uint32_t)kClsWallD ? tzp * dzp : T(0);
+        }
+    }
+    bzm = bzp;
+    return r;
+}
+
+}  // namespace
+
+// T: double (FP64 solves) or float (inner solves of FP32 + refinement); NC
+// columns of NZ cells a thread; KEEP: q and the diagonal stay in registers
+// between the two halves of an iteration, else they are formed again (the
+// largest bricks).
+template <typename T, int NC, int NZ, bool KEEP>
+__global__ void __launch_bounds__(kResThreads)
+k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
+{
+    constexpr bool F64 = std::is_same<T, double>::value;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    T *Lp = reinterpret_cast<T *>(smem);
+    __shared__ T tab[kClasses * kClasses];
+    __shared__ double red[2][2 * (kResThreads / 64)];
+    __shared__ int s_fail;
+    const int t = (int)threadIdx.x;
+    int s = s0;
+    while (s + 1 < s1 && slots[s + 1].rblk <= (int)blockIdx.x) ++s;
+    const Slot &S = slots[s];
+    const int g = (int)blockIdx.x - S.rblk, G = S.rnby * S.rnbz;
+    if (!S.resident || g >= G) return;
+    SlotState &st = *S.st;
+    if (st.phase != (F64 ? K1_CG_A : K1_IR_A)) return;
+
+    const int nx = S.nx, ny = S.ny, nz = S.nz, P = nx * ny, bm = S.bcmask;
+    const bool px = (S.permask & 1) && nx > 1, py = (S.permask & 2) && ny > 1;
+    const int j0 = (g % S.rnby) * S.rby, k0 = (g / S.rnby) * NZ;
+    const int by = min(S.rby, ny - j0), bz = min(NZ, nz - k0), C = nx * by;
+    const bool ylo = j0 > 0 || py, yhi = j0 + by < ny || py, zlo = k0 > 0, zhi = k0 + bz < nz;
+    const int RS = nx + 2, PS = (S.rby + 2) * RS;
+    GLB T *zg = gp((T *)S.z), *pg = gp((T *)dir_buf(S, st.pbuf));
+    GLB T *xg = gp(F64 ? (T *)S.x : (T *)S.d32);
+    const GLB uint8_t *gcls = gp(S.cls);
+
+    for (int i = t; i < NZ * PS; i += kResThreads) Lp[i] = T(0);
+    for (int i = t; i < kClasses * kClasses; i += kResThreads)
+        tab[i] = F64 ? (T)gp(S.tab64)[i] : (T)gp(S.tab32)[i];
+    if (t == 0) s_fail = 0;
+    __syncthreads();
+
+    const bool first = st.first != 0;
+    const double tol2 = st.tol2, goal2 = F64 ? 0.0 : st.inner_goal2 * st.rr0_inner;
+    const int maxit = st.maxit, inner_max = st.inner_maxit;
+    int iter = st.iter, inner = st.inner_iter;
+    uint32_t tag = st.repoch;
+    double rz = st.rz, rr = st.rr, pap = st.pap, alpha = st.alpha;
+    double beta = first ? 0.0 : st.beta;
+
+    T z[NC][NZ], x[NC][NZ], pl[NC], ph[NC], q[KEEP ? NC : 1][KEEP ? NZ : 1],
+        dg[KEEP ? NC : 1][KEEP ? NZ : 1];
+    uint32_t code[NC][NZ];
+    int off[NC], gi[NC];
+    uint32_t cflag = 0;   // 4 bits a column: active, i == 0, i == nx - 1, on a y face
+    uint32_t uni = 0;     // columns of one class throughout the wave
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const int col = t + c * kResThreads;
+        const bool act = col < C;
+        const int jl = act ? col / nx : 0, i = act ? col - jl * nx : 0, j = j0 + jl;
+        off[c] = (jl + 1) * RS + i + 1;
+        gi[c] = k0 * P + j * nx + i;
+        const bool yface = (jl == 0 && ylo) || (jl == by - 1 && yhi);
+        cflag |= ((act ? 1u : 0u) | (i == 0 ? 2u : 0u) | (i == nx - 1 ? 4u : 0u) |
+                  (yface ? 8u : 0u)) << (4 * c);
+        const int oxm = i > 0 ? -1 : (px ? nx - 1 : 0), oxp = i < nx - 1 ? 1 : (px ? 1 - nx : 0);
+        const int oym = j > 0 ? -nx : (py ? (ny - 1) * nx : 0);
+        const int oyp = j < ny - 1 ? nx : (py ? -(ny - 1) * nx : 0);
+        bool same = act && bz == NZ;
+        uint32_t kc0 = 0;
+#pragma unroll
+        for (int k = 0; k < NZ; ++k) {
+            const bool in = act && k < bz;
+            const int m = in ? gi[c] + k * P : 0;
+            uint32_t cd = 0x0fffffffu;
+            z[c][k] = x[c][k] = T(0);
+            if (in) {
+                const int kk = k0 + k;
+                const uint32_t kc = gcls[m];
+                auto key = [&](bool there, int o, int wall) -> uint32_t {
+                    if (there) return gcls[m + o];
+                    return (uint32_t)((bm >> wall) & 1 ? kClsWallD : kClsSolid);
+                };
+                const uint32_t w[6] = { key(oxm != 0, oxm, 0), key(oxp != 0, oxp, 1),
+                                        key(oym != 0, oym, 2), key(oyp != 0, oyp, 3),
+                                        key(kk > 0, -P, 4),    key(kk < nz - 1, P, 5) };
+                if (kc != (uint32_t)kClsSolid)
+                    cd = kc | w[0] << 4 | w[1] << 8 | w[2] << 12 | w[3] << 16 | w[4] << 20 | w[5] << 24;
+                z[c][k] = zg[m];
+                x[c][k] = xg[m];
+                if (!first) Lp[off[c] + k * PS] = pg[m];
+            }
+            code[c][k] = cd;
+            // one class throughout, the x walls of the row aside
+            if (k == 0) kc0 = __builtin_amdgcn_readfirstlane(cd) & 15u;
+            uint32_t want = kc0 * 0x1111111u, have = cd;
+            if (i == 0 && !px) { want &= ~0xf0u; have &= ~0xf0u; }
+            if (i == nx - 1 && !px) { want &= ~0xf00u; have &= ~0xf00u; }
+            same = same && kc0 < (uint32_t)kMaxFluidClasses && have == want;
+        }
+        if (__all(same)) uni |= 1u << c;
+        // p of the planes below and above the brick
+        pl[c] = ph[c] = T(0);
+        if (act && !first) {
+            if (zlo) pl[c] = pg[gi[c] - P];
+            if (zhi) ph[c] = pg[gi[c] + NZ * P];
+        }
+    }
+    // the rows beside the brick: cell e of this thread comes from global cell
+    // hg[e] and lives at hl[e] (-1: none)
+    int hg[kResHalo], hl[kResHalo];
+#pragma unroll
+    for (int e = 0; e < kResHalo; ++e) {
+        const int m = t + e * kResThreads, r = m / nx, i = m - r * nx;
+        const int side = r & 1, k = r >> 1;
+        hl[e] = -1;
+        hg[e] = 0;
+        if (k < bz && (side ? yhi : ylo)) {
+            int j = side ? j0 + by : j0 - 1;
+            j = j < 0 ? ny - 1 : (j >= ny ? 0 : j);
+            hg[e] = (k0 + k) * P + j * nx + i;
+            hl[e] = k * PS + (side ? by + 1 : 0) * RS + i + 1;
+            if (!first) Lp[hl[e]] = pg[hg[e]];
+        }
+    }
+    const int nhalo = 2 * bz * nx;   // wave-uniform bound of the halo loops
+    GLB u64 *area1 = gp(S.rsync), *area2 = area1 + 2 * (size_t)G;
+
+    int end = 0;       // 0: budget spent, 1: converged or capped, 2: breakdown, 3: vanished direction
+    for (int n = 0;; ++n) {
+        if (n == budget) break;
+        // p = z + beta p: halo loads first, own cells while they are in flight
+        const T tb = (T)beta;
+        T zl[NC], zh[NC], hz[kResHalo];
+        keep_here(cflag);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            keep_here(gi[c]);
+            keep_here(off[c]);
+            const bool act = (cflag >> (4 * c)) & 1u;
+            zl[c] = zh[c] = T(0);
+            if (zlo && act) zl[c] = dev_load(zg + gi[c] - P);
+            if (zhi && act) zh[c] = dev_load(zg + gi[c] + NZ * P);
+        }
+#pragma unroll
+        for (int e = 0; e < kResHalo; ++e) {
+            hz[e] = T(0);
+            keep_here(hg[e]);
+            keep_here(hl[e]);
+            if (e * kResThreads < nhalo && hl[e] >= 0) hz[e] = dev_load(zg + hg[e]);
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const uint32_t f = cflag >> (4 * c);
+            if (f & 1u) {
+#pragma unroll
+                for (int k = 0; k < NZ; ++k) {
+                    T *a = Lp + off[c] + k * PS;
+                    const T pn = z[c][k] + tb * *a;
+                    *a = pn;
+                    if (px && (f & 2u)) a[nx] = pn;
+                    if (px && (f & 4u)) a[-nx] = pn;
+                }
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            pl[c] = zl[c] + tb * pl[c];
+            ph[c] = zh[c] + tb * ph[c];
+        }
+#pragma unroll
+        for (int e = 0; e < kResHalo; ++e)
+            if (e * kResThreads < nhalo && hl[e] >= 0) Lp[hl[e]] = hz[e] + tb * Lp[hl[e]];
+        __syncthreads();
+
+        // q = A p and p.A p
+        double sum[2] = { 0.0, 0.0 };
+        auto column = [&](auto U, auto SUM, int c, auto &&each) __attribute__((always_inline)) {
+            constexpr bool kU = decltype(U)::value, kS = decltype(SUM)::value;
+            keep_here(off[c]);
+            keep_here(cflag);
+            const T *a = Lp + off[c];
+            const uint32_t f = cflag >> (4 * c);
+            T bu = T(0), fxm = T(1), fxp = T(1);
+            if (kU) {
+                bu = tab[(__builtin_amdgcn_readfirstlane(code[c][0]) & 15u) * (kClasses + 1)];
+                if (!px && (f & 2u)) fxm = bm & 1 ? T(2) : T(0);
+                if (!px && (f & 4u)) fxp = bm & 2 ? T(2) : T(0);
+            }
+            T zm = pl[c], pc = a[0];
+            T bzm = kU ? bu : tab[(code[c][0] & 15u) * kClasses + ((code[c][0] >> 20) & 15u)];
+#pragma unroll
+            for (int k = 0; k < NZ; ++k) {
+                const T *b = a + k * PS;
+                keep_here(code[c][k]);
+                const T zp = k + 1 < NZ ? b[PS] : ph[c];
+                const Row<T> r = cell_row<T, kU, kS>(code[c][k], tab, bu, fxm, fxp, bzm, pc, b[-1],
+                                                     b[1], b[-RS], b[RS], zm, zp);
+                each(c, k, r, pc);
+                // above the grid's last plane there is no cell to share a face with
+                if (!kU) bzm = k + 1 < bz ? bzm : T(0);
+                zm = pc;
+                pc = zp;
+            }
+        };
+        using Yes = std::integral_constant<bool, true>;
+        using No = std::integral_constant<bool, false>;
+        auto first_half = [&](int c, int k, const Row<T> &r, T) __attribute__((always_inline)) {
+            sum[0] += (double)r.s;
+            if constexpr (KEEP) { q[c][k] = r.q; dg[c][k] = r.dg; }
+        };
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if ((uni >> c) & 1u) column(Yes{}, Yes{}, c, first_half);
+            else column(No{}, Yes{}, c, first_half);
+        }
+        double v1[1] = { sum[0] };
+        if (!all_sum<1>(v1, area1, G, g, ++tag, red, &s_fail)) break;
+        pap = v1[0];
+        if (!isfinite(pap) || !(pap > 0.0)) { end = (F64 || !isfinite(pap)) ? 2 : 3; break; }
+        alpha = rz / pap;
+
+        // x += alpha p, z -= alpha q / diag, the faces of z, r.z and r.r
+        const T ta = (T)alpha;
+        keep_here(cflag);
+        double v2[2] = { 0.0, 0.0 };
+        auto second_half = [&](int c, int k, const Row<T> &r, T pc) __attribute__((always_inline)) {
+            const T inv = r.dg > T(0) ? recip(r.dg) : T(0);   // hull rows keep z = 0
+            const T zn = z[c][k] - ta * r.q * inv;
+            z[c][k] = zn;
+            x[c][k] = fma(ta, pc, x[c][k]);
+            const double res = (double)r.dg * (double)zn;
+            v2[0] += res * (double)zn;
+            v2[1] += res * res;
+            const uint32_t f = cflag >> (4 * c);
+            if ((f & 1u) && k < bz &&
+                ((f & 8u) || (k == 0 && zlo) || (k == NZ - 1 && zhi)))
+                dev_store(zg + gi[c] + k * P, zn);
+        };
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            keep_here(gi[c]);
+            keep_here(off[c]);
+            if constexpr (KEEP) {
+#pragma unroll
+                for (int k = 0; k < NZ; ++k)
+                    second_half(c, k, Row<T>{ q[c][k], dg[c][k], T(0) }, Lp[off[c] + k * PS]);
+            } else {
+                if ((uni >> c) & 1u) column(Yes{}, No{}, c, second_half);
+                else column(No{}, No{}, c, second_half);
+            }
+        }
+        // the faces have reached memory before this workgroup's sums go out
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (!all_sum<2>(v2, area2, G, g, ++tag, red, &s_fail)) break;
+        beta = v2[0] / rz;
+        rz = v2[0];
+        rr = v2[1];
+        ++iter;
+        ++inner;
+        if (!isfinite(rr) || (F64 && !isfinite(rz))) { end = 2; break; }
+        if (F64 ? (rr <= tol2 || iter >= maxit)
+                : (rr <= goal2 || inner >= inner_max || iter >= maxit)) { end = 1; break; }
+    }
+    if (s_fail) {
+        if (t == 0) dev_store(gp(&st.rfail), 1);
+        return;
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        if ((cflag >> (4 * c)) & 1u) {
+#pragma unroll
+            for (int k = 0; k < NZ; ++k)
+                if (k < bz) {
+                    const int m = gi[c] + k * P;
+                    zg[m] = z[c][k];
+                    xg[m] = x[c][k];
+                    pg[m] = Lp[off[c] + k * PS];
+                }
+        }
+    }
+    if (g == 0 && t == 0) {
+        st.rz = rz;
+        st.rr = rr;
+        st.pap = pap;
+        st.alpha = alpha;
+        st.beta = beta;
+        st.iter = iter;
+        st.inner_iter = inner;
+        st.first = 0;
+        st.repoch = tag;
+        if (end == 2) {
+            st.status = PCG_EBREAKDOWN;
+            st.phase = PH_DONE;
+        } else if (F64) {
+            if (end == 1) st.phase = K1_CHECK64;
+        } else if (end) {
+            // refine (a vanished direction too)
+            st.scale = pow2_scale(sqrt(st.rr_true * st.inner_tol2));
+            st.phase = K1_IR_RESID;
+        }
+    }
+}
+
+namespace {
+struct Entry {
+    ResidentShape shape;
+    const void *fn;
+};
+template <typename T, int NC, int NZ, bool KEEP>
+Entry entry()
+{
+    return { { NC, NZ }, (const void *)k_resident<T, NC, NZ, KEEP> };
+}
+// Shapes by cells a thread.  FP64 keeps q and the diagonal in registers up
+// to 16 cells, FP32 up to 32 (256 registers a thread with two waves a SIMD).
+const Entry kF64[] = {
+    entry<double, 1, 1, true>(), entry<double, 1, 2, true>(), entry<double, 1, 4, true>(),
+    entry<double, 2, 4, true>(), entry<double, 1, 8, true>(), entry<double, 2, 8, true>(),
+    entry<double, 4, 4, true>(), entry<double, 3, 8, false>(), entry<double, 5, 6, false>(),
+    entry<double, 4, 8, false>(),
+};
+const Entry kF32[] = {
+    entry<float, 1, 1, true>(), entry<float, 1, 2, true>(), entry<float, 1, 4, true>(),
+    entry<float, 2, 4, true>(), entry<float, 1, 8, true>(), entry<float, 2, 8, true>(),
+    entry<float, 4, 4, true>(), entry<float, 4, 8, true>(), entry<float, 6, 8, false>(),
+};
+}  // namespace
+
+int resident_shapes(int family, ResidentShape *out, int cap)
+{
+    const Entry *t = family == PCG_PREC_FP64 ? kF64 : kF32;
+    const int n = family == PCG_PREC_FP64 ? (int)(sizeof(kF64) / sizeof(Entry))
+                                          : (int)(sizeof(kF32) / sizeof(Entry));
+    for (int i = 0; i < n && i < cap; ++i) out[i] = t[i].shape;
+    return n;
+}
+
+// One launch of the resident kernel of shape `shape` over slots [s0, s1) of
+// the table: `blocks` workgroups, all resident at once, `lds` bytes each.
+hipError_t launch_resident(int family, int shape, int blocks, unsigned lds, const Slot *slots,
+                           int s0, int s1, int budget, hipStream_t s)
+{
+    const void *fn = (family == PCG_PREC_FP64 ? kF64 : kF32)[shape].fn;
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    void *args[] = { (void *)&slots, (void *)&s0, (void *)&s1, (void *)&budget };
+    return hipLaunchCooperativeKernel(fn, dim3((unsigned)blocks), dim3(kResThreads), args, lds, s);
+}
+
+}  // namespace pcgmi
