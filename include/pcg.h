@@ -163,9 +163,9 @@ enum {
  *   precision   PCG_PREC_FP64 [default] or PCG_PREC_FP32_IR: FP32 stencil
  *               and vectors inside, FP64 residual, dot products, alpha/beta
  *               and solution update (iterative refinement).
- *   check_every iterations per captured graph replay between host polls [32];
- *               a grid that fits on the chip takes this many iterations before
- *               the first poll, twice as many before the second, then more
+ *   check_every iterations per captured graph replay between host polls [32]
+ *               (a single solve that fits on the chip is polled when its
+ *               iterations have ended)
  *   flags       PCG_WARM_START | PCG_SKIP_CONNECTIVITY_CHECK |
  *               PCG_NO_DENSITY_CLASSES | PCG_FRACTIONS | PCG_FLAT_TILES |
  *               PCG_PLANE_TILES | PCG_TWO_SWEEPS

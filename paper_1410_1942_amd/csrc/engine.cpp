@@ -48,6 +48,7 @@ hipError_t static_scratch(void **ptr, size_t *bytes);
 // The resident kernel (resident.hip); weak, so that the host engine also
 // links without its device side (then no solve is resident).
 __attribute__((weak)) int resident_shapes(int family, ResidentShape *out, int cap);
+__attribute__((weak)) hipError_t resident_occupancy(int family, int shape, unsigned lds, int *wgs);
 __attribute__((weak)) hipError_t launch_resident(int family, int shape, int blocks, unsigned lds,
                                                  const Slot *slots, int s0, int s1, int budget,
                                                  hipStream_t s);
@@ -366,43 +367,50 @@ struct ResidentPlan {
     int bricks() const { return rnby * rnbz; }
 };
 
-// One brick a CU, all at once.
-constexpr int kResMaxBricks = 256;
+// The bricks of a grid in one shape; shape -1 when they do not hold it.
+ResidentPlan resident_bricks(const pcg_grid_t &g, int prec, const ResidentShape &sh, int index)
+{
+    ResidentPlan p;
+    const int64_t cols = (int64_t)sh.cols * kResThreads;
+    if (g.nx > cols) return p;
+    p.rbz = sh.planes;
+    p.rnbz = (g.nz + p.rbz - 1) / p.rbz;
+    p.rby = (int)std::min<int64_t>(g.ny, cols / g.nx);
+    p.rnby = (g.ny + p.rby - 1) / p.rby;
+    p.rby = (g.ny + p.rnby - 1) / p.rnby;      // bricks of even height
+    p.rnby = (g.ny + p.rby - 1) / p.rby;
+    const size_t es = prec == PCG_PREC_FP32_IR ? 4 : 8;
+    const size_t lds = (size_t)p.rbz * (p.rby + 2) * (g.nx + 2) * es;
+    if ((int64_t)2 * p.rbz * g.nx > res_halo(sh.cols * sh.planes) * kResThreads || lds > kResLds) return p;
+    // the exchange words live in the second direction buffer
+    if ((size_t)p.rnby * p.rnbz * kResWords * 8 > es * g.nx * g.ny * g.nz) return p;
+    p.lds = (unsigned)align_up(lds, 16);
+    p.shape = index;
+    return p;
+}
 
-// The resident form of a grid: single solves with no tile form asked for,
-// where the bricks' registers and LDS hold the whole grid.  Of the shapes
-// that do, the one of the least estimated time an iteration.
-ResidentPlan resident_plan(const pcg_grid_t &g, int prec, const pcg_opts_t &o, bool batch)
+// The resident form of a grid, where one exists: no tile form asked for, and
+// the bricks of a shape (cap[i] of shape i fit on the device at once) hold
+// the whole grid.  A single solve takes the shape of the least estimated
+// time an iteration.  Solves of a batch share launches, so all of a
+// precision take the batch's shape, or the largest where that one does not
+// hold the grid.
+ResidentPlan resident_plan(const pcg_grid_t &g, int prec, const pcg_opts_t &o, bool batch,
+                           const ResidentShape *sh, const int *cap, int n)
 {
     ResidentPlan best;
-    if (!resident_shapes || batch || o.tz > 0 || o.grid_blocks > 0) return best;
+    if (o.tz > 0 || o.grid_blocks > 0) return best;
     if (o.flags & (PCG_FRACTIONS | PCG_FLAT_TILES | PCG_PLANE_TILES | PCG_TWO_SWEEPS |
                    PCG_NARROW_TILES))
         return best;
-    ResidentShape sh[32];
-    const int n = std::min(32, resident_shapes(prec, sh, 32));
-    const size_t es = prec == PCG_PREC_FP32_IR ? 4 : 8;
     double cost = 0.0;
     for (int i = 0; i < n; ++i) {
-        const int64_t cols = (int64_t)sh[i].cols * kResThreads;
-        if (g.nx > cols) continue;
-        ResidentPlan p;
-        p.shape = i;
-        p.rbz = sh[i].planes;
-        p.rnbz = (g.nz + p.rbz - 1) / p.rbz;
-        p.rby = (int)std::min<int64_t>(g.ny, cols / g.nx);
-        p.rnby = (g.ny + p.rby - 1) / p.rby;
-        p.rby = (g.ny + p.rnby - 1) / p.rnby;      // bricks of even height
-        p.rnby = (g.ny + p.rby - 1) / p.rby;
-        if ((int64_t)p.rnby * p.rnbz > kResMaxBricks) continue;
-        if ((int64_t)2 * p.rbz * g.nx > kResHalo * kResThreads) continue;
-        // the exchange words live in the second direction buffer
-        if ((size_t)p.bricks() * kResWords * 8 > es * g.nx * g.ny * g.nz) continue;
-        const size_t lds = (size_t)p.rbz * (p.rby + 2) * (g.nx + 2) * es;
-        if (lds > kResLds) continue;
-        p.lds = (unsigned)align_up(lds, 16);
-        const double c = (p.bricks() > 1 ? 3.5 + 0.006 * p.bricks() : 0.0) +
-                         0.1 * sh[i].cols * sh[i].planes;
+        if (batch && !sh[i].batch) continue;
+        const ResidentPlan p = resident_bricks(g, prec, sh[i], i);
+        if (p.shape < 0 || p.bricks() > cap[i]) continue;
+        if (batch) return p;
+        const double c = (p.bricks() > 1 ? 4.0 + 0.008 * p.bricks() : 0.0) +
+                         (sh[i].keep ? 0.37 : 0.67) * sh[i].cols * sh[i].planes;
         if (best.shape < 0 || c < cost) { best = p; cost = c; }
     }
     return best;
@@ -653,7 +661,9 @@ struct SlotHost {
     ResidentPlan res;            // resident form, if the grid has one
     unsigned long long *rsync = nullptr;   // its exchange words
     bool resident = false;       // the running solve takes it
-    int rsteps = 0;              // polling steps of the running solve
+    // of the running solve: its next stage, the trips since the host last
+    // waited, and the waits
+    int rstage = 0, rtrips = 0, rwaits = 0;
     const double *rhs = nullptr;
     double *x = nullptr;
     Clock::time_point t0;
@@ -721,8 +731,19 @@ struct Engine {
     bool k2only = false;    // second-half launches only (every solve in one sweep)
     int graph_k2only = -1;  // the same for the captured graph
     pcg_opts_t opts{};      // as given (zero: defaults)
-    int cus = 0;            // compute units of the device
+    // shapes of the resident kernel and the bricks of each the device holds
+    static constexpr int kMaxShapes = 32;
+    ResidentShape rshapes[kMaxShapes];
+    int rcap[kMaxShapes] = {};
+    int nshapes = 0;
     int nresident = 0;      // running solves in the resident kernel
+    // its launches: slots [s0, s1) of the table, one shape, all at once
+    struct ResidentLaunch {
+        int shape, s0, s1, blocks;
+        unsigned lds;
+    };
+    std::vector<ResidentLaunch> rlaunch;
+    bool looked = false;    // the last step refreshed the host's states
     int fail_after = 0;     // test hook: the step call that reports a failure
     HostMirror *mirror = nullptr;  // caller-owned host mirrors: no pinned memory,
                                    // no capture stream, launches without graphs
@@ -812,9 +833,21 @@ struct Engine {
         HIP_TRY(hipMemcpyAsync(d_hdr, h_hdr, sizeof(BatchHeader), hipMemcpyHostToDevice, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         if (!mirror) HIP_TRY(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
-        int dev = 0;
-        HIP_TRY(hipGetDevice(&dev));
-        HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        if (resident_shapes) {
+            int dev = 0, cus = 0, coop = 0;
+            HIP_TRY(hipGetDevice(&dev));
+            HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+            HIP_TRY(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
+            nshapes = coop ? std::min(kMaxShapes, resident_shapes(prec, rshapes, kMaxShapes)) : 0;
+            // one brick a CU for single solves, whose exchanges grow with the
+            // bricks; batches fill what fits
+            for (int i = 0; i < nshapes; ++i) {
+                int wgs = 1;
+                if (is_batch)
+                    HIP_TRY(resident_occupancy(prec, i, kResLds / (rshapes[i].batch > 0 ? rshapes[i].batch : 1), &wgs));
+                rcap[i] = cus * (is_batch ? std::min(wgs, rshapes[i].batch) : 1);
+            }
+        }
         return PCG_OK;
     }
 
@@ -915,7 +948,7 @@ struct Engine {
         const bool sweep = one_sweep(geo, prec, flags | this->flags);
         pcg_opts_t ro = opts;
         ro.flags |= flags;
-        const ResidentPlan res = resident_plan(*grid_, prec, ro, batch_mode());
+        const ResidentPlan res = resident_plan(*grid_, prec, ro, batch_mode(), rshapes, rcap, nshapes);
         const size_t need = slot_bytes(geo, prec, frac_space, sweep);
         size_t off = 0;
         if (!alloc.alloc(need, &off)) return max_slots == 1 ? PCG_ENOMEM : PCG_EBUSY;
@@ -955,7 +988,7 @@ struct Engine {
         }
         // the resident kernel uses one direction buffer; its exchange words
         // live in the next, which every solve's set-up action zeroes
-        if (res.shape >= 0 && res.bricks() <= cus) {
+        if (res.shape >= 0) {
             S.res = res;
             S.rsync = (unsigned long long *)S.dir1;
         }
@@ -1115,7 +1148,7 @@ struct Engine {
         h.warm = (flags & PCG_WARM_START) ? 1 : 0;
         // classes on grids with a resident form, unless each launch is timed
         S.resident = S.res.shape >= 0 && S.classes && !S.has_frac && !timing;
-        S.rsteps = 0;
+        S.rstage = S.rtrips = S.rwaits = 0;
         h.resident = S.resident ? 1 : 0;
         h.fused = S.z2 && !S.resident ? 1 : 0;
         h.scale = 1.0;
@@ -1144,10 +1177,18 @@ struct Engine {
         int ns = 0;
         int m = 0;
         bool all_fused = true;
-        int nres = 0, rblk = 0;
-        for (int id = 0; id < max_slots; ++id) {
+        // resident solves first, by shape: a launch takes a run of the table
+        std::vector<int> order;
+        for (int id = 0; id < max_slots; ++id)
+            if (slots[id].used && slots[id].running) order.push_back(id);
+        std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+            auto key = [&](int id) { return slots[id].resident ? slots[id].res.shape : kMaxShapes; };
+            return key(a) < key(b);
+        });
+        rlaunch.clear();
+        int nres = 0;
+        for (int id : order) {
             SlotHost &S = slots[id];
-            if (!S.used || !S.running) continue;
             Slot &d = h_slots[ns++];
             std::memset(&d, 0, sizeof(Slot));
             d.nx = S.geo.nx; d.ny = S.geo.ny; d.nz = S.geo.nz;
@@ -1179,15 +1220,22 @@ struct Engine {
             set_frac(d, S);
             d.tab64 = S.tab64;
             d.tab32 = S.tab32;
-            d.rblk = rblk;
             if (S.resident) {
+                const ResidentPlan &r = S.res;
+                if (rlaunch.empty() || rlaunch.back().shape != r.shape ||
+                    rlaunch.back().blocks + r.bricks() > rcap[r.shape])
+                    rlaunch.push_back({ r.shape, ns - 1, ns - 1, 0, 0u });
+                ResidentLaunch &q = rlaunch.back();
+                d.rblk = q.blocks;
+                q.s1 = ns;
+                q.blocks += r.bricks();
+                q.lds = std::max(q.lds, r.lds);
                 d.resident = 1;
                 d.rby = S.res.rby;
                 d.rbz = S.res.rbz;
                 d.rnby = S.res.rnby;
                 d.rnbz = S.res.rnbz;
                 d.rsync = S.rsync;
-                rblk += S.res.bricks();
                 ++nres;
             }
             m |= 1 << slot_mode(S);
@@ -1329,50 +1377,89 @@ struct Engine {
     }
 
     // The set-up, residual and update actions of resident solves: n launches,
-    // each taking every solve's next one.
+    // each taking every solve's next one.  (Without other solves there is no
+    // pass A to launch for the further coefficient modes.)
     hipError_t launch_actions(int n)
     {
         hipError_t e = hipSuccess;
-        for (int i = 0; i < n && e == hipSuccess; ++i)
-            e = k2only ? launch_position(2, stream) : launch_iteration(stream);
+        for (int i = 0; i < n && e == hipSuccess; ++i) {
+            if (!k2only) e = launch_iter(prec, 3, __builtin_ctz(modes), grid, d_hdr, d_slots, stream);
+            if (e == hipSuccess) e = launch_position(2, stream);
+        }
         return e;
     }
 
-    // One polling step of a single resident solve: the actions it is waiting
-    // for, its iterations, and the actions after them.  A solve takes
-    // check_every iterations in the first step, twice that in the second and
-    // then up to kResBudget (FP32 + refinement: to the end of its inner solve,
-    // one trip a step).  A step costs about 40 us beside its iterations (the
-    // cooperative launch 20), which 32 iterations of a small grid (130 us)
-    // would not hide.
-    static constexpr int kResBudget = 4096;
-    int resident_step()
+    // Actions a resident solve takes before its iterations go on, from the
+    // phase the host saw last; `pair`: a launch of actions is one of each half.
+    static int actions_before(int phase, bool ir, bool singular, bool pair)
     {
-        int id = 0;
-        while (!slots[id].resident || !slots[id].running) ++id;
-        SlotHost &S = slots[id];
+        switch (phase) {
+        case K1_CHECK64: return singular ? 3 - pair : 1;
+        case K1_MEAN_B: return ir ? 4 - pair : 2;
+        case K1_INIT64: return 1;
+        case K1_IR_INIT: return 3 - pair;
+        case K1_IR_RESID: return 2 - pair;
+        case K1_CG_A: case K1_IR_A: return 0;
+        default: return 3;
+        }
+    }
+
+    // One polling step of the resident solves: the actions they are waiting
+    // for, and check_every iterations.
+    int resident_step(bool others)
+    {
         const bool ir = prec == PCG_PREC_FP32_IR;
         int pre = 0;
-        switch (h_states[id].phase) {
-        case K1_MEAN_B: pre = ir ? 4 : 2; break;
-        case K1_INIT64: pre = 1; break;
-        case K1_IR_INIT: pre = 3; break;
-        case K1_CG_A: case K1_IR_A: break;
-        default: pre = 3;
+        for (int id = 0; id < max_slots; ++id) {
+            SlotHost &S = slots[id];
+            if (!S.used || !S.running || !S.resident) continue;
+            pre = std::max(pre, actions_before(h_states[id].phase, ir, S.singular, !k2only));
         }
-        int budget = kResBudget;
-        if (S.rsteps < 2) budget = std::min(budget, check_every << S.rsteps);
-        ++S.rsteps;
-        HIP_TRY(launch_actions(pre));
-        HIP_TRY(launch_resident(prec, S.res.shape, S.res.bricks(), S.res.lds, d_slots, 0, nrunning,
-                                budget, stream));
-        HIP_TRY(launch_actions((ir ? 2 : 1) + (S.singular ? 2 : 0)));
+        if (!others) HIP_TRY(launch_actions(pre));   // else the others' launches took them
+        for (const ResidentLaunch &q : rlaunch)
+            HIP_TRY(launch_resident(prec, q.shape, q.blocks, q.lds, d_slots, q.s0, q.s1,
+                                    check_every, stream));
+        return PCG_OK;
+    }
+
+    // The same for a context's one solve, a stage a step: the actions before
+    // its iterations, up to kResBudget iterations (FP32 + refinement: an inner
+    // solve), the actions after them.  The host waits after the last of these
+    // only (and with refinement not before the trips its tolerance needs at
+    // least): a wait and a start cost about 40 us, six iterations of a small
+    // grid.  *wait: whether this step ends with a look at the state.
+    static constexpr int kResBudget = 4096;
+    int resident_stage(bool *wait)
+    {
+        const bool ir = prec == PCG_PREC_FP32_IR;
+        SlotHost *S = nullptr;
+        for (auto &q : slots)
+            if (q.used && q.running) S = &q;
+        const SlotState &h = h_states[S - slots.data()];
+        *wait = false;
+        if (S->rstage == 0) {
+            if (S->rtrips == 0) HIP_TRY(launch_actions(actions_before(h.phase, ir, S->singular, !k2only)));
+        } else if (S->rstage == 1) {
+            const ResidentLaunch &q = rlaunch[0];
+            HIP_TRY(launch_resident(prec, q.shape, q.blocks, q.lds, d_slots, q.s0, q.s1, kResBudget,
+                                    stream));
+        } else {
+            HIP_TRY(launch_actions((ir ? 2 - !k2only : 1) + (S->singular ? 2 - !k2only : 0)));
+            const double trips = ir ? std::log(h.tol) / (0.5 * std::log(h.inner_tol2)) : 0.0;
+            *wait = S->rwaits > 0 || ++S->rtrips >= trips;
+        }
+        S->rstage = (S->rstage + 1) % 3;
+        if (*wait) {
+            ++S->rwaits;
+            S->rtrips = 0;
+        }
         return PCG_OK;
     }
 
     // Run `replays` graphs (or timed chunks), then refresh the status mirror.
     int step(int replays)
     {
+        looked = false;
         if (fail_after > 0 && --fail_after == 0) {
             g_hip_err = "failure injected by pcg_inject_failure";
             return PCG_EHIP;
@@ -1380,16 +1467,15 @@ struct Engine {
         int st = upload_table();
         if (st) return st;
         if (nrunning == 0) return PCG_OK;
-        if (mirror || nresident) {
+        const bool others = nrunning > nresident;
+        if (mirror || !others) {
             grid = choose_grid();    // launched directly: no graph to capture
         } else {
             st = capture();
             if (st) return st;
         }
         for (int r = 0; r < replays; ++r) {
-            if (nresident) {
-                st = resident_step();
-                if (st) return st;
+            if (!others) {
             } else if (timing) {
                 st = timed_chunk();
                 if (st) return st;
@@ -1398,10 +1484,19 @@ struct Engine {
             } else {
                 HIP_TRY(hipGraphLaunch(exec, stream));
             }
+            if (nresident && max_slots == 1 && !is_batch) {
+                bool wait = false;
+                st = resident_stage(&wait);
+                if (st || !wait) return st;
+            } else if (nresident) {
+                st = resident_step(others);
+                if (st) return st;
+            }
         }
         HIP_TRY(hipMemcpyAsync(h_states, d_states, sizeof(SlotState) * max_slots,
                                hipMemcpyDeviceToHost, stream));
         HIP_TRY(hipStreamSynchronize(stream));
+        looked = true;
         for (int id = 0; id < max_slots; ++id) {
             SlotHost &S = slots[id];
             if (!S.used || !S.running) continue;
@@ -1474,6 +1569,7 @@ int run_to_end(Engine &eng, int slot, Clock::time_point t0, pcg_stats_t *stats)
     while (eng.slots[slot].running) {
         const int st = eng.step(1);
         if (st) return fail(st);
+        if (!eng.looked) continue;
         const SlotState &h = eng.h_states[slot];
         if (h.iter == last_iter && h.phase == last_phase) {
             if (++still >= 4) {

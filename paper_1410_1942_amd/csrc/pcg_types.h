@@ -20,18 +20,23 @@ constexpr int kTileY = 4;
 // Bytes of the device array behind the allocation-free entry point.
 constexpr unsigned long long kStaticScratchBytes = 64ull << 20;
 
-// Resident form: threads of a workgroup, the most y-halo cells of a brick a
-// thread carries, 8-byte words a brick exchanges through (four for the sums
-// after the update, two for p.A p, each half a double beside a 32-bit tag),
-// and the most LDS a brick may take (of 160 KiB a CU, less the kernel's tables).
+// Resident form: threads of a workgroup, 8-byte words a brick exchanges
+// through (four for the sums after the update, two for p.A p, each half a
+// double beside a 32-bit tag), the most LDS a brick may take (of 160 KiB a
+// CU, less the kernel's tables), and the most values of the rows beside its
+// brick a thread carries, by its cells.
 constexpr int kResThreads = 512;
-constexpr int kResHalo = 8;
 constexpr int kResWords = 6;
 constexpr unsigned kResLds = 160u * 1024u - 4096u;
+constexpr int res_halo(int cells) { return cells <= 2 ? 2 : cells <= 8 ? 4 : 8; }
 
-// A shape of the resident kernel: cols columns of planes cells a thread.
+// A shape of the resident kernel: cols columns of planes cells a thread;
+// whether the row's results stay in registers between the halves of an
+// iteration; in batches the workgroups a CU holds of it (0: not for batches).
 struct ResidentShape {
     int cols, planes;
+    bool keep;
+    int batch;
 };
 
 // Density classes: up to kMaxFluidClasses distinct fluid densities get a

@@ -15,11 +15,13 @@
 //
 // What bounds it: the two exchanges, about 1.5 us each across the eight XCDs
 // (a store that reaches memory, a load that sees it), and for bricks of many
-// cells their LDS traffic, 56 to 96 B a cell.  A launch per iteration instead
-// waits for memory plane after plane and streams 41 B a cell.  Measured per
-// iteration, launches against this: FP64 32^3 15.9 -> 6.8 us, 64^3 22.3 -> 8.1,
-// 101 x 77 x 59 32.5 -> 10.1, 128^3 45.0 -> 15.4, 320 x 128 x 96 90.0 -> 34.9;
-// FP32 32^3 16.0 -> 7.0, 64^3 21.4 -> 7.7, 128^3 48.5 -> 12.9.
+// cells their LDS reads and arithmetic (40 B and about 60 vector instructions
+// a cell).  A launch per iteration instead waits for memory plane after plane
+// and streams 41 B a cell.  Measured per iteration of a whole solve, launches
+// against this: FP64 32^3 16.4 -> 5.9 us, 64^3 21.7 -> 7.4, 101 x 77 x 59 32.6
+// -> 8.4, 128^3 44.7 -> 15.0, 150 x 141 x 133 98 -> 22, 320 x 128 x 96 90 -> 35;
+// FP32 32^3 16.4 -> 6.1, 64^3 21.7 -> 7.5, 128^3 48.6 -> 12.5, 320 x 128 x 96
+// 65.6 -> 20.1.
 //
 // Exchange: a workgroup's sums go out as words of half a double beside a
 // 32-bit tag, the number of the exchange, written and read with relaxed
@@ -65,11 +67,38 @@ __device__ __forceinline__ void dev_store(GLB T *p, T v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ double wave_sum(double v)
+// Lane i - d's value of v (0 where there is none) through the data-parallel
+// path of the vector unit: a shuffle through LDS takes several times as long.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    typedef int i2 __attribute__((ext_vector_type(2)));
+    i2 h = __builtin_bit_cast(i2, v);
+    h.x = __builtin_amdgcn_update_dpp(0, h.x, CTRL, ROWS, 0xf, false);
+    h.y = __builtin_amdgcn_update_dpp(0, h.y, CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(double, h);
+}
+
+// Sum over the wave, in lane 63: within rows of 16 lanes (shifts by 1, 2, 4,
+// 8), then from row to row.
+__device__ __forceinline__ double wave_sum63(double v)
+{
+    v += dpp<0x111, 0xf>(v);
+    v += dpp<0x112, 0xf>(v);
+    v += dpp<0x114, 0xf>(v);
+    v += dpp<0x118, 0xf>(v);
+    v += dpp<0x142, 0xa>(v);
+    v += dpp<0x143, 0xc>(v);
     return v;
+}
+
+__device__ __forceinline__ double lane63(double v)
+{
+    typedef int i2 __attribute__((ext_vector_type(2)));
+    i2 h = __builtin_bit_cast(i2, v);
+    h.x = __builtin_amdgcn_readlane(h.x, 63);
+    h.y = __builtin_amdgcn_readlane(h.y, 63);
+    return __builtin_bit_cast(double, h);
 }
 
 __device__ __forceinline__ double recip(double d)
@@ -99,31 +128,36 @@ __device__ double pow2_scale(double norm)
 template <typename V>
 __device__ __forceinline__ void keep_here(V &v) { asm volatile("" : "+v"(v)); }
 
+constexpr int kWaves = kResThreads / 64;
+
+// The eight waves' values of v at red, added pairwise.
+__device__ __forceinline__ double add_waves(const double *red)
+{
+    static_assert(kWaves == 8, "eight waves");
+    return ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
+}
+
 // Sum NV values over the workgroups of a solve: every thread brings its part
-// and leaves with the total, added in an order fixed by the bricks.  False
-// when a workgroup did not answer.
+// and leaves with the total, added in an order fixed by the bricks.  The
+// workgroup's earlier stores have reached memory before its sums go out.
+// False when a workgroup did not answer.
 template <int NV>
 __device__ __forceinline__ bool all_sum(double (&v)[NV], GLB u64 *area, int G, int g, uint32_t tag,
-                                        double (*red)[2 * (kResThreads / 64)], int *fail)
+                                        double (*red)[4 * kWaves], int *fail)
 {
-    constexpr int W = kResThreads / 64;
-    const int t = (int)threadIdx.x, w = t >> 6;
-    // a lone workgroup passes one barrier a call: calls alternate the halves
-    const int r0 = G == 1 && (tag & 1) ? W : 0;
+    const int t = (int)threadIdx.x, w = t >> 6, lane = t & 63;
+    // calls alternate the halves: a wave may still read the last call's
+    const int r0 = (tag & 1) ? 2 * kWaves : 0;
 #pragma unroll
-    for (int m = 0; m < NV; ++m) v[m] = wave_sum(v[m]);
-    if ((t & 63) == 0) {
+    for (int m = 0; m < NV; ++m) v[m] = wave_sum63(v[m]);
+    if (lane == 63) {
 #pragma unroll
         for (int m = 0; m < NV; ++m) red[m][r0 + w] = v[m];
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 #pragma unroll
-    for (int m = 0; m < NV; ++m) {
-        double s = red[m][r0];
-#pragma unroll
-        for (int x = 1; x < W; ++x) s += red[m][r0 + x];
-        v[m] = s;
-    }
+    for (int m = 0; m < NV; ++m) v[m] = add_waves(red[m] + r0);
     if (G == 1) return true;
     if (t < 2 * NV) {
         double mine = v[0];
@@ -153,19 +187,14 @@ __device__ __forceinline__ bool all_sum(double (&v)[NV], GLB u64 *area, int G, i
     }
     if (!ok) *fail = 1;
 #pragma unroll
-    for (int m = 0; m < NV; ++m) v[m] = wave_sum(v[m]);
-    if ((t & 63) == 0) {
+    for (int m = 0; m < NV; ++m) v[m] = wave_sum63(v[m]);
+    if (lane == 63) {
 #pragma unroll
-        for (int m = 0; m < NV; ++m) red[m][W + w] = v[m];
+        for (int m = 0; m < NV; ++m) red[m][r0 + kWaves + w] = v[m];
     }
     __syncthreads();
 #pragma unroll
-    for (int m = 0; m < NV; ++m) {
-        double s = red[m][W];
-#pragma unroll
-        for (int x = 1; x < W; ++x) s += red[m][W + x];
-        v[m] = s;
-    }
+    for (int m = 0; m < NV; ++m) v[m] = add_waves(red[m] + r0 + kWaves);
     return *fail == 0;
 }
 
@@ -228,10 +257,11 @@ __global__ void __launch_bounds__(kResThreads)
 k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
 {
     constexpr bool F64 = std::is_same<T, double>::value;
+    constexpr int NH = res_halo(NC * NZ);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     T *Lp = reinterpret_cast<T *>(smem);
     __shared__ T tab[kClasses * kClasses];
-    __shared__ double red[2][2 * (kResThreads / 64)];
+    __shared__ double red[2][4 * kWaves];
     __shared__ int s_fail;
     const int t = (int)threadIdx.x;
     int s = s0;
@@ -244,7 +274,7 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
 
     const int nx = S.nx, ny = S.ny, nz = S.nz, P = nx * ny, bm = S.bcmask;
     const bool px = (S.permask & 1) && nx > 1, py = (S.permask & 2) && ny > 1;
-    const int j0 = (g % S.rnby) * S.rby, k0 = (g / S.rnby) * NZ;
+    const int gy = g % S.rnby, gz = g / S.rnby, j0 = gy * S.rby, k0 = gz * NZ;
     const int by = min(S.rby, ny - j0), bz = min(NZ, nz - k0), C = nx * by;
     const bool ylo = j0 > 0 || py, yhi = j0 + by < ny || py, zlo = k0 > 0, zhi = k0 + bz < nz;
     const int RS = nx + 2, PS = (S.rby + 2) * RS;
@@ -265,11 +295,12 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
     uint32_t tag = st.repoch;
     double rz = st.rz, rr = st.rr, pap = st.pap, alpha = st.alpha;
     double beta = first ? 0.0 : st.beta;
+    GLB u64 *area1 = gp(S.rsync), *area2 = area1 + 2 * (size_t)G;
 
     T z[NC][NZ], x[NC][NZ], pl[NC], ph[NC], q[KEEP ? NC : 1][KEEP ? NZ : 1],
         dg[KEEP ? NC : 1][KEEP ? NZ : 1];
     uint32_t code[NC][NZ];
-    int off[NC], gi[NC];
+    int off[NC], gi[NC];  // LDS and grid cell of the column's first plane
     uint32_t cflag = 0;   // 4 bits a column: active, i == 0, i == nx - 1, on a y face
     uint32_t uni = 0;     // columns of one class throughout the wave
 #pragma unroll
@@ -277,11 +308,11 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
         const int col = t + c * kResThreads;
         const bool act = col < C;
         const int jl = act ? col / nx : 0, i = act ? col - jl * nx : 0, j = j0 + jl;
-        off[c] = (jl + 1) * RS + i + 1;
         gi[c] = k0 * P + j * nx + i;
-        const bool yface = (jl == 0 && ylo) || (jl == by - 1 && yhi);
+        off[c] = (jl + 1) * RS + i + 1;
         cflag |= ((act ? 1u : 0u) | (i == 0 ? 2u : 0u) | (i == nx - 1 ? 4u : 0u) |
-                  (yface ? 8u : 0u)) << (4 * c);
+                  ((jl == 0 && ylo) || (jl == by - 1 && yhi) ? 8u : 0u))
+                 << (4 * c);
         const int oxm = i > 0 ? -1 : (px ? nx - 1 : 0), oxp = i < nx - 1 ? 1 : (px ? 1 - nx : 0);
         const int oym = j > 0 ? -nx : (py ? (ny - 1) * nx : 0);
         const int oyp = j < ny - 1 ? nx : (py ? -(ny - 1) * nx : 0);
@@ -320,57 +351,62 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
         if (__all(same)) uni |= 1u << c;
         // p of the planes below and above the brick
         pl[c] = ph[c] = T(0);
-        if (act && !first) {
-            if (zlo) pl[c] = pg[gi[c] - P];
-            if (zhi) ph[c] = pg[gi[c] + NZ * P];
-        }
+        if (act && !first && zlo) pl[c] = pg[gi[c] - P];
+        if (act && !first && zhi) ph[c] = pg[gi[c] + NZ * P];
     }
-    // the rows beside the brick: cell e of this thread comes from global cell
-    // hg[e] and lives at hl[e] (-1: none)
-    int hg[kResHalo], hl[kResHalo];
+    // The rows beside the brick: value e of this thread, m = t + e kResThreads
+    // of them all, belongs to row m / nx (below and above the brick in turn,
+    // plane by plane), is grid cell hg and lives at LDS cell hl (-1: none).
+    // m / nx is exact from the rounded-up reciprocal for m, nx < 2^12.
+    const int nhalo = 2 * bz * nx;
+    const uint32_t inv_nx = ((1u << 24) + (uint32_t)nx - 1u) / (uint32_t)nx;
+    uint32_t tk = (uint32_t)t;
+    const int glo = j0 > 0 ? j0 - 1 : ny - 1, ghi = j0 + by < ny ? j0 + by : 0;
+    auto beside = [&](int e, int &hl, int &hg) __attribute__((always_inline)) {
+        const uint32_t m = tk + (uint32_t)(e * kResThreads);
+        const uint32_t r = nx > 1 ? __umulhi(m << 8, inv_nx) : m, i = m - r * (uint32_t)nx;
+        const bool up = r & 1u;
+        const int k = (int)(r >> 1);
+        hl = k < bz && (up ? yhi : ylo) ? k * PS + (up ? by + 1 : 0) * RS + (int)i + 1 : -1;
+        hg = (k0 + k) * P + (up ? ghi : glo) * nx + (int)i;
+    };
 #pragma unroll
-    for (int e = 0; e < kResHalo; ++e) {
-        const int m = t + e * kResThreads, r = m / nx, i = m - r * nx;
-        const int side = r & 1, k = r >> 1;
-        hl[e] = -1;
-        hg[e] = 0;
-        if (k < bz && (side ? yhi : ylo)) {
-            int j = side ? j0 + by : j0 - 1;
-            j = j < 0 ? ny - 1 : (j >= ny ? 0 : j);
-            hg[e] = (k0 + k) * P + j * nx + i;
-            hl[e] = k * PS + (side ? by + 1 : 0) * RS + i + 1;
-            if (!first) Lp[hl[e]] = pg[hg[e]];
-        }
+    for (int e = 0; e < NH; ++e) {
+        int hl, hg;
+        beside(e, hl, hg);
+        if (e * kResThreads < nhalo && hl >= 0 && !first) Lp[hl] = pg[hg];
     }
-    const int nhalo = 2 * bz * nx;   // wave-uniform bound of the halo loops
-    GLB u64 *area1 = gp(S.rsync), *area2 = area1 + 2 * (size_t)G;
+    int end = 0;   // 0: budget spent, 1: converged or capped, 2: breakdown, 3: vanished direction
 
-    int end = 0;       // 0: budget spent, 1: converged or capped, 2: breakdown, 3: vanished direction
     for (int n = 0;; ++n) {
         if (n == budget) break;
-        // p = z + beta p: halo loads first, own cells while they are in flight
+        // p = z + beta p, of the rows and planes around the brick too: their
+        // z is in flight during the own cells' update
         const T tb = (T)beta;
-        T zl[NC], zh[NC], hz[kResHalo];
+        T zl[NC], zh[NC], hz[NH];
         keep_here(cflag);
+        keep_here(tk);
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             keep_here(gi[c]);
-            keep_here(off[c]);
             const bool act = (cflag >> (4 * c)) & 1u;
             zl[c] = zh[c] = T(0);
             if (zlo && act) zl[c] = dev_load(zg + gi[c] - P);
             if (zhi && act) zh[c] = dev_load(zg + gi[c] + NZ * P);
         }
 #pragma unroll
-        for (int e = 0; e < kResHalo; ++e) {
+        for (int e = 0; e < NH; ++e) {
             hz[e] = T(0);
-            keep_here(hg[e]);
-            keep_here(hl[e]);
-            if (e * kResThreads < nhalo && hl[e] >= 0) hz[e] = dev_load(zg + hg[e]);
+            if (e * kResThreads < nhalo) {
+                int hl, hg;
+                beside(e, hl, hg);
+                if (hl >= 0) hz[e] = dev_load(zg + hg);
+            }
         }
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             const uint32_t f = cflag >> (4 * c);
+            keep_here(off[c]);
             if (f & 1u) {
 #pragma unroll
                 for (int k = 0; k < NZ; ++k) {
@@ -387,13 +423,18 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
             pl[c] = zl[c] + tb * pl[c];
             ph[c] = zh[c] + tb * ph[c];
         }
+        keep_here(tk);
 #pragma unroll
-        for (int e = 0; e < kResHalo; ++e)
-            if (e * kResThreads < nhalo && hl[e] >= 0) Lp[hl[e]] = hz[e] + tb * Lp[hl[e]];
+        for (int e = 0; e < NH; ++e)
+            if (e * kResThreads < nhalo) {
+                int hl, hg;
+                beside(e, hl, hg);
+                if (hl >= 0) Lp[hl] = hz[e] + tb * Lp[hl];
+            }
         __syncthreads();
 
         // q = A p and p.A p
-        double sum[2] = { 0.0, 0.0 };
+        double sum = 0.0;
         auto column = [&](auto U, auto SUM, int c, auto &&each) __attribute__((always_inline)) {
             constexpr bool kU = decltype(U)::value, kS = decltype(SUM)::value;
             keep_here(off[c]);
@@ -425,7 +466,7 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
         using Yes = std::integral_constant<bool, true>;
         using No = std::integral_constant<bool, false>;
         auto first_half = [&](int c, int k, const Row<T> &r, T) __attribute__((always_inline)) {
-            sum[0] += (double)r.s;
+            sum += (double)r.s;
             if constexpr (KEEP) { q[c][k] = r.q; dg[c][k] = r.dg; }
         };
 #pragma unroll
@@ -433,15 +474,16 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
             if ((uni >> c) & 1u) column(Yes{}, Yes{}, c, first_half);
             else column(No{}, Yes{}, c, first_half);
         }
-        double v1[1] = { sum[0] };
+        double v1[1] = { sum };
         if (!all_sum<1>(v1, area1, G, g, ++tag, red, &s_fail)) break;
         pap = v1[0];
         if (!isfinite(pap) || !(pap > 0.0)) { end = (F64 || !isfinite(pap)) ? 2 : 3; break; }
-        alpha = rz / pap;
+        alpha = rz * recip(pap);
 
         // x += alpha p, z -= alpha q / diag, the faces of z, r.z and r.r
         const T ta = (T)alpha;
         keep_here(cflag);
+        const double inv_rz = recip(rz);   // ready before the sums are
         double v2[2] = { 0.0, 0.0 };
         auto second_half = [&](int c, int k, const Row<T> &r, T pc) __attribute__((always_inline)) {
             const T inv = r.dg > T(0) ? recip(r.dg) : T(0);   // hull rows keep z = 0
@@ -451,6 +493,7 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
             const double res = (double)r.dg * (double)zn;
             v2[0] += res * (double)zn;
             v2[1] += res * res;
+            // the faces the neighbours wait for
             const uint32_t f = cflag >> (4 * c);
             if ((f & 1u) && k < bz &&
                 ((f & 8u) || (k == 0 && zlo) || (k == NZ - 1 && zhi)))
@@ -458,8 +501,8 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
         };
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            keep_here(gi[c]);
             keep_here(off[c]);
+            keep_here(gi[c]);
             if constexpr (KEEP) {
 #pragma unroll
                 for (int k = 0; k < NZ; ++k)
@@ -469,10 +512,8 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
                 else column(No{}, No{}, c, second_half);
             }
         }
-        // the faces have reached memory before this workgroup's sums go out
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (!all_sum<2>(v2, area2, G, g, ++tag, red, &s_fail)) break;
-        beta = v2[0] / rz;
+        beta = v2[0] * inv_rz;
         rz = v2[0];
         rr = v2[1];
         ++iter;
@@ -481,6 +522,7 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
         if (F64 ? (rr <= tol2 || iter >= maxit)
                 : (rr <= goal2 || inner >= inner_max || iter >= maxit)) { end = 1; break; }
     }
+    __syncthreads();
     if (s_fail) {
         if (t == 0) dev_store(gp(&st.rfail), 1);
         return;
@@ -527,22 +569,29 @@ struct Entry {
     const void *fn;
 };
 template <typename T, int NC, int NZ, bool KEEP>
-Entry entry()
+Entry entry(int batch = 0)
 {
-    return { { NC, NZ }, (const void *)k_resident<T, NC, NZ, KEEP> };
+    return { { NC, NZ, KEEP, batch }, (const void *)k_resident<T, NC, NZ, KEEP> };
 }
-// Shapes by cells a thread.  FP64 keeps q and the diagonal in registers up
-// to 16 cells, FP32 up to 32 (256 registers a thread with two waves a SIMD).
+// Shapes.  FP64 keeps q and the diagonal in registers up to 16 cells a thread,
+// FP32 up to 32 (256 registers a thread with two waves a SIMD); batches take
+// the first shape marked that holds a grid (two workgroups a CU where its
+// registers allow, which hide each other's exchanges).
 const Entry kF64[] = {
-    entry<double, 1, 1, true>(), entry<double, 1, 2, true>(), entry<double, 1, 4, true>(),
-    entry<double, 2, 4, true>(), entry<double, 1, 8, true>(), entry<double, 2, 8, true>(),
-    entry<double, 4, 4, true>(), entry<double, 3, 8, false>(), entry<double, 5, 6, false>(),
-    entry<double, 4, 8, false>(),
+    entry<double, 1, 1, true>(),  entry<double, 1, 2, true>(),  entry<double, 1, 3, true>(),
+    entry<double, 1, 4, true>(),  entry<double, 2, 2, true>(),  entry<double, 1, 6, true>(),
+    entry<double, 2, 4, true>(),  entry<double, 1, 8, true>(1), entry<double, 2, 6, true>(),
+    entry<double, 3, 4, true>(),  entry<double, 2, 8, true>(1), entry<double, 4, 4, true>(),
+    entry<double, 4, 6, false>(), entry<double, 3, 8, false>(), entry<double, 5, 6, false>(),
+    entry<double, 4, 8, false>(1),
 };
 const Entry kF32[] = {
-    entry<float, 1, 1, true>(), entry<float, 1, 2, true>(), entry<float, 1, 4, true>(),
-    entry<float, 2, 4, true>(), entry<float, 1, 8, true>(), entry<float, 2, 8, true>(),
-    entry<float, 4, 4, true>(), entry<float, 4, 8, true>(), entry<float, 6, 8, false>(),
+    entry<float, 1, 1, true>(),  entry<float, 1, 2, true>(),  entry<float, 1, 3, true>(),
+    entry<float, 1, 4, true>(),  entry<float, 2, 2, true>(),  entry<float, 1, 6, true>(),
+    entry<float, 2, 4, true>(),  entry<float, 1, 8, true>(2), entry<float, 2, 6, true>(),
+    entry<float, 3, 4, true>(),  entry<float, 4, 4, true>(),  entry<float, 2, 8, true>(),
+    entry<float, 3, 8, true>(),  entry<float, 4, 6, true>(),  entry<float, 5, 6, true>(),
+    entry<float, 4, 8, true>(1), entry<float, 6, 8, false>(1),
 };
 }  // namespace
 
@@ -553,6 +602,15 @@ int resident_shapes(int family, ResidentShape *out, int cap)
                                           : (int)(sizeof(kF32) / sizeof(Entry));
     for (int i = 0; i < n && i < cap; ++i) out[i] = t[i].shape;
     return n;
+}
+
+// Workgroups of a shape that a CU holds at once with lds bytes each.
+hipError_t resident_occupancy(int family, int shape, unsigned lds, int *wgs)
+{
+    const void *fn = (family == PCG_PREC_FP64 ? kF64 : kF32)[shape].fn;
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(wgs, fn, kResThreads, lds);
 }
 
 // One launch of the resident kernel of shape `shape` over slots [s0, s1) of
