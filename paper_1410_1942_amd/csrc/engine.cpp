@@ -24,10 +24,10 @@
 namespace pcgmi {
 hipError_t launch_iter(int family, int which, int mode, int grid,
                        const BatchHeader *hdr, const Slot *slots, hipStream_t s);
-hipError_t launch_classify(const double *r64, uint8_t *cls, int64_t n, int round,
-                           unsigned long long *words, hipStream_t s);
-hipError_t launch_encode(const double *rho, const uint8_t *mask, double *r64,
-                         float *r32, int64_t n, int *bad, hipStream_t s);
+__attribute__((weak)) hipError_t launch_setup(const double *rho, const uint8_t *mask, double *r64,
+                                              float *r32, uint8_t *cls, int64_t n, int *bad,
+                                              unsigned long long *words, double *t64, float *t32,
+                                              hipStream_t s);
 hipError_t launch_copy(const double *src, double *dst, size_t n, hipStream_t s);
 hipError_t launch_pack_mask(const uint8_t *mask, uint32_t *bits, int nx,
                             int words_per_row, int64_t nwords, hipStream_t s);
@@ -1032,20 +1032,28 @@ struct Engine {
             if (kind < 0) return kind;
             S.singular = kind == 1;
         }
+        // one pass checks, encodes and classes the densities and one small
+        // launch makes the coefficient tables; the host reads the error flag
+        // and the distinct values found, all in one round trip
         const bool want_classes = !(flags & PCG_NO_DENSITY_CLASSES);
+        unsigned long long *d_words = (unsigned long long *)(d_bad + 2);
+        unsigned long long *h_words = (unsigned long long *)(h_bad + 2);
+        const size_t bytes = 8 + 8 * (kMaxFluidClasses + 1);
         *h_bad = 0;
-        hipError_t e = hipMemcpyAsync(d_bad, h_bad, sizeof(int), hipMemcpyHostToDevice, stream);
-        if (e == hipSuccess) e = launch_encode(rho, mask, S.rho64, S.rho32, geo.n, d_bad, stream);
-        if (e == hipSuccess && want_classes) e = classify_launch(S);
+        for (int r = 0; r <= kMaxFluidClasses; ++r) h_words[r] = ~0ull;
+        hipError_t e = hipMemcpyAsync(d_bad, h_bad, bytes, hipMemcpyHostToDevice, stream);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(h_bad, d_bad, want_classes ? 8 + 8 * kRounds : sizeof(int),
-                               hipMemcpyDeviceToHost, stream);
+            e = launch_setup ? launch_setup(rho, mask, S.rho64, S.rho32, want_classes ? S.cls : nullptr,
+                                            geo.n, d_bad, d_words, S.tab64, S.tab32, stream)
+                             : hipErrorNoDevice;
+        if (e == hipSuccess) e = hipMemcpyAsync(h_bad, d_bad, bytes, hipMemcpyDeviceToHost, stream);
         if (e == hipSuccess) e = hipStreamSynchronize(stream);
         if (e != hipSuccess) return hip_fail(e, "encode");
         if (*h_bad) return PCG_EDOMAIN;
         if (want_classes) {
-            int st = classify_finish(S);
-            if (st) return st;
+            while (S.nclasses <= kMaxFluidClasses && h_words[S.nclasses] != ~0ull) ++S.nclasses;
+            S.classes = S.nclasses <= kMaxFluidClasses;   // not with one value too many
+            if (!S.classes) S.nclasses = 0;
         }
         S.ready = true;
         table_dirty = true;      // coefficient mode and pointers may have changed
@@ -1059,65 +1067,6 @@ struct Engine {
         SlotHost &S = slots[id];
         if (S.running) return PCG_EBUSY;
         return encode_slot(S, rho, mask, flags);
-    }
-
-    // Code the densities as classes when there are at most kMaxFluidClasses
-    // distinct fluid values.  kMaxFluidClasses + 2 chained device rounds (no
-    // host round trip between them) find the distinct values in increasing
-    // order and label the cells; one copy brings the values back, and the
-    // face coefficient table is computed here exactly as 2/(rho_a + rho_b)
-    // in FP64 (and FP32).
-    static constexpr int kRounds = kMaxFluidClasses + 2;
-
-    hipError_t classify_launch(SlotHost &S)
-    {
-        unsigned long long *d_words = (unsigned long long *)(d_bad + 2);
-        unsigned long long *h_words = (unsigned long long *)(h_bad + 2);
-        for (int r = 0; r < kRounds; ++r) h_words[r] = ~0ull;
-        hipError_t e = hipMemcpyAsync(d_words, h_words, 8 * kRounds, hipMemcpyHostToDevice, stream);
-        for (int r = 0; r < kRounds && e == hipSuccess; ++r)
-            e = launch_classify(S.rho64, S.cls, S.geo.n, r, d_words, stream);
-        return e;
-    }
-
-    // After classify_launch and a synchronize: read the distinct values and
-    // build the coefficient tables.
-    int classify_finish(SlotHost &S)
-    {
-        const unsigned long long *h_words = (const unsigned long long *)(h_bad + 2);
-        std::vector<double> pal;
-        for (int r = 0; r < kRounds && h_words[r] != ~0ull; ++r) {
-            double v;
-            std::memcpy(&v, &h_words[r], 8);
-            pal.push_back(v);
-        }
-        // a value in words[kMaxFluidClasses] means a 15th distinct density
-        if ((int)pal.size() > kMaxFluidClasses) return PCG_OK;
-        double rho[kClasses];
-        for (int a = 0; a < kClasses; ++a) rho[a] = 0.0;
-        for (size_t a = 0; a < pal.size(); ++a) rho[a] = pal[a];
-        rho[kClsWallD] = 0.0;
-        rho[kClsSolid] = INFINITY;
-        std::vector<double> t64(kClasses * kClasses);
-        std::vector<float> t32(kClasses * kClasses);
-        for (int a = 0; a < kClasses; ++a)
-            for (int b = 0; b < kClasses; ++b) {
-                const bool live = (a < (int)pal.size() || a >= kClsWallD) &&
-                                  (b < (int)pal.size() || b >= kClsWallD);
-                const double sum = rho[a] + rho[b];
-                t64[a * kClasses + b] = live && std::isfinite(sum) && sum > 0.0 ? 2.0 / sum : 0.0;
-                const float sf = (float)rho[a] + (float)rho[b];
-                t32[a * kClasses + b] = live && std::isfinite(sf) && sf > 0.0f ? 2.0f / sf : 0.0f;
-            }
-        // on the engine's stream (not the null stream, which would wait for
-        // every other stream of the device); the host tables live until the
-        // copies have finished
-        HIP_TRY(hipMemcpyAsync(S.tab64, t64.data(), t64.size() * 8, hipMemcpyHostToDevice, stream));
-        HIP_TRY(hipMemcpyAsync(S.tab32, t32.data(), t32.size() * 4, hipMemcpyHostToDevice, stream));
-        HIP_TRY(hipStreamSynchronize(stream));
-        S.classes = true;
-        S.nclasses = (int)pal.size();
-        return PCG_OK;
     }
 
     // Start a solve on a prepared slot.
@@ -1779,7 +1728,7 @@ int pcg_get_tile_rules(int32_t precision, int32_t table, int32_t cap,
 
 static int project_blocks(const SlotHost &S)
 {
-    return (int)std::max<int64_t>(1, std::min<int64_t>((S.geo.n + 255) / 256, 4096));
+    return (int)col_tiles((int64_t)S.geo.nx * S.geo.ny, S.geo.nz);
 }
 
 int pcg_project(pcg_ctx_t *c, const double *p, double dt, double *u, double *v,
@@ -1853,9 +1802,8 @@ int pcg_divergence(pcg_ctx_t *c, const double *u, const double *v, const double 
     if (st) return st;
     const SlotHost &S = c->eng.slots[c->slot];
     // one partial pair per workgroup, in the slot's partial-sum buffer
-    const int64_t blocks = std::max<int64_t>(
-        1, std::min<int64_t>({ (S.geo.n + 255) / 256, 2048,
-                               (int64_t)(kMaxPartials * S.geo.ntiles / 2) }));
+    const int64_t room = kMaxPartials * S.geo.ntiles / 2;
+    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>({ project_blocks(S), 4096, room }));
     HIP_TRY(launch_divnorm(ds, 1.0 / std::sqrt(S.h2), u, v, w, S.partials, (int)blocks,
                            c->eng.stream));
     std::vector<double> part(2 * blocks);

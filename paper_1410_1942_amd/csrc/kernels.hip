@@ -2854,23 +2854,165 @@ k_iter(const BatchHeader *__restrict__ hdr, const Slot *__restrict__ slots)
     if (run) arrive(slots[cur], cur_ph, run, lds, &s_last);
 }
 
-// Density encoding: fluid keeps rho (checked > 0 and finite), hull -> +inf.
+// Density encoding in one pass: fluid keeps rho (checked > 0 and finite),
+// hull -> +inf, and (cls given) every cell gets the class of its density.
+// words[0 .. kMaxFluidClasses] hold the distinct fluid densities found so
+// far as bits, all ones where none; a class is the place its density took
+// there (the coefficient table follows the places, so their order does not
+// matter), and a density that finds the first kMaxFluidClasses places taken
+// takes the last: the field then has too many, and no more classes are
+// written.  A workgroup keeps the densities it has met in LDS and goes to
+// memory for a new one only.
+// Bound by its streams, 18 B a cell (22 with the FP32 copy).  On 384^3 cells
+// with two densities encoding and then a pass for each value and one more
+// took 610 us (and 13 empty launches); this 260.
+struct Palette {
+    unsigned long long v[kMaxFluidClasses + 1];
+    int full;
+};
+
+__device__ __noinline__ int palette_insert(Palette &pal, unsigned long long bits,
+                                           unsigned long long *__restrict__ words)
+{
+    for (int i = 0; i <= kMaxFluidClasses; ++i) {
+        unsigned long long have = __hip_atomic_load(&words[i], __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+        if (have == ~0ull) {
+            const unsigned long long old = atomicCAS(&words[i], ~0ull, bits);
+            have = old == ~0ull ? bits : old;
+        }
+        if (i == kMaxFluidClasses) break;
+        // lanes that meet the same density at once write the same place
+        __hip_atomic_store(&pal.v[i], have, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (have == bits) return i;
+    }
+    __hip_atomic_store(&pal.full, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return -1;
+}
+
+// The palette as memory has it, into LDS.
+__device__ __forceinline__ void palette_load(Palette &pal,
+                                             const unsigned long long *__restrict__ words)
+{
+    if (threadIdx.x <= kMaxFluidClasses)
+        pal.v[threadIdx.x] = __hip_atomic_load(&words[threadIdx.x], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) pal.full = 0;
+    __syncthreads();
+}
+
+// Class of a density (-1: too many), looked up in LDS and entered if new.
+// Lanes may come in any number; those with a new density take turns.
+__device__ __forceinline__ int palette_class(Palette &pal, unsigned long long bits,
+                                             unsigned long long *__restrict__ words)
+{
+    for (;;) {
+        int id = -1;
+#pragma unroll
+        for (int i = 0; i < kMaxFluidClasses; ++i)
+            if (__hip_atomic_load(&pal.v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == bits)
+                id = i;
+        if (id >= 0) return id;
+        if (__hip_atomic_load(&pal.full, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) return -1;
+        const unsigned long long waiting = __ballot(1);
+        if ((int)(threadIdx.x & 63) == __builtin_ctzll(waiting)) return palette_insert(pal, bits, words);
+    }
+}
+
+// The distinct densities of 4096 cells spread over the grid, entered before
+// the encoding so that its workgroups find them.
+__global__ void __launch_bounds__(256)
+k_seed(const double *__restrict__ rho, const uint8_t *__restrict__ mask, int64_t n,
+       unsigned long long *__restrict__ words)
+{
+    __shared__ Palette pal;
+    palette_load(pal, words);
+    unsigned long long last = ~0ull;
+    for (int e = threadIdx.x; e < 4096; e += 256) {
+        const int64_t c = (int64_t)((double)e * (double)n / 4096.0);
+        const double v = rho[c];
+        if ((mask && mask[c]) || !(v > 0.0) || !isfinite(v)) continue;
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(v);
+        if (bits != last && palette_class(pal, bits, words) < 0) break;
+        last = bits;
+    }
+}
+
+// V cells a thread, adjacent (the pointers aligned to V doubles).
+template <int V>
 __global__ void __launch_bounds__(256)
 k_encode(const double *__restrict__ rho, const uint8_t *__restrict__ mask,
-         double *__restrict__ r64, float *__restrict__ r32, int64_t n,
-         int *__restrict__ bad)
+         double *__restrict__ r64, float *__restrict__ r32, uint8_t *__restrict__ cls, int64_t n,
+         int *__restrict__ bad, unsigned long long *__restrict__ words)
 {
+    using DV = typename VecN<double, V>::type;
+    using FV = typename VecN<float, V>::type;
+    using BV = typename VecN<uint8_t, V>::type;
+    __shared__ Palette pal;
+    palette_load(pal, words);
     int local_bad = 0;
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n;
-         c += (int64_t)gridDim.x * blockDim.x) {
-        const bool solid = mask != nullptr && mask[c] != 0;
-        double v = rho[c];
-        if (solid) v = INFINITY;
-        else if (!(v > 0.0) || !isfinite(v) || v > 1.0e37) local_bad = 1;
-        r64[c] = v;
-        if (r32) r32[c] = (float)v;
+    unsigned long long last = ~0ull;   // the density of this thread's last cell, and its class
+    int last_id = 0;
+    bool full = cls == nullptr;
+    const int64_t groups = n / V;
+    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < groups;
+         g += (int64_t)gridDim.x * blockDim.x) {
+        const DV in = __builtin_nontemporal_load((const DV *)rho + g);
+        BV m = 0;
+        if (mask) m = __builtin_nontemporal_load((const BV *)mask + g);
+        DV out;
+        BV id;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            double v = in[e];
+            const bool solid = m[e] != 0;
+            if (solid) v = INFINITY;
+            else if (!(v > 0.0) || !isfinite(v) || v > 1.0e37) local_bad = 1;
+            out[e] = v;
+            int k = kClsSolid;
+            if (!solid && !full) {
+                const unsigned long long bits = (unsigned long long)__double_as_longlong(v);
+                if (bits != last) {
+                    last = bits;
+                    last_id = palette_class(pal, bits, words);
+                    full = last_id < 0;
+                }
+                k = last_id;
+            }
+            id[e] = (uint8_t)k;
+        }
+        __builtin_nontemporal_store(out, (DV *)r64 + g);
+        if (r32) {
+            FV f;
+#pragma unroll
+            for (int e = 0; e < V; ++e) f[e] = (float)out[e];
+            __builtin_nontemporal_store(f, (FV *)r32 + g);
+        }
+        if (cls && !full) __builtin_nontemporal_store(id, (BV *)cls + g);
     }
     if (local_bad) atomicOr(bad, 1);
+}
+
+// Face coefficient tables 2/(rho_a + rho_b) of the classes found (their
+// densities as bits in words), 0 where no cell has one: one thread an entry.
+__global__ void __launch_bounds__(kClasses *kClasses)
+k_tables(const unsigned long long *__restrict__ words, double *__restrict__ t64,
+         float *__restrict__ t32)
+{
+    const int a = threadIdx.x / kClasses, b = threadIdx.x % kClasses;
+    auto density = [&](int c, bool &live) {
+        live = true;
+        if (c == kClsWallD) return 0.0;
+        if (c == kClsSolid) return (double)INFINITY;
+        live = words[c] != ~0ull;
+        return live ? __longlong_as_double((long long)words[c]) : 0.0;
+    };
+    bool la, lb;
+    const double ra = density(a, la), rb = density(b, lb);
+    const double sum = ra + rb;
+    const float sf = (float)ra + (float)rb;
+    t64[threadIdx.x] = la && lb && isfinite(sum) && sum > 0.0 ? 2.0 / sum : 0.0;
+    t32[threadIdx.x] = la && lb && isfinite(sf) && sf > 0.0f ? 2.0f / sf : 0.0f;
 }
 
 // The hull mask one bit per cell for the host's connectivity check: row r
@@ -2891,44 +3033,6 @@ k_pack_mask(const uint8_t *__restrict__ mask, uint32_t *__restrict__ bits, int n
         uint32_t v = cnt < 32 ? ~0u << cnt : 0u;
         for (int j = 0; j < cnt; ++j) v |= (uint32_t)(m[j] != 0) << j;
         bits[t] = v;
-    }
-}
-
-// One round of density classification, chained on the device: round r reads
-// the candidate found by round r-1 (words[r-1]; round 0 uses 0), labels the
-// cells whose density equals it with class r-1, and leaves the smallest
-// density above it in words[r] (all ones when none is left, after which
-// later rounds do nothing).  Densities are positive, so the order of their
-// bit patterns is numeric order.  Round 0 also marks hull cells.
-__global__ void __launch_bounds__(256)
-k_classify(const double *__restrict__ r64, uint8_t *__restrict__ cls, int64_t n,
-           int round, unsigned long long *__restrict__ words)
-{
-    __shared__ unsigned long long wmin[4];
-    const unsigned long long cand = round > 0 ? words[round - 1] : 0ull;
-    if (cand == ~0ull) return;
-    unsigned long long local = ~0ull;
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n;
-         c += (int64_t)gridDim.x * blockDim.x) {
-        const double v = r64[c];
-        if (isinf(v)) {
-            if (round == 0) cls[c] = (uint8_t)kClsSolid;
-            continue;
-        }
-        const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-        if (b == cand) cls[c] = (uint8_t)(round - 1);
-        else if (b > cand && b < local) local = b;
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        const unsigned long long o = __shfl_xor(local, off, 64);
-        local = o < local ? o : local;
-    }
-    if ((threadIdx.x & 63) == 0) wmin[threadIdx.x >> 6] = local;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long m = wmin[0];
-        for (int w = 1; w < 4; ++w) m = wmin[w] < m ? wmin[w] : m;
-        if (m != ~0ull) atomicMin(&words[round], m);
     }
 }
 
@@ -2963,60 +3067,87 @@ __device__ inline double face_in(const FaceSet &a, const FaceSet &b, int axis, i
     return gp(A)[f] + gp(B)[f];
 }
 
+// The columns of a workgroup of these kernels: f(q, i, j, k0, k1) for each of
+// its column tiles, the thread's column (i, j) = q of a plane over planes
+// [k0, k1).  A column marches up in z, so what belongs to the plane below is
+// carried and the index arithmetic is done once a column.  All three are bound
+// by their streams.  384^3, one cell a thread in a grid-stride loop (64-bit
+// divisions a cell, the hull from 8 B densities) against this: projection 726
+// -> 610 us (57 B a cell: 5.3 TB/s), with a second field 964 -> 845 (81 B: 5.4),
+// source 516 -> 358 (33 B: 5.2) and 903 -> 585 (57 B: 5.5), divergence 420 ->
+// 323 (25 B: 4.4).  Tiles in launch order measured better than a contiguous
+// run of them a XCD (projection 663, source 656): neighbouring tiles' streams
+// then lie side by side.
+template <class F>
+__device__ __forceinline__ void for_columns(const Slot &S, F &&f)
+{
+    const int nx = S.nx, nz = S.nz, P = nx * S.ny;
+    const int zc = col_planes(P, nz), pt = (P + kBlock - 1) / kBlock;
+    const int64_t T = (int64_t)pt * ((nz + zc - 1) / zc);
+    const int G = (int)gridDim.x;
+    for (int64_t t = blockIdx.x; t < T; t += G) {
+        const int q = (int)(t % pt) * kBlock + (int)threadIdx.x, zt = (int)(t / pt);
+        if (q >= P) continue;
+        const int j = q / nx;
+        f(q, q - j * nx, j, zt * zc, min(nz, (zt + 1) * zc));
+    }
+}
+
 template <bool ADD, class C>
 __device__ void project_cells(const Slot &S, const C &cf, const double *__restrict__ p,
                               double s, double wt, FaceSet a, FaceSet b, ProjOut o)
 {
     using K = typename C::Key;
     const int nx = S.nx, ny = S.ny, nz = S.nz;
-    const int64_t P = (int64_t)nx * ny, n = P * nz;
+    const int64_t P = (int64_t)nx * ny;
     const int bm = S.bcmask;
     const bool perx = S.permask & 1, pery = S.permask & 2;
     const GLB double *__restrict__ pg = gp(p);
     GLB double *ou = gp(o.u);
     GLB double *ov = gp(o.v);
     GLB double *ow = gp(o.w);
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n;
-         c += (int64_t)gridDim.x * blockDim.x) {
-        const int i = (int)(c % nx);
-        const int j = (int)((c / nx) % ny);
-        const int k = (int)(c / P);
-        const K kc = cf.load(c);
-        const double pc = pg[c];
-        const int64_t fu = ((int64_t)k * ny + j) * (nx + 1) + i;
-        const int64_t fv = ((int64_t)k * (ny + 1) + j) * nx + i;
-        const int64_t fw = c;
-        if (i > 0) {
-            ou[fu] = wt * (face_in<ADD>(a, b, 0, fu) - s * cf.beta(cf.load(c - 1), kc) * (pc - pg[c - 1]));
-        } else if (perx) {   // shared face with the row's last cell, and its repeat
-            const int64_t m = c + nx - 1;
-            const double u0 = nx > 1 ? wt * (face_in<ADD>(a, b, 0, fu) - s * cf.beta(cf.load(m), kc) * (pc - pg[m]))
-                                     : wt * face_in<ADD>(a, b, 0, fu);
-            ou[fu] = u0;
-            ou[fu + nx] = u0;
-        } else {
-            ou[fu] = wt * (face_in<ADD>(a, b, 0, fu) - s * cf.beta(kc, (bm & 1) ? cf.dirichlet() : cf.neumann()) * pc);
+    const K wxm = (bm & 1) ? cf.dirichlet() : cf.neumann(), wxp = (bm & 2) ? cf.dirichlet() : cf.neumann();
+    const K wym = (bm & 4) ? cf.dirichlet() : cf.neumann(), wyp = (bm & 8) ? cf.dirichlet() : cf.neumann();
+    const K wzm = (bm & 16) ? cf.dirichlet() : cf.neumann(), wzp = (bm & 32) ? cf.dirichlet() : cf.neumann();
+    for_columns(S, [&](int q, int i, int j, int k0, int k1) {
+        // the cells below x and y: across a periodic wall the axis's last (an
+        // axis of one cell has none); at other walls p = 0 and the wall's key
+        const bool hx = i > 0 || (perx && nx > 1), hy = j > 0 || (pery && ny > 1);
+        const int ox = i > 0 ? -1 : (hx ? nx - 1 : 0);
+        const int64_t oy = j > 0 ? -nx : (hy ? P - nx : 0);
+        int64_t c = k0 * P + q;
+        int64_t fu = ((int64_t)k0 * ny + j) * (nx + 1) + i;
+        int64_t fv = ((int64_t)k0 * (ny + 1) + j) * nx + i;
+        double pb = k0 > 0 ? pg[c - P] : 0.0;
+        K kb = k0 > 0 ? cf.load(c - P) : wzm;
+#pragma unroll 2
+        for (int k = k0; k < k1; ++k, c += P, fu += (int64_t)ny * (nx + 1), fv += (int64_t)(ny + 1) * nx) {
+            const K kc = cf.load(c), lkx = cf.load(c + ox), lky = cf.load(c + oy);
+            const double pc = pg[c], lpx = pg[c + ox], lpy = pg[c + oy];
+            const double u = face_in<ADD>(a, b, 0, fu), v = face_in<ADD>(a, b, 1, fv),
+                         w = face_in<ADD>(a, b, 2, c);
+            const double un = wt * (u - s * cf.beta(hx ? lkx : wxm, kc) * (pc - (hx ? lpx : 0.0)));
+            const double vn = wt * (v - s * cf.beta(hy ? lky : wym, kc) * (pc - (hy ? lpy : 0.0)));
+            const double wn = wt * (w - s * cf.beta(kb, kc) * (pc - pb));
+            __builtin_nontemporal_store(un, &ou[fu]);
+            __builtin_nontemporal_store(vn, &ov[fv]);
+            __builtin_nontemporal_store(wn, &ow[c]);
+            // high walls: their own face, or the repeat of the shared one
+            if (perx) {
+                if (i == 0) ou[fu + nx] = un;
+            } else if (i == nx - 1) {
+                ou[fu + 1] = wt * (face_in<ADD>(a, b, 0, fu + 1) + s * cf.beta(kc, wxp) * pc);
+            }
+            if (pery) {
+                if (j == 0) ov[fv + (int64_t)ny * nx] = vn;
+            } else if (j == ny - 1) {
+                ov[fv + nx] = wt * (face_in<ADD>(a, b, 1, fv + nx) + s * cf.beta(kc, wyp) * pc);
+            }
+            if (k == nz - 1) ow[c + P] = wt * (face_in<ADD>(a, b, 2, c + P) + s * cf.beta(kc, wzp) * pc);
+            pb = pc;
+            kb = kc;
         }
-        if (i == nx - 1 && !perx)
-            ou[fu + 1] = wt * (face_in<ADD>(a, b, 0, fu + 1) + s * cf.beta(kc, (bm & 2) ? cf.dirichlet() : cf.neumann()) * pc);
-        if (j > 0) {
-            ov[fv] = wt * (face_in<ADD>(a, b, 1, fv) - s * cf.beta(cf.load(c - nx), kc) * (pc - pg[c - nx]));
-        } else if (pery) {
-            const int64_t m = c + (int64_t)(ny - 1) * nx;
-            const double v0 = ny > 1 ? wt * (face_in<ADD>(a, b, 1, fv) - s * cf.beta(cf.load(m), kc) * (pc - pg[m]))
-                                     : wt * face_in<ADD>(a, b, 1, fv);
-            ov[fv] = v0;
-            ov[fv + (int64_t)ny * nx] = v0;
-        } else {
-            ov[fv] = wt * (face_in<ADD>(a, b, 1, fv) - s * cf.beta(kc, (bm & 4) ? cf.dirichlet() : cf.neumann()) * pc);
-        }
-        if (j == ny - 1 && !pery)
-            ov[fv + nx] = wt * (face_in<ADD>(a, b, 1, fv + nx) + s * cf.beta(kc, (bm & 8) ? cf.dirichlet() : cf.neumann()) * pc);
-        if (k > 0) ow[fw] = wt * (face_in<ADD>(a, b, 2, fw) - s * cf.beta(cf.load(c - P), kc) * (pc - pg[c - P]));
-        else ow[fw] = wt * (face_in<ADD>(a, b, 2, fw) - s * cf.beta(kc, (bm & 16) ? cf.dirichlet() : cf.neumann()) * pc);
-        if (k == nz - 1)
-            ow[fw + P] = wt * (face_in<ADD>(a, b, 2, fw + P) + s * cf.beta(kc, (bm & 32) ? cf.dirichlet() : cf.neumann()) * pc);
-    }
+    });
 }
 
 template <bool ADD>
@@ -3050,47 +3181,59 @@ k_project(const Slot *__restrict__ slot, const double *__restrict__ p, double s,
 // source div(u* + u^k)/dt, without it the first-stage div(u^k)/dt.  On a
 // periodic axis the high face of the last cell is face 0 (the last face of
 // the array is not read).
-template <bool ADD>
-__device__ void rhs_cells(const Slot &S, double h, double dt, FaceSet a, FaceSet b,
+template <bool ADD, class C>
+__device__ void rhs_cells(const Slot &S, const C &cf, double h, double dt, FaceSet a, FaceSet b,
                           double *__restrict__ rhs)
 {
-    const int nx = S.nx, ny = S.ny, nz = S.nz;
-    const int64_t P = (int64_t)nx * ny, n = P * nz;
+    const int nx = S.nx, ny = S.ny;
+    const int64_t P = (int64_t)nx * ny;
     const bool perx = S.permask & 1, pery = S.permask & 2;
-    const RhoCoef<double> cf{ gp(S.rho64) };
     GLB double *out = gp(rhs);
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n;
-         c += (int64_t)gridDim.x * blockDim.x) {
-        if (cf.solid(cf.load(c))) { out[c] = 0.0; continue; }
-        const int i = (int)(c % nx);
-        const int j = (int)((c / nx) % ny);
-        const int k = (int)(c / P);
-        const int64_t fu = ((int64_t)k * ny + j) * (nx + 1) + i;
-        const int64_t fv = ((int64_t)k * (ny + 1) + j) * nx + i;
+    for_columns(S, [&](int q, int i, int j, int k0, int k1) {
         // the high face of a periodic row's last cell is the row's face 0
-        const int64_t fu1 = (perx && i == nx - 1) ? fu - i : fu + 1;
-        const int64_t fv1 = (pery && j == ny - 1) ? fv - (int64_t)j * nx : fv + nx;
-        if (S.ax) {   // cut cells: area-weighted faces over the volume fraction
-            const GLB double *ax = gp(S.ax), *ay = gp(S.ay), *az = gp(S.az);
-            const double du = ax[fu1] * face_in<ADD>(a, b, 0, fu1) - ax[fu] * face_in<ADD>(a, b, 0, fu);
-            const double dv = ay[fv1] * face_in<ADD>(a, b, 1, fv1) - ay[fv] * face_in<ADD>(a, b, 1, fv);
-            const double dw = az[c + P] * face_in<ADD>(a, b, 2, c + P) - az[c] * face_in<ADD>(a, b, 2, c);
-            out[c] = ((du + dv) + dw) / (gp(S.vol)[c] * h) / dt;
-            continue;
+        const int64_t ou = (perx && i == nx - 1) ? -i : 1;
+        const int64_t ov = (pery && j == ny - 1) ? -(int64_t)j * nx : nx;
+        int64_t c = k0 * P + q;
+        int64_t fu = ((int64_t)k0 * ny + j) * (nx + 1) + i;
+        int64_t fv = ((int64_t)k0 * (ny + 1) + j) * nx + i;
+        double wl = face_in<ADD>(a, b, 2, c);
+#pragma unroll 2
+        for (int k = k0; k < k1; ++k, c += P, fu += (int64_t)ny * (nx + 1), fv += (int64_t)(ny + 1) * nx) {
+            const bool solid = cf.solid(cf.load(c));
+            const double u0 = face_in<ADD>(a, b, 0, fu), u1 = face_in<ADD>(a, b, 0, fu + ou);
+            const double v0 = face_in<ADD>(a, b, 1, fv), v1 = face_in<ADD>(a, b, 1, fv + ov);
+            const double wh = face_in<ADD>(a, b, 2, c + P);
+            double r;
+            if (S.ax) {   // cut cells: area-weighted faces over the volume fraction
+                const GLB double *ax = gp(S.ax), *ay = gp(S.ay), *az = gp(S.az);
+                const double du = ax[fu + ou] * u1 - ax[fu] * u0;
+                const double dv = ay[fv + ov] * v1 - ay[fv] * v0;
+                const double dw = az[c + P] * wh - az[c] * wl;
+                r = ((du + dv) + dw) / (gp(S.vol)[c] * h) / dt;
+            } else {
+                r = (((u1 - u0) + (v1 - v0)) + (wh - wl)) / h / dt;
+            }
+            __builtin_nontemporal_store(solid ? 0.0 : r, &out[c]);
+            wl = wh;
         }
-        const double du = face_in<ADD>(a, b, 0, fu1) - face_in<ADD>(a, b, 0, fu);
-        const double dv = face_in<ADD>(a, b, 1, fv1) - face_in<ADD>(a, b, 1, fv);
-        const double dw = face_in<ADD>(a, b, 2, c + P) - face_in<ADD>(a, b, 2, c);
-        out[c] = ((du + dv) + dw) / h / dt;
-    }
+    });
+}
+
+template <bool ADD>
+__device__ __forceinline__ void rhs_slot(const Slot &S, double h, double dt, FaceSet a, FaceSet b,
+                                         double *rhs)
+{
+    // the hull from the class bytes where there are any (1 B a cell, not 8)
+    if (S.cls) rhs_cells<ADD>(S, ClsCoef<double>{ gp(S.cls), nullptr }, h, dt, a, b, rhs);
+    else rhs_cells<ADD>(S, RhoCoef<double>{ gp(S.rho64) }, h, dt, a, b, rhs);
 }
 
 __global__ void __launch_bounds__(256)
 k_rhs(const Slot *__restrict__ slot, double h, double dt, FaceSet a, FaceSet b,
       double *__restrict__ rhs)
 {
-    if (b.u) rhs_cells<true>(*slot, h, dt, a, b, rhs);
-    else rhs_cells<false>(*slot, h, dt, a, b, rhs);
+    if (b.u) rhs_slot<true>(*slot, h, dt, a, b, rhs);
+    else rhs_slot<false>(*slot, h, dt, a, b, rhs);
 }
 
 // (D u)_c = (u_{i+1/2} - u_{i-1/2} + v_{j+1/2} - v_{j-1/2} + w_{k+1/2} -
@@ -3098,6 +3241,43 @@ k_rhs(const Slot *__restrict__ slot, double h, double dt, FaceSet a, FaceSet b,
 // source kernel):
 // per-workgroup sum of squares and maximum magnitude, combined on the host in
 // workgroup order.
+template <class C>
+__device__ __forceinline__ void divnorm_cells(const Slot &S, const C &cf, double inv_h,
+                                              const double *__restrict__ u,
+                                              const double *__restrict__ v,
+                                              const double *__restrict__ w, double &ss, double &mx)
+{
+    const int nx = S.nx, ny = S.ny;
+    const int64_t P = (int64_t)nx * ny;
+    const bool perx = S.permask & 1, pery = S.permask & 2;
+    const GLB double *ug = gp(u), *vg = gp(v), *wg = gp(w);
+    for_columns(S, [&](int q, int i, int j, int k0, int k1) {
+        const int64_t ou = (perx && i == nx - 1) ? -i : 1;
+        const int64_t ov = (pery && j == ny - 1) ? -(int64_t)j * nx : nx;
+        int64_t c = k0 * P + q;
+        int64_t fu = ((int64_t)k0 * ny + j) * (nx + 1) + i;
+        int64_t fv = ((int64_t)k0 * (ny + 1) + j) * nx + i;
+        double wl = wg[c];
+#pragma unroll 2
+        for (int k = k0; k < k1; ++k, c += P, fu += (int64_t)ny * (nx + 1), fv += (int64_t)(ny + 1) * nx) {
+            const bool solid = cf.solid(cf.load(c));
+            const double u0 = ug[fu], u1 = ug[fu + ou], v0 = vg[fv], v1 = vg[fv + ov], wh = wg[c + P];
+            double d;
+            if (S.ax) {   // cut cells: area-weighted faces over the volume fraction
+                const GLB double *ax = gp(S.ax), *ay = gp(S.ay), *az = gp(S.az);
+                d = ((ax[fu + ou] * u1 - ax[fu] * u0) + (ay[fv + ov] * v1 - ay[fv] * v0) +
+                     (az[c + P] * wh - az[c] * wl)) / gp(S.vol)[c] * inv_h;
+            } else {
+                d = ((u1 - u0) + (v1 - v0) + (wh - wl)) * inv_h;
+            }
+            d = solid ? 0.0 : d;
+            ss += d * d;
+            mx = fmax(mx, fabs(d));
+            wl = wh;
+        }
+    });
+}
+
 __global__ void __launch_bounds__(256)
 k_divnorm(const Slot *__restrict__ slot, double inv_h, const double *__restrict__ u,
           const double *__restrict__ v, const double *__restrict__ w,
@@ -3105,32 +3285,9 @@ k_divnorm(const Slot *__restrict__ slot, double inv_h, const double *__restrict_
 {
     __shared__ double lds[8];
     const Slot &S = *slot;
-    const int nx = S.nx, ny = S.ny, nz = S.nz;
-    const int64_t P = (int64_t)nx * ny, n = P * nz;
-    const RhoCoef<double> cf{ gp(S.rho64) };
-    const bool perx = S.permask & 1, pery = S.permask & 2;
     double ss = 0.0, mx = 0.0;
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n;
-         c += (int64_t)gridDim.x * blockDim.x) {
-        if (cf.solid(cf.load(c))) continue;
-        const int i = (int)(c % nx);
-        const int j = (int)((c / nx) % ny);
-        const int k = (int)(c / P);
-        const int64_t fu = ((int64_t)k * ny + j) * (nx + 1) + i;
-        const int64_t fv = ((int64_t)k * (ny + 1) + j) * nx + i;
-        const int64_t fu1 = (perx && i == nx - 1) ? fu - i : fu + 1;
-        const int64_t fv1 = (pery && j == ny - 1) ? fv - (int64_t)j * nx : fv + nx;
-        double d;
-        if (S.ax) {   // cut cells: area-weighted faces over the volume fraction
-            const GLB double *ax = gp(S.ax), *ay = gp(S.ay), *az = gp(S.az);
-            d = ((ax[fu1] * u[fu1] - ax[fu] * u[fu]) + (ay[fv1] * v[fv1] - ay[fv] * v[fv]) +
-                 (az[c + P] * w[c + P] - az[c] * w[c])) / gp(S.vol)[c] * inv_h;
-        } else {
-            d = ((u[fu1] - u[fu]) + (v[fv1] - v[fv]) + (w[c + P] - w[c])) * inv_h;
-        }
-        ss += d * d;
-        mx = fmax(mx, fabs(d));
-    }
+    if (S.cls) divnorm_cells(S, ClsCoef<double>{ gp(S.cls), nullptr }, inv_h, u, v, w, ss, mx);
+    else divnorm_cells(S, RhoCoef<double>{ gp(S.rho64) }, inv_h, u, v, w, ss, mx);
     double a[1] = { ss };
     ss = wave_sum(a[0]);
     for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
@@ -3242,25 +3399,27 @@ hipError_t launch_iter(int family, int which, int mode, int grid,
     return hipGetLastError();
 }
 
-hipError_t launch_classify(const double *r64, uint8_t *cls, int64_t n, int round,
-                           unsigned long long *words, hipStream_t s)
+// Encoding with classes (cls, words and the tables given) or without.
+hipError_t launch_setup(const double *rho, const uint8_t *mask, double *r64, float *r32,
+                        uint8_t *cls, int64_t n, int *bad, unsigned long long *words, double *t64,
+                        float *t32, hipStream_t s)
 {
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
+    // four cells a thread where the caller's arrays and the grid allow, else
+    // one; eight workgroups a CU cover the latency
+    const bool wide = n % 4 == 0 && (uintptr_t)rho % 32 == 0 && (uintptr_t)mask % 4 == 0;
+    const int64_t groups = wide ? n / 4 : n;
+    int64_t blocks = (groups + 255) / 256;
+    if (blocks > 2048) blocks = 2048;
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_classify, dim3((unsigned)blocks), dim3(256), 0, s, r64, cls,
-                       n, round, words);
-    return hipGetLastError();
-}
-
-hipError_t launch_encode(const double *rho, const uint8_t *mask, double *r64,
-                         float *r32, int64_t n, int *bad, hipStream_t s)
-{
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_encode, dim3((unsigned)blocks), dim3(256), 0, s, rho,
-                       mask, r64, r32, n, bad);
+    if (cls) hipLaunchKernelGGL(k_seed, dim3(1), dim3(256), 0, s, rho, mask, n, words);
+    if (wide)
+        hipLaunchKernelGGL((k_encode<4>), dim3((unsigned)blocks), dim3(256), 0, s, rho, mask, r64,
+                           r32, cls, n, bad, words);
+    else
+        hipLaunchKernelGGL((k_encode<1>), dim3((unsigned)blocks), dim3(256), 0, s, rho, mask, r64,
+                           r32, cls, n, bad, words);
+    if (cls)
+        hipLaunchKernelGGL(k_tables, dim3(1), dim3(kClasses * kClasses), 0, s, words, t64, t32);
     return hipGetLastError();
 }
 
