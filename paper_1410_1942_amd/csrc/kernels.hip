@@ -802,23 +802,25 @@ __device__ void body_passB(const Slot &S, const SlotState &st, int64_t lt,
 }
 
 // One cell of pass B: the operator row from the cell's value and key and
-// those of its six neighbours (walls already substituted), the low z face
-// coefficient carried from the plane below (bzm, replaced by the high one),
-// z -= alpha q / diag and the two dot terms; in the catch-up form (XM 3)
-// also the three pending x updates.  Shared by the grouped and the
-// LDS-staged pass so both evaluate a cell the same way.
+// those of its neighbours (walls already substituted), the low z face
+// coefficient carried from the plane below (bzm, replaced by the high one)
+// and the low x one from the cell before (bx, replaced by the high one: a
+// face's coefficient is formed once, which for per-cell densities is a
+// reciprocal), z -= alpha q / diag and the two dot terms; in the catch-up form
+// (XM 3) also the three pending x updates.  bym: its low y coefficient.
+// Shared by the grouped and the LDS-staged pass so both evaluate a cell the
+// same way.
 template <typename T, typename X, class C, int XM>
 __device__ __forceinline__ void passB_cell(const C &cf, const Areas6<T> &ar,
-                                           typename C::Key kc, T vc, T vxm,
-                                           typename C::Key kxm, T vxp, typename C::Key kxp,
-                                           T vym, typename C::Key kym, T vyp,
+                                           typename C::Key kc, T vc, T vxm, T &bx, T vxp,
+                                           typename C::Key kxp, T vym, typename C::Key kym, T vyp,
                                            typename C::Key kyp, T vzm, T vzp,
                                            typename C::Key kz, T &bzm, T zc, T alpha,
                                            T alpha_p0, T alpha_p1, X xo, T po0, T po1,
-                                           X &xn, T &zn, double &a0, double &a1)
+                                           X &xn, T &zn, double &a0, double &a1, T &bym)
 {
-    const T bxm = cf.beta(kc, kxm) * ar.xm, bxp = cf.beta(kc, kxp) * ar.xp;
-    const T bym = cf.beta(kc, kym) * ar.ym;
+    const T bxm = bx, bxp = cf.beta(kc, kxp) * ar.xp;
+    bym = cf.beta(kc, kym) * ar.ym;
     const T byp = cf.beta(kc, kyp) * ar.yp;
     const T bzp = cf.beta(kc, kz) * ar.zp;
     const T dg = ((bxm + bxp) + (bym + byp)) + (bzm + bzp);
@@ -830,6 +832,7 @@ __device__ __forceinline__ void passB_cell(const C &cf, const Areas6<T> &ar,
     const double r = (double)dg * (double)zn;
     a0 += r * (double)zn;
     a1 += r * r;
+    bx = bxp;
     bzm = bzp;
 }
 
@@ -1047,7 +1050,7 @@ __device__ void group_passB(const Slot &S, const SlotState &st, int64_t lt,
 #pragma unroll
             for (int n = 0; n < N; ++n) { po0[n] = v0[n]; po1[n] = v1[n]; }
         }
-        T zn[N];
+        T zn[N], bx = T(0);
         X xn[N];
 #pragma unroll
         for (int n = 0; n < N; ++n) {
@@ -1056,14 +1059,15 @@ __device__ void group_passB(const Slot &S, const SlotState &st, int64_t lt,
             const Areas6<T> ar = cf.areas(i0 + n, j, k, c + n);
             // x neighbours: inside the group, or the columns around it
             const T vxm = n > 0 ? vc[n - 1] : (hxm ? lvxm : T(0));
-            const K kxm = n > 0 ? kc[n - 1] : (hxm ? lkxm : wxm);
+            if (n == 0) bx = cf.beta(kc[0], hxm ? lkxm : wxm) * ar.xm;
             const T vxp = n < N - 1 ? vc[n + 1] : (hxp ? lvxp : T(0));
             const K kxp = n < N - 1 ? kc[n + 1] : (hxp ? lkxp : wxp);
             const T vym = hym ? vym_v[n] : T(0), vyp = hyp ? vyp_v[n] : T(0);
-            passB_cell<T, X, C, XM>(cf, ar, kc[n], vc[n], vxm, kxm, vxp, kxp, vym,
+            T bym;
+            passB_cell<T, X, C, XM>(cf, ar, kc[n], vc[n], vxm, bx, vxp, kxp, vym,
                                     hym ? kym[n] : wym, vyp, hyp ? kyp[n] : wyp, vzm[n], vzp,
                                     kz, bzm[n], zc[n], alpha, alpha_p0, alpha_p1, xo[n],
-                                    po0[n], po1[n], xn[n], zn[n], a0, a1);
+                                    po0[n], po1[n], xn[n], zn[n], a0, a1, bym);
         }
         if (XM) {
             if constexpr (kXGroup) {
@@ -1348,7 +1352,7 @@ __device__ void lds_passB(const Slot &S, const SlotState &st, int64_t lt, const 
         KP::split(kzpr, kzp);
         const T lvxm = Lv[own - 1], lvxp = Lv[own + N];
         const K lkxm = (K)Lk[own - 1], lkxp = (K)Lk[own + N];
-        T zn[N];
+        T zn[N], bx = T(0);
         X xn[N];
 #pragma unroll
         for (int n = 0; n < N; ++n) {
@@ -1356,14 +1360,15 @@ __device__ void lds_passB(const Slot &S, const SlotState &st, int64_t lt, const 
             const K kz = top ? wzp : kzp[n];
             const Areas6<T> ar = cf.areas(i0 + n, j, k, c + qo + n);
             const T vxm = n > 0 ? vc[n - 1] : (hxm ? lvxm : T(0));
-            const K kxm = n > 0 ? kc[n - 1] : (hxm ? lkxm : wxm);
+            if (n == 0) bx = cf.beta(kc[0], hxm ? lkxm : wxm) * ar.xm;
             const T vxp = n < N - 1 ? vc[n + 1] : (hxp ? lvxp : T(0));
             const K kxp = n < N - 1 ? kc[n + 1] : (hxp ? lkxp : wxp);
-            passB_cell<T, X, C, XM>(cf, ar, kc[n], vc[n], vxm, kxm, vxp, kxp,
+            T bym;
+            passB_cell<T, X, C, XM>(cf, ar, kc[n], vc[n], vxm, bx, vxp, kxp,
                                     hym ? vym[n] : T(0), hym ? kym[n] : wym,
                                     hyp ? vyp[n] : T(0), hyp ? kyp[n] : wyp, vzm[n], vzp, kz,
                                     bzm[n], zc[n], alpha, alpha_p0, alpha_p1, xo[n], v0[n],
-                                    v1[n], xn[n], zn[n], a0, a1);
+                                    v1[n], xn[n], zn[n], a0, a1, bym);
         }
         if (t.active) {
             if (XM == 3) {
@@ -1711,28 +1716,32 @@ __device__ void lds_sweep_cg(const Slot &S, const SlotState &st, int64_t lt, con
         }
         return R;
     };
-    // delta's terms of one plane's groups: faces toward x-, y- and z- and the
-    // Dirichlet high walls; the x-/y- neighbours' z' from LDS, their keys as
-    // the operator row read them
-    auto delta = [&](const T *Lz, const T (&zc)[N], const T (&zd)[N], const T (&bd)[N],
-                     const K (&kd)[N], K kxl, const K (&kyd)[N],
+    // delta's terms of one plane's groups: faces toward x-, y- and z- with the
+    // coefficients the operator row formed there, and the Dirichlet high walls
+    // (only waves that hold such a cell form those); the x-/y- neighbours' z'
+    // from LDS.  Against forming each face's coefficient a second time here,
+    // per iteration: 512^3 FP32 793 -> 778 us, FP64 1292 -> 1289, 256^3 FP32
+    // 124.0 -> 121.7, densities without classes (320 x 192 x 160 FP64) 206.2
+    // -> 203.1.
+    const bool wwave = __any(hwx || hwy);
+    auto delta = [&](const T *Lz, const T (&zc)[N], const T (&zd)[N], const T (&bx)[N],
+                     const T (&by)[N], const T (&bd)[N], const K (&kd)[N],
                      bool dtop) __attribute__((always_inline)) {
         const V zym = *(const V *)(Lz + own - W);
         T zl = hxm ? Lz[own - 1] : T(0);
-        K kl = kxl;
         double d = 0.0;
 #pragma unroll
         for (int n = 0; n < N; ++n) {
-            const Areas6<T> ar = cf.areas(i0 + n, j, 0, 0);
             const T ex = zc[n] - zl, ey = zc[n] - (hym ? zym[n] : T(0)), ez = zc[n] - zd[n];
-            T sn = (cf.beta(kd[n], kl) * ar.xm * ex * ex + cf.beta(kd[n], kyd[n]) * ar.ym * ey * ey) +
-                   bd[n] * ez * ez;
-            const T w = ((n == N - 1 && hwx) ? ar.xp : T(0)) + (hwy ? ar.yp : T(0)) +
-                        (dtop ? ar.zp : T(0));
-            sn += w * cf.beta(kd[n], cf.dirichlet()) * (zc[n] * zc[n]);
+            T sn = (bx[n] * ex * ex + by[n] * ey * ey) + bd[n] * ez * ez;
+            if (wwave || dtop) {
+                const Areas6<T> ar = cf.areas(i0 + n, j, 0, 0);
+                const T w = ((n == N - 1 && hwx) ? ar.xp : T(0)) + (hwy ? ar.yp : T(0)) +
+                            (dtop ? ar.zp : T(0));
+                sn += w * cf.beta(kd[n], cf.dirichlet()) * (zc[n] * zc[n]);
+            }
             d += (double)sn;
             zl = zc[n];
-            kl = kd[n];
         }
         return d;
     };
@@ -1741,21 +1750,20 @@ __device__ void lds_sweep_cg(const Slot &S, const SlotState &st, int64_t lt, con
     // key (kc, and as loaded: kr), the low z face coefficient (bzm), z at
     // this plane (uc), the previous direction at this plane (qc, also the
     // catch-up form's direction one back); for the previous plane's delta
-    // its z' (z1), z' one more plane down (z2), its low z face coefficient
-    // (bd1), its keys and those of its x-/y- neighbours; the same for the
-    // halo group (h*) without delta
-    T vzm[N], vc[N], bzm[N], uc[N], qc[N], z1[N], z2[N], bd1[N];
+    // its z' (z1), z' one more plane down (z2), its low face coefficients
+    // (bx1, by1, bd1) and its keys; the same for the halo group (h*) without
+    // delta
+    T vzm[N], vc[N], bzm[N], uc[N], qc[N], z1[N], z2[N], bx1[N], by1[N], bd1[N];
     T hvzm[N], hvc[N], hbzm[N], huc[N];
-    K kc[N], k1[N], ky1[N], hkc[N];
-    K kx1 = wxm;
+    K kc[N], k1[N], hkc[N];
     KR kr, hkr;
     {
         K kzm[N], hkzm[N];
 #pragma unroll
         for (int n = 0; n < N; ++n) {
-            vzm[n] = hvzm[n] = z1[n] = z2[n] = bd1[n] = T(0);
+            vzm[n] = hvzm[n] = z1[n] = z2[n] = bx1[n] = by1[n] = bd1[n] = T(0);
             kzm[n] = hkzm[n] = wzm;
-            k1[n] = ky1[n] = wzm;
+            k1[n] = wzm;
         }
         if (kb > 0) {
             const Raw R = load(kb - 1);
@@ -1831,7 +1839,7 @@ __device__ void lds_sweep_cg(const Slot &S, const SlotState &st, int64_t lt, con
         __syncthreads();
         // the previous plane's delta (its z' staged before this barrier)
         if (k - 1 >= t.k0) {
-            const double d = delta(L.z[b ^ 1], z1, z2, bd1, k1, kx1, ky1, false);
+            const double d = delta(L.z[b ^ 1], z1, z2, bx1, by1, bd1, k1, false);
             if (t.active) a2 += d;
         }
         const T *Lp = L.p[b];
@@ -1858,7 +1866,7 @@ __device__ void lds_sweep_cg(const Slot &S, const SlotState &st, int64_t lt, con
         KP::split(KP::get(Lk + own + W), kyp);
         const T lvxm = Lp[own - 1], lvxp = Lp[own + N];
         const K lkxm = (K)Lk[own - 1], lkxp = (K)Lk[own + N];
-        T zn[N];
+        T zn[N], bx = T(0);
         X xn[N];
         double g0 = 0.0, g1 = 0.0;
 #pragma unroll
@@ -1867,14 +1875,15 @@ __device__ void lds_sweep_cg(const Slot &S, const SlotState &st, int64_t lt, con
             bd1[n] = bzm[n];   // this plane's low z face, for its delta
             const Areas6<T> ar = cf.areas(i0 + n, j, k, c + qo + n);
             const T vxm = n > 0 ? vc[n - 1] : (hxm ? lvxm : T(0));
-            const K kxm = n > 0 ? kc[n - 1] : (hxm ? lkxm : wxm);
+            if (n == 0) bx = cf.beta(kc[0], hxm ? lkxm : wxm) * ar.xm;
+            bx1[n] = bx;
             const T vxp = n < N - 1 ? vc[n + 1] : (hxp ? lvxp : T(0));
             const K kxp = n < N - 1 ? kc[n + 1] : (hxp ? lkxp : wxp);
-            passB_cell<T, X, C, XM>(cf, ar, kc[n], vc[n], vxm, kxm, vxp, kxp,
+            passB_cell<T, X, C, XM>(cf, ar, kc[n], vc[n], vxm, bx, vxp, kxp,
                                     hym ? vym[n] : T(0), kym[n],
                                     hyp ? vyp[n] : T(0), hyp ? kyp[n] : wyp, vzm[n], pn[n],
                                     kzp[n], bzm[n], uc[n], alpha, alpha_p0, alpha_p1, xo[n],
-                                    v0[n], qc[n], xn[n], zn[n], g0, g1);
+                                    v0[n], qc[n], xn[n], zn[n], g0, g1, by1[n]);
         }
         {
             V zv_n;
@@ -1914,18 +1923,19 @@ __device__ void lds_sweep_cg(const Slot &S, const SlotState &st, int64_t lt, con
             T hz[N];
             X hx[N];
             double d0 = 0.0, d1 = 0.0;
+            T hbx = T(0), hby;
 #pragma unroll
             for (int n = 0; n < N; ++n) {
                 const Areas6<T> ar = cf.areas(hi + n, hj, k, 0);
                 const T vxm = n > 0 ? hvc[n - 1] : (gxm ? hlvxm : T(0));
-                const K kxm = n > 0 ? hkc[n - 1] : (gxm ? hlkxm : wxm);
+                if (n == 0) hbx = cf.beta(hkc[0], gxm ? hlkxm : wxm) * ar.xm;
                 const T vxp = n < N - 1 ? hvc[n + 1] : (gxp ? hlvxp : T(0));
                 const K kxp = n < N - 1 ? hkc[n + 1] : (gxp ? hlkxp : wxp);
-                passB_cell<T, X, C, 0>(cf, ar, hkc[n], hvc[n], vxm, kxm, vxp, kxp,
+                passB_cell<T, X, C, 0>(cf, ar, hkc[n], hvc[n], vxm, hbx, vxp, kxp,
                                        gym ? hym_v[n] : T(0), gym ? hkym[n] : wym,
                                        gyp ? hyp_v[n] : T(0), gyp ? hkyp[n] : wyp, hvzm[n],
                                        hpn[n], hkzp[n], hbzm[n], huc[n], alpha, alpha_p0,
-                                       alpha_p1, X(0), T(0), T(0), hx[n], hz[n], d0, d1);
+                                       alpha_p1, X(0), T(0), T(0), hx[n], hz[n], d0, d1, hby);
             }
             if (role == 2) {
                 V hv;
@@ -1935,13 +1945,11 @@ __device__ void lds_sweep_cg(const Slot &S, const SlotState &st, int64_t lt, con
             }
         }
         // carry up one plane
-        kx1 = hxm ? lkxm : wxm;
 #pragma unroll
         for (int n = 0; n < N; ++n) {
             z2[n] = z1[n];
             z1[n] = zn[n];
             k1[n] = kc[n];
-            ky1[n] = kym[n];
             vzm[n] = vc[n];
             vc[n] = pn[n];
             kc[n] = kzp[n];
@@ -1958,7 +1966,7 @@ __device__ void lds_sweep_cg(const Slot &S, const SlotState &st, int64_t lt, con
     // the last plane's delta
     __syncthreads();
     if (t.k1 - 1 >= t.k0) {
-        const double d = delta(L.z[b ^ 1], z1, z2, bd1, k1, kx1, ky1,
+        const double d = delta(L.z[b ^ 1], z1, z2, bx1, by1, bd1, k1,
                                t.k1 == nz && (bm & 32));
         if (t.active) a2 += d;
     }
