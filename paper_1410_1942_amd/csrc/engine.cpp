@@ -339,6 +339,24 @@ Geometry make_geometry(const pcg_grid_t &g, int prec, int tz_opt, bool batch, in
     return G;
 }
 
+// Planes a tile of a solve with cut-cell fractions: at most one tile a CU.
+// Its two passes read five arrays beside the vectors, and two workgroups a CU
+// run them slower than one after the other: per iteration 192 x 160 x 144
+// FP64 480 tiles (18 planes) 149 us on 512 workgroups, 120 on 256, and 240
+// tiles (36) 113; 128^3 352 tiles 102, 256 79, 192 81; 160 x 140 x 160 440
+// tiles 137, 220 109; 192 x 160 x 144 FP32 360 tiles 126, 240 96, 180 100.
+// Tiles of one height, too: 192 x 160 x 144 FP64 in chunks of 64, 64 and 16
+// planes 150, of 48 124 (its four chunks of 36 would need more partial sums
+// than the plain form's tiles, which the workspace is sized for).
+constexpr int kFracTiles = 256;
+
+int frac_tz(const Geometry &G)
+{
+    const int64_t chunks = std::min<int64_t>(kFracTiles, G.ntiles) / G.plane_tiles;
+    if (chunks < 1) return G.tz;
+    return (int)((G.nz + chunks - 1) / chunks);
+}
+
 // Bytes of the four fraction arrays of a grid (FP64 MAC faces and cells).
 size_t frac_bytes(const Geometry &G)
 {
@@ -640,6 +658,8 @@ struct SlotHost {
     bool running = false;   // in the slot table
     bool finished = false;  // completion observed on the host
     Geometry geo{};
+    int plain_tz = 0;        // planes a tile without fractions, and its tile count
+    int64_t plain_tiles = 0; // (partial sums are reserved for these)
     int bcmask = 0;
     int permask = 0;
     bool singular = false;   // no Dirichlet wall reaches the fluid
@@ -861,6 +881,24 @@ struct Engine {
         d.vol = S.has_frac ? S.vol : nullptr;
     }
 
+    // Tile height of a slot, which depends on whether it has fractions (single
+    // solves; a caller's own height stands).
+    void set_tile_height(SlotHost &S)
+    {
+        Geometry &G = S.geo;
+        auto cut = [&](int tz) {
+            G.tz = tz;
+            G.ztiles = (G.nz + tz - 1) / tz;
+            G.ntiles = (int64_t)G.plane_tiles * G.ztiles;
+        };
+        cut(S.plain_tz);
+        if (S.has_frac && !batch_mode() && tz_opt == 0) {
+            const int64_t cap = kMaxTileBytes / ((int64_t)G.nx * G.ny * 8) - 2;
+            const int tz = frac_tz(G);
+            if (tz <= cap) cut(tz);
+        }
+    }
+
     // Cut-cell fractions for a prepared slot that is not running: copy the
     // caller's arrays into the slot's reserved space and validate them on the
     // device (areas in [0, 1], fluid volumes in (0, 1]); all NULL clears.
@@ -875,6 +913,7 @@ struct Engine {
         if (view_id == id) view_id = -1;
         table_dirty = true;
         S.has_frac = false;
+        set_tile_height(S);
         if (!given) return PCG_OK;
         if (!S.ax) return PCG_EINVAL;   // no room reserved (PCG_FRACTIONS not set)
         const size_t nx = S.geo.nx, ny = S.geo.ny, nz = S.geo.nz;
@@ -894,6 +933,7 @@ struct Engine {
         if (e != hipSuccess) return hip_fail(e, "fractions");
         if (*h_bad) return PCG_EDOMAIN;
         S.has_frac = true;
+        set_tile_height(S);
         return PCG_OK;
     }
 
@@ -956,6 +996,8 @@ struct Engine {
         SlotHost &S = slots[id];
         S = SlotHost{};
         S.geo = geo;
+        S.plain_tz = geo.tz;
+        S.plain_tiles = geo.ntiles;
         S.bcmask = bm;
         S.permask = per;
         S.h2 = grid_->h * grid_->h;
@@ -1165,7 +1207,7 @@ struct Engine {
             d.d32 = S.d32;
             d.partials = S.partials;
             d.st = d_states + id;
-            d.cls = S.classes && !S.has_frac ? S.cls : nullptr;
+            d.cls = S.classes ? S.cls : nullptr;
             set_frac(d, S);
             d.tab64 = S.tab64;
             d.tab32 = S.tab32;
@@ -1802,7 +1844,7 @@ int pcg_divergence(pcg_ctx_t *c, const double *u, const double *v, const double 
     if (st) return st;
     const SlotHost &S = c->eng.slots[c->slot];
     // one partial pair per workgroup, in the slot's partial-sum buffer
-    const int64_t room = kMaxPartials * S.geo.ntiles / 2;
+    const int64_t room = kMaxPartials * S.plain_tiles / 2;
     const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>({ project_blocks(S), 4096, room }));
     HIP_TRY(launch_divnorm(ds, 1.0 / std::sqrt(S.h2), u, v, w, S.partials, (int)blocks,
                            c->eng.stream));

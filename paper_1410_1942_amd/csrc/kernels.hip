@@ -221,6 +221,32 @@ template <typename T, int N> struct VecN {
     typedef T type __attribute__((ext_vector_type(N)));
 };
 
+// Area fractions of N adjacent cells' faces (N + 1 x faces: cell n's high one
+// is cell n + 1's low one): the low ones, and those toward the high neighbours.
+template <typename T, int N>
+struct LowAreas {
+    T x[N], y[N], z[N];
+    static __device__ __forceinline__ LowAreas ones()
+    {
+        LowAreas a;
+#pragma unroll
+        for (int n = 0; n < N; ++n) a.x[n] = a.y[n] = a.z[n] = T(1);
+        return a;
+    }
+};
+template <typename T, int N>
+struct HighAreas {
+    T x, y[N], z[N];   // x: of the last cell
+    static __device__ __forceinline__ HighAreas ones()
+    {
+        HighAreas a;
+        a.x = T(1);
+#pragma unroll
+        for (int n = 0; n < N; ++n) a.y[n] = a.z[n] = T(1);
+        return a;
+    }
+};
+
 template <typename T>
 struct RhoCoef {
     using Key = T;
@@ -241,6 +267,14 @@ struct RhoCoef {
     __device__ __forceinline__ Areas6<T> areas(int, int, int, int64_t) const
     {
         return { T(1), T(1), T(1), T(1), T(1), T(1) };
+    }
+    template <int N> __device__ __forceinline__ LowAreas<T, N> low_areas(int, int, int, int64_t) const
+    {
+        return LowAreas<T, N>::ones();
+    }
+    template <int N> __device__ __forceinline__ HighAreas<T, N> high_areas(int, int, int, int64_t) const
+    {
+        return HighAreas<T, N>::ones();
     }
 };
 
@@ -269,54 +303,103 @@ struct ClsCoef {
     {
         return { T(1), T(1), T(1), T(1), T(1), T(1) };
     }
+    template <int N> __device__ __forceinline__ LowAreas<T, N> low_areas(int, int, int, int64_t) const
+    {
+        return LowAreas<T, N>::ones();
+    }
+    template <int N> __device__ __forceinline__ HighAreas<T, N> high_areas(int, int, int, int64_t) const
+    {
+        return HighAreas<T, N>::ones();
+    }
 };
 
-// Per-cell density with free-slip cut cells: the density key of RhoCoef and
+// Free-slip cut cells: the keys of KC (per-cell density, or its classes) and
 // the area fractions of the MAC faces (FP64, converted for FP32 passes).  On
 // a periodic axis the face beyond the last cell is the row's face 0.
-template <typename T>
-struct FracCoef {
-    using Key = T;
-    const GLB T *__restrict__ rho;
+// The passes are bound by what they read (pass A 49 B a cell with class keys,
+// pass B 51, a quarter of it the fractions of each direction) and by a wave's
+// wait for it, plane after plane: fractions come in groups, pass A's a plane
+// ahead, and the high faces only where a Dirichlet wall needs them.  192 x 160
+// x 144 FP64 per iteration: six loads a cell and density keys 177 us, groups
+// 163, class keys 151 (all with 64 planes a tile; 124 at 48).  A plane ahead
+// in pass B too: 122 against 113 (36 planes), its registers cost more.
+template <typename T, class KC>
+struct FracCoef : KC {
     const GLB double *__restrict__ ax;
     const GLB double *__restrict__ ay;
     const GLB double *__restrict__ az;
     int nx, ny;
     int64_t P;
     bool perx, pery;
-    __device__ __forceinline__ Key load(int64_t c) const { return rho[c]; }
-    template <int N>
-    __device__ __forceinline__ void loadN(int64_t c, Key (&k)[N]) const
+    __device__ __forceinline__ FracCoef(const Slot &S, const KC &key)
+        : KC(key), ax(gp(S.ax)), ay(gp(S.ay)), az(gp(S.az)), nx(S.nx), ny(S.ny),
+          P((int64_t)S.nx * S.ny), perx(S.permask & 1), pery(S.permask & 2)
     {
-        using V = typename VecN<T, N>::type;
-        const V v = ((const GLB V *)rho)[c / N];
-#pragma unroll
-        for (int n = 0; n < N; ++n) k[n] = v[n];
     }
-    __device__ __forceinline__ Key dirichlet() const { return T(0); }
-    __device__ __forceinline__ Key neumann() const { return (T)INFINITY; }
-    __device__ __forceinline__ bool solid(Key k) const { return isinf(k); }
-    __device__ __forceinline__ T beta(Key a, Key b) const { return fb(a + b); }
+    __device__ __forceinline__ int64_t u_face(int i, int j, int k) const
+    {
+        return ((int64_t)k * ny + j) * (nx + 1) + i;
+    }
+    __device__ __forceinline__ int64_t v_face(int i, int j, int k) const
+    {
+        return ((int64_t)k * (ny + 1) + j) * nx + i;
+    }
+    // the face above cell (i, j, .), from its low face
+    __device__ __forceinline__ int64_t u_high(int i, int64_t fu) const
+    {
+        return (perx && i == nx - 1) ? fu - i : fu + 1;
+    }
+    __device__ __forceinline__ int64_t v_high(int j, int64_t fv) const
+    {
+        return (pery && j == ny - 1) ? fv - (int64_t)j * nx : fv + nx;
+    }
     __device__ __forceinline__ Areas6<T> areas(int i, int j, int k, int64_t c) const
     {
-        const int64_t fu = ((int64_t)k * ny + j) * (nx + 1) + i;
-        const int64_t fv = ((int64_t)k * (ny + 1) + j) * nx + i;
+        const int64_t fu = u_face(i, j, k), fv = v_face(i, j, k);
         Areas6<T> a;
         a.xm = (T)ax[fu];
-        a.xp = (T)ax[(perx && i == nx - 1) ? fu - i : fu + 1];
+        a.xp = (T)ax[u_high(i, fu)];
         a.ym = (T)ay[fv];
-        a.yp = (T)ay[(pery && j == ny - 1) ? fv - (int64_t)j * nx : fv + nx];
+        a.yp = (T)ay[v_high(j, fv)];
         a.zm = (T)az[c];
         a.zp = (T)az[c + P];
+        return a;
+    }
+    // N cells from (i, j, k), cell c; i and nx multiples of N, so y and z
+    // faces are aligned groups (x faces begin anywhere: rows of nx + 1)
+    template <int N> __device__ __forceinline__ LowAreas<T, N> low_areas(int i, int j, int k, int64_t c) const
+    {
+        using D = typename VecN<double, N>::type;
+        using U = double __attribute__((ext_vector_type(N), aligned(8)));
+        const U x = *(const GLB U *)(ax + u_face(i, j, k));
+        const D y = *(const GLB D *)(ay + v_face(i, j, k)), z = *(const GLB D *)(az + c);
+        LowAreas<T, N> a;
+#pragma unroll
+        for (int n = 0; n < N; ++n) { a.x[n] = (T)x[n]; a.y[n] = (T)y[n]; a.z[n] = (T)z[n]; }
+        return a;
+    }
+    template <int N> __device__ __forceinline__ HighAreas<T, N> high_areas(int i, int j, int k, int64_t c) const
+    {
+        using D = typename VecN<double, N>::type;
+        const int last = i + N - 1;
+        const D y = *(const GLB D *)(ay + v_high(j, v_face(i, j, k))), z = *(const GLB D *)(az + c + P);
+        HighAreas<T, N> a;
+        a.x = (T)ax[u_high(last, u_face(last, j, k))];
+#pragma unroll
+        for (int n = 0; n < N; ++n) { a.y[n] = (T)y[n]; a.z[n] = (T)z[n]; }
         return a;
     }
 };
 
 template <typename T>
-__device__ __forceinline__ FracCoef<T> frac_coef(const Slot &S, const T *rho)
+__device__ __forceinline__ FracCoef<T, RhoCoef<T>> frac_coef(const Slot &S, const T *rho)
 {
-    return { gp(rho), gp(S.ax), gp(S.ay), gp(S.az), S.nx, S.ny, (int64_t)S.nx * S.ny,
-             (S.permask & 1) != 0, (S.permask & 2) != 0 };
+    return { S, RhoCoef<T>{ gp(rho) } };
+}
+template <typename T>
+__device__ __forceinline__ FracCoef<T, ClsCoef<T>> frac_coef(const Slot &S, const ClsCoef<T> &key)
+{
+    return { S, key };
 }
 
 // Volume fraction of cell c (1 without cut cells): weights the source.
@@ -624,12 +707,10 @@ template <typename T>
 __device__ __forceinline__ const void *key_array(const RhoCoef<T> &cf) { return (const void *)cf.rho; }
 template <typename T>
 __device__ __forceinline__ const void *key_array(const ClsCoef<T> &cf) { return (const void *)cf.cls; }
-template <typename T>
-__device__ __forceinline__ const void *key_array(const FracCoef<T> &cf) { return (const void *)cf.rho; }
 template <class C> struct KeyElem;
 template <typename T> struct KeyElem<RhoCoef<T>> { using type = T; };
 template <typename T> struct KeyElem<ClsCoef<T>> { using type = uint8_t; };
-template <typename T> struct KeyElem<FracCoef<T>> { using type = T; };
+template <typename T, class KC> struct KeyElem<FracCoef<T, KC>> : KeyElem<KC> {};
 
 // K1_CG_A / K1_IR_A: p_new = z + beta p_old, stored; the quadratic form
 // p.Ap = sum over faces of beta_f (p_c - p_n)^2, each face counted once
@@ -641,6 +722,7 @@ template <typename T, typename K>
 struct PlaneA {
     T zc, qc, zxm, qxm, zym, qym;
     K kc, kxm, kym;
+    LowAreas<T, 1> lo;
 };
 
 template <typename T, class C>
@@ -669,6 +751,7 @@ __device__ void body_passA(const Slot &S, const SlotState &st, int64_t lt,
     const int bm = S.bcmask;
     // Dirichlet high walls of this column (x+, y+); z+ is added on the top plane
     const bool hwx = !n.hxp && (bm & 2), hwy = !n.hyp && (bm & 8);
+    const bool wwave = __any(hwx || hwy);
     const int nz = S.nz;
     auto load = [&](int kk) {
         kk = kk < t.k1 ? kk : t.k1 - 1;    // past the tile's end: re-read its last plane
@@ -679,6 +762,7 @@ __device__ void body_passA(const Slot &S, const SlotState &st, int64_t lt,
         L.kxm = bload<KE>(bk, ok.xm, sk); L.kym = bload<KE>(bk, ok.ym, sk);
         L.zc = bload<T>(bz, ov.c, sv); L.qc = bload<T>(bps, ov.c, sv);
         L.kc = bload<KE>(bk, ok.c, sk);
+        L.lo = cf.template low_areas<1>(t.i, t.j, kk, (int64_t)kk * t.P + t.q);
         return L;
     };
     T pzm = T(0);
@@ -695,14 +779,17 @@ __device__ void body_passA(const Slot &S, const SlotState &st, int64_t lt,
         const T pxm = n.hxm ? L.zxm + beta * L.qxm : T(0);
         const T pym = n.hym ? L.zym + beta * L.qym : T(0);
         const T dx = pc - pxm, dy = pc - pym, dz = pc - pzm;
-        const Areas6<T> ar = cf.areas(t.i, t.j, kk, (int64_t)kk * t.P + t.q);
-        T s = (cf.beta(L.kc, kxm) * ar.xm * dx * dx + cf.beta(L.kc, kym) * ar.ym * dy * dy) +
-              cf.beta(L.kc, kzm) * ar.zm * dz * dz;
+        T s = (cf.beta(L.kc, kxm) * L.lo.x[0] * dx * dx + cf.beta(L.kc, kym) * L.lo.y[0] * dy * dy) +
+              cf.beta(L.kc, kzm) * L.lo.z[0] * dz * dz;
         // Dirichlet high walls (x+, y+ of this column, z+ on the top plane),
         // each weighted by its area
-        const T w = (hwx ? ar.xp : T(0)) + (hwy ? ar.yp : T(0)) +
-                    ((kk == nz - 1 && (bm & 32)) ? ar.zp : T(0));
-        s += w * cf.beta(L.kc, cf.dirichlet()) * (pc * pc);   // + 0 without walls
+        const bool top = kk == nz - 1 && (bm & 32);
+        if (wwave || top) {
+            const HighAreas<T, 1> hi =
+                cf.template high_areas<1>(t.i, t.j, kk, (int64_t)kk * t.P + t.q);
+            const T w = (hwx ? hi.x : T(0)) + (hwy ? hi.y[0] : T(0)) + (top ? hi.z[0] : T(0));
+            s += w * cf.beta(L.kc, cf.dirichlet()) * (pc * pc);
+        }
         a += (double)s;
         bstore_nt(bpd, ov.c, W.so(kk, sizeof(T)), pc);
         pzm = pc;
@@ -851,6 +938,7 @@ template <typename T, typename K, int N>
 struct GroupA {
     T z[N], q[N], zy[N], qy[N], zx, qx;
     K k[N], ky[N], kx;
+    LowAreas<T, N> lo;
 };
 
 template <typename T, class C, int N>
@@ -879,6 +967,7 @@ __device__ void group_passA(const Slot &S, const SlotState &st, int64_t lt,
     // Dirichlet high walls: x+ of the last cell, y+ of all
     const bool hwx = !(i0 + N - 1 < nx - 1 || px) && (bm & 2);
     const bool hwy = !(j < ny - 1 || py) && (bm & 8);
+    const bool wwave = __any(hwx || hwy);
     const K wxm = (bm & 1) ? cf.dirichlet() : cf.neumann();
     const K wym = (bm & 4) ? cf.dirichlet() : cf.neumann();
     const K wzm = (bm & 16) ? cf.dirichlet() : cf.neumann();
@@ -899,6 +988,7 @@ __device__ void group_passA(const Slot &S, const SlotState &st, int64_t lt,
         L.zx = bload<T>(bz, vx, sv);
         L.qx = bload<T>(bps, vx, sv);
         L.kx = bload<KE>(bk, kx, sk);
+        L.lo = cf.template low_areas<N>(i0, j, kk, (int64_t)kk * t.P + t.q);
         return L;
     };
     T pzm[N];
@@ -916,8 +1006,9 @@ __device__ void group_passA(const Slot &S, const SlotState &st, int64_t lt,
     }
     double a = 0.0;
     auto step = [&](const GroupA<T, K, N> &L, int kk) {
-        const int64_t c0 = (int64_t)kk * t.P + t.q;
         const bool top = kk == nz - 1 && (bm & 32);
+        HighAreas<T, N> hi;
+        if (wwave || top) hi = cf.template high_areas<N>(i0, j, kk, (int64_t)kk * t.P + t.q);
         T pl = hxm ? L.zx + beta * L.qx : T(0);   // x- value of the next cell
         K kl = hxm ? L.kx : wxm;
         T p[N];
@@ -926,13 +1017,15 @@ __device__ void group_passA(const Slot &S, const SlotState &st, int64_t lt,
             p[n] = L.z[n] + beta * L.q[n];
             const T pym = hym ? L.zy[n] + beta * L.qy[n] : T(0);
             const K kym = hym ? L.ky[n] : wym;
-            const Areas6<T> ar = cf.areas(i0 + n, j, kk, c0 + n);
             const T dx = p[n] - pl, dy = p[n] - pym, dz = p[n] - pzm[n];
-            T sn = (cf.beta(L.k[n], kl) * ar.xm * dx * dx + cf.beta(L.k[n], kym) * ar.ym * dy * dy) +
-                   cf.beta(L.k[n], kzm[n]) * ar.zm * dz * dz;
-            const T w = ((n == N - 1 && hwx) ? ar.xp : T(0)) + (hwy ? ar.yp : T(0)) +
-                        (top ? ar.zp : T(0));
-            sn += w * cf.beta(L.k[n], cf.dirichlet()) * (p[n] * p[n]);
+            T sn = (cf.beta(L.k[n], kl) * L.lo.x[n] * dx * dx +
+                    cf.beta(L.k[n], kym) * L.lo.y[n] * dy * dy) +
+                   cf.beta(L.k[n], kzm[n]) * L.lo.z[n] * dz * dz;
+            if (wwave || top) {
+                const T w = ((n == N - 1 && hwx) ? hi.x : T(0)) + (hwy ? hi.y[n] : T(0)) +
+                            (top ? hi.z[n] : T(0));
+                sn += w * cf.beta(L.k[n], cf.dirichlet()) * (p[n] * p[n]);
+            }
             a += (double)sn;
             pzm[n] = p[n];
             kzm[n] = L.k[n];
@@ -1019,6 +1112,8 @@ __device__ void group_passB(const Slot &S, const SlotState &st, int64_t lt,
     for (int k = t.k0; k < t.k1; ++k, c += P) {
         const bool top = k == S.nz - 1;
         const int64_t cz = top ? c : c + P;
+        const LowAreas<T, N> lo = cf.template low_areas<N>(i0, j, k, c);
+        const HighAreas<T, N> hi = cf.template high_areas<N>(i0, j, k, c);
         const V vzp_v = pv[cz / N];
         K kzp[N], kym[N], kyp[N];
         cf.template loadN<N>(cz, kzp);
@@ -1056,7 +1151,8 @@ __device__ void group_passB(const Slot &S, const SlotState &st, int64_t lt,
         for (int n = 0; n < N; ++n) {
             const T vzp = top ? T(0) : vzp_v[n];
             const K kz = top ? wzp : kzp[n];
-            const Areas6<T> ar = cf.areas(i0 + n, j, k, c + n);
+            const Areas6<T> ar = { lo.x[n], n < N - 1 ? lo.x[(n + 1) % N] : hi.x, lo.y[n], hi.y[n],
+                                   lo.z[n], hi.z[n] };
             // x neighbours: inside the group, or the columns around it
             const T vxm = n > 0 ? vc[n - 1] : (hxm ? lvxm : T(0));
             if (n == 0) bx = cf.beta(kc[0], hxm ? lkxm : wxm) * ar.xm;
@@ -2602,13 +2698,13 @@ __device__ __forceinline__ void run_body(int ph, const Slot &S,
         if (ph == K1_MEAN_X) { body_mean_x(S, st, lt, r64, acc); return; }
         if (ph == K1_FLUSH_X) { body_flush_x(S, st, lt, acc); return; }
         if (FAMILY == PCG_PREC_FP64) {
-            if (S.ax) run_k0_fp64(ph, S, st, lt, frac_coef<double>(S, S.rho64), acc);
+            if (S.ax) run_k0_fp64(ph, S, st, lt, frac_coef(S, S.rho64), acc);
             else if (S.cls) run_k0_fp64(ph, S, st, lt, c64, acc);
             else run_k0_fp64(ph, S, st, lt, r64, acc);
         } else {
             if (S.ax)
-                run_k0_ir(ph, S, st, lt, frac_coef<double>(S, S.rho64),
-                          frac_coef<float>(S, S.rho32), acc);
+                run_k0_ir(ph, S, st, lt, frac_coef(S, S.rho64),
+                          frac_coef(S, S.rho32), acc);
             else if (S.cls) run_k0_ir(ph, S, st, lt, c64, ClsCoef<float>{ gp(S.cls), tab32 }, acc);
             else run_k0_ir(ph, S, st, lt, r64, RhoCoef<float>{ gp(S.rho32) }, acc);
         }
@@ -2699,7 +2795,8 @@ __device__ __forceinline__ void run_body(int ph, const Slot &S,
     if (FAMILY == PCG_PREC_FP64) {
         if (WHICH == 1) {
             if (ph == K1_CG_A) {
-                if (MODE == 2) passA<double>(S, st, lt, frac_coef<double>(S, S.rho64), acc);
+                if (MODE == 2 && S.cls) passA<double>(S, st, lt, frac_coef(S, c64), acc);
+                else if (MODE == 2) passA<double>(S, st, lt, frac_coef(S, S.rho64), acc);
                 else if (MODE == 1) passA<double>(S, st, lt, c64, acc);
                 else passA<double>(S, st, lt, r64, acc);
             }
@@ -2708,9 +2805,15 @@ __device__ __forceinline__ void run_body(int ph, const Slot &S,
                 // x is read and written every third iteration (XM 0, 0, 3)
                 const bool catch_up = __builtin_amdgcn_readfirstlane(st.xpend) == 2;
                 if (MODE == 2) {
-                    const FracCoef<double> f = frac_coef<double>(S, S.rho64);
-                    if (catch_up) passB<double, double, FracCoef<double>, 3>(S, st, lt, f, acc);
-                    else passB<double, double, FracCoef<double>, 0>(S, st, lt, f, acc);
+                    if (S.cls) {
+                        const auto f = frac_coef(S, c64);
+                        if (catch_up) passB<double, double, std::decay_t<decltype(f)>, 3>(S, st, lt, f, acc);
+                        else passB<double, double, std::decay_t<decltype(f)>, 0>(S, st, lt, f, acc);
+                    } else {
+                        const auto f = frac_coef(S, S.rho64);
+                        if (catch_up) passB<double, double, std::decay_t<decltype(f)>, 3>(S, st, lt, f, acc);
+                        else passB<double, double, std::decay_t<decltype(f)>, 0>(S, st, lt, f, acc);
+                    }
                 } else if (MODE == 1) {
                     if (catch_up) passB<double, double, ClsCoef<double>, 3>(S, st, lt, c64, acc);
                     else passB<double, double, ClsCoef<double>, 0>(S, st, lt, c64, acc);
@@ -2726,7 +2829,8 @@ __device__ __forceinline__ void run_body(int ph, const Slot &S,
         const ClsCoef<float> c32{ gp(S.cls), tab32 };
         if (WHICH == 1) {
             if (ph == K1_IR_A) {
-                if (MODE == 2) passA<float>(S, st, lt, frac_coef<float>(S, S.rho32), acc);
+                if (MODE == 2 && S.cls) passA<float>(S, st, lt, frac_coef(S, c32), acc);
+                else if (MODE == 2) passA<float>(S, st, lt, frac_coef(S, S.rho32), acc);
                 else if (MODE == 1) passA<float>(S, st, lt, c32, acc);
                 else passA<float>(S, st, lt, r32, acc);
             }
@@ -2735,9 +2839,15 @@ __device__ __forceinline__ void run_body(int ph, const Slot &S,
                 // d is read and written every third iteration, as x in FP64
                 const bool catch_up = __builtin_amdgcn_readfirstlane(st.xpend) == 2;
                 if (MODE == 2) {
-                    const FracCoef<float> f = frac_coef<float>(S, S.rho32);
-                    if (catch_up) passB<float, float, FracCoef<float>, 3>(S, st, lt, f, acc);
-                    else passB<float, float, FracCoef<float>, 0>(S, st, lt, f, acc);
+                    if (S.cls) {
+                        const auto f = frac_coef(S, c32);
+                        if (catch_up) passB<float, float, std::decay_t<decltype(f)>, 3>(S, st, lt, f, acc);
+                        else passB<float, float, std::decay_t<decltype(f)>, 0>(S, st, lt, f, acc);
+                    } else {
+                        const auto f = frac_coef(S, S.rho32);
+                        if (catch_up) passB<float, float, std::decay_t<decltype(f)>, 3>(S, st, lt, f, acc);
+                        else passB<float, float, std::decay_t<decltype(f)>, 0>(S, st, lt, f, acc);
+                    }
                 } else if (MODE == 1) {
                     if (catch_up) passB<float, float, ClsCoef<float>, 3>(S, st, lt, c32, acc);
                     else passB<float, float, ClsCoef<float>, 0>(S, st, lt, c32, acc);
