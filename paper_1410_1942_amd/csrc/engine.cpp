@@ -412,18 +412,21 @@ ResidentPlan resident_bricks(const pcg_grid_t &g, int prec, const ResidentShape 
 // the whole grid.  A single solve takes the shape of the least estimated
 // time an iteration.  Solves of a batch share launches, so all of a
 // precision take the batch's shape, or the largest where that one does not
-// hold the grid.
+// hold the grid.  faces: the form that holds face coefficients (densities
+// without classes, cut cells; single solves).
 ResidentPlan resident_plan(const pcg_grid_t &g, int prec, const pcg_opts_t &o, bool batch,
-                           const ResidentShape *sh, const int *cap, int n)
+                           bool faces, const ResidentShape *sh, const int *cap, int n)
 {
     ResidentPlan best;
-    if (o.tz > 0 || o.grid_blocks > 0) return best;
-    if (o.flags & (PCG_FRACTIONS | PCG_FLAT_TILES | PCG_PLANE_TILES | PCG_TWO_SWEEPS |
+    if (o.tz > 0 || o.grid_blocks > 0 || (batch && faces)) return best;
+    // (room for fractions: consecutive tiles until there are any)
+    if ((o.flags & PCG_FRACTIONS) && !faces) return best;
+    if (o.flags & (PCG_FLAT_TILES | PCG_PLANE_TILES | PCG_TWO_SWEEPS |
                    PCG_NARROW_TILES))
         return best;
     double cost = 0.0;
     for (int i = 0; i < n; ++i) {
-        if (batch && !sh[i].batch) continue;
+        if (sh[i].faces != faces || (batch && !sh[i].batch)) continue;
         const ResidentPlan p = resident_bricks(g, prec, sh[i], i);
         if (p.shape < 0 || p.bricks() > cap[i]) continue;
         if (batch) return p;
@@ -678,7 +681,8 @@ struct SlotHost {
     int nclasses = 0;            // fluid classes when coded
     double *ax = nullptr, *ay = nullptr, *az = nullptr, *vol = nullptr;  // arena, if reserved
     bool has_frac = false;       // cut-cell fractions in use (coefficient mode 2)
-    ResidentPlan res;            // resident form, if the grid has one
+    ResidentPlan by_class, by_face;   // resident forms, if the grid has them
+    ResidentPlan res;            // that of the solve at hand
     unsigned long long *rsync = nullptr;   // its exchange words
     bool resident = false;       // the running solve takes it
     // of the running solve: its next stage, the trips since the host last
@@ -988,7 +992,10 @@ struct Engine {
         const bool sweep = one_sweep(geo, prec, flags | this->flags);
         pcg_opts_t ro = opts;
         ro.flags |= flags;
-        const ResidentPlan res = resident_plan(*grid_, prec, ro, batch_mode(), rshapes, rcap, nshapes);
+        const ResidentPlan by_class =
+            resident_plan(*grid_, prec, ro, batch_mode(), false, rshapes, rcap, nshapes);
+        const ResidentPlan by_face =
+            resident_plan(*grid_, prec, ro, batch_mode(), true, rshapes, rcap, nshapes);
         const size_t need = slot_bytes(geo, prec, frac_space, sweep);
         size_t off = 0;
         if (!alloc.alloc(need, &off)) return max_slots == 1 ? PCG_ENOMEM : PCG_EBUSY;
@@ -1030,8 +1037,9 @@ struct Engine {
         }
         // the resident kernel uses one direction buffer; its exchange words
         // live in the next, which every solve's set-up action zeroes
-        if (res.shape >= 0) {
-            S.res = res;
+        S.by_class = by_class;
+        S.by_face = by_face;
+        if (by_class.shape >= 0 || by_face.shape >= 0) {
             S.rsync = (unsigned long long *)S.dir1;
         }
 
@@ -1137,8 +1145,9 @@ struct Engine {
         h.inner_maxit = inner_maxit > 0 ? inner_maxit : INT32_MAX;
         h.inner_tol2 = inner_tol * inner_tol;
         h.warm = (flags & PCG_WARM_START) ? 1 : 0;
-        // classes on grids with a resident form, unless each launch is timed
-        S.resident = S.res.shape >= 0 && S.classes && !S.has_frac && !timing;
+        // grids with a resident form, unless each launch is timed
+        S.res = S.has_frac || !S.classes ? S.by_face : S.by_class;
+        S.resident = S.res.shape >= 0 && !timing && S.has_frac == frac_space;
         S.rstage = S.rtrips = S.rwaits = 0;
         h.resident = S.resident ? 1 : 0;
         h.fused = S.z2 && !S.resident ? 1 : 0;

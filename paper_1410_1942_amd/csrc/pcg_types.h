@@ -32,10 +32,12 @@ constexpr int res_halo(int cells) { return cells <= 2 ? 2 : cells <= 8 ? 4 : 8; 
 
 // A shape of the resident kernel: cols columns of planes cells a thread;
 // whether the row's results stay in registers between the halves of an
-// iteration; in batches the workgroups a CU holds of it (0: not for batches).
+// iteration; whether face coefficients are held (densities without classes,
+// cut cells) or looked up by class; in batches the workgroups a CU holds of
+// it (0: not for batches).
 struct ResidentShape {
     int cols, planes;
-    bool keep;
+    bool keep, faces;
     int batch;
 };
 

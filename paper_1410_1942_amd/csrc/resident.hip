@@ -23,6 +23,15 @@
 // FP32 32^3 16.4 -> 6.1, 64^3 21.7 -> 7.5, 128^3 48.6 -> 12.5, 320 x 128 x 96
 // 65.6 -> 20.1.
 //
+// Densities without classes and cut cells hold the face coefficients in
+// registers beside z and x (FACES), 16 words a cell FP64, which bounds them
+// to ten or twelve cells a thread.  Per iteration, launches against this:
+// densities FP64 32^3 17.6 -> 5.9 us, 64^3 24.2 -> 7.8, 96^3 44.2 -> 11.3,
+// 110 x 128 x 90 (twelve cells) 58.5 -> 17.8; FP32 32^3 16.2 -> 8.4 (100
+// iterations with their refinements), 128^3 59.0 -> 17.2, 150 x 141 x 133
+// 90 -> 25; cut cells FP64 64^3 32.8 -> 8.2, 96^3 59.6 -> 11.9; FP32 128^3
+// 88 -> 18.
+//
 // Exchange: a workgroup's sums go out as words of half a double beside a
 // 32-bit tag, the number of the exchange, written and read with relaxed
 // device-scope atomics (which reach the memory all XCDs share); a reader
@@ -111,6 +120,13 @@ __device__ __forceinline__ double recip(double d)
 }
 __device__ __forceinline__ float recip(float d) { return __builtin_amdgcn_rcpf(d); }
 
+// Face coefficient 2 / (a + b) of two cells' densities, 0 at solids (+inf).
+template <typename T>
+__device__ __forceinline__ T face_beta(T den)
+{
+    return den < (T)INFINITY ? T(2) * recip(den) : T(0);
+}
+
 __device__ __forceinline__ void *dir_buf(const Slot &S, int b)
 {
     return b == 0 ? S.dir0 : (b == 1 ? S.dir1 : S.dir2);
@@ -198,52 +214,57 @@ __device__ __forceinline__ bool all_sum(double (&v)[NV], GLB u64 *area, int G, i
     return *fail == 0;
 }
 
-// The operator row of one cell of a column: coefficients from the class
-// nibbles of its code (own, x-, x+, y-, y+, z-, z+), or one coefficient for
-// the whole wave where every cell of the column and its neighbours are of
-// one class (UNI; the x walls of a row then scale it by 0 or 2).
+// The operator row of one cell of a column, and its faces' share of p.A p.
 template <typename T>
 struct Row {
     T q, dg, s;
 };
 
-template <typename T, bool UNI, bool SUM>
-__device__ __forceinline__ Row<T> cell_row(uint32_t code, const T *tab, T bu, T fxm, T fxp, T &bzm,
-                                           T pc, T xm, T xp, T ym, T yp, T zm, T zp)
+template <typename T>
+struct Betas {
+    T xm, xp, ym, yp, zm, zp;
+    bool wx, wy, wz;   // p = 0 walls above the cell
+};
+
+template <typename T, bool SUM>
+__device__ __forceinline__ Row<T> row_of(const Betas<T> &b, T pc, T xm, T xp, T ym, T yp, T zm, T zp)
 {
-    T bxm, bxp, bym, byp, bzp;
-    if (UNI) {
-        bxm = bu * fxm;
-        bxp = bu * fxp;
-        bym = byp = bzp = bzm = bu;
-    } else {
-        const T *row = tab + (code & 15u) * kClasses;
-        bxm = row[(code >> 4) & 15u];
-        bxp = row[(code >> 8) & 15u];
-        bym = row[(code >> 12) & 15u];
-        byp = row[(code >> 16) & 15u];
-        bzp = row[(code >> 24) & 15u];
-    }
     const T dxm = pc - xm, dxp = pc - xp, dym = pc - ym, dyp = pc - yp, dzm = pc - zm, dzp = pc - zp;
-    const T txm = bxm * dxm, txp = bxp * dxp, tym = bym * dym, typ = byp * dyp, tzm = bzm * dzm,
-            tzp = bzp * dzp;
+    const T txm = b.xm * dxm, txp = b.xp * dxp, tym = b.ym * dym, typ = b.yp * dyp,
+            tzm = b.zm * dzm, tzp = b.zp * dzp;
     Row<T> r;
     r.q = ((txm + txp) + (tym + typ)) + (tzm + tzp);
-    r.dg = ((bxm + bxp) + (bym + byp)) + (bzm + bzp);
+    r.dg = ((b.xm + b.xp) + (b.ym + b.yp)) + (b.zm + b.zp);
     r.s = T(0);
     if (SUM) {
         // each face from its upper cell, and the p = 0 walls above a cell
         r.s = (txm * dxm + tym * dym) + tzm * dzm;
-        if (UNI) {
-            r.s += fxp == T(2) ? txp * dxp : T(0);
-        } else {
-            r.s += ((code >> 8) & 15u) == (uint32_t)kClsWallD ? txp * dxp : T(0);
-            r.s += ((code >> 16) & 15u) == (uint32_t)kClsWallD ? typ * dyp : T(0);
-            r.s += ((code >> 24) & 15u) == (uint32_t)kClsWallD ? tzp * dzp : T(0);
-        }
+        r.s += b.wx ? txp * dxp : T(0);
+        r.s += b.wy ? typ * dyp : T(0);
+        r.s += b.wz ? tzp * dzp : T(0);
     }
-    bzm = bzp;
     return r;
+}
+
+// From a cell's class nibbles (own, x-, x+, y-, y+, z-, z+), or one
+// coefficient for the whole wave where every cell of the column and its
+// neighbours are of one class (UNI; the x walls of a row then scale it by 0
+// or 2).  bzm: the low z coefficient, replaced by the high one.
+template <typename T, bool UNI, bool SUM>
+__device__ __forceinline__ Row<T> cell_row(uint32_t code, const T *tab, T bu, T fxm, T fxp, T &bzm,
+                                           T pc, T xm, T xp, T ym, T yp, T zm, T zp)
+{
+    Betas<T> b;
+    if (UNI) {
+        b = { bu * fxm, bu * fxp, bu, bu, bu, bu, fxp == T(2), false, false };
+    } else {
+        const T *row = tab + (code & 15u) * kClasses;
+        const uint32_t kx = (code >> 8) & 15u, ky = (code >> 16) & 15u, kz = (code >> 24) & 15u;
+        b = { row[(code >> 4) & 15u], row[kx], row[(code >> 12) & 15u], row[ky], bzm, row[kz],
+              kx == (uint32_t)kClsWallD, ky == (uint32_t)kClsWallD, kz == (uint32_t)kClsWallD };
+    }
+    bzm = b.zp;
+    return row_of<T, SUM>(b, pc, xm, xp, ym, yp, zm, zp);
 }
 
 }  // namespace
@@ -251,8 +272,11 @@ __device__ __forceinline__ Row<T> cell_row(uint32_t code, const T *tab, T bu, T 
 // T: double (FP64 solves) or float (inner solves of FP32 + refinement); NC
 // columns of NZ cells a thread; KEEP: q and the diagonal stay in registers
 // between the two halves of an iteration, else they are formed again (the
-// largest bricks).
-template <typename T, int NC, int NZ, bool KEEP>
+// largest bricks); FACES: the face coefficients are formed once, from the
+// densities and with the area fractions where a solve has them, and stay in
+// registers (five a cell; z faces are shared by a column's cells), instead of
+// being looked up by class.
+template <typename T, int NC, int NZ, bool KEEP, bool FACES>
 __global__ void __launch_bounds__(kResThreads)
 k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
 {
@@ -298,8 +322,11 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
     GLB u64 *area1 = gp(S.rsync), *area2 = area1 + 2 * (size_t)G;
 
     T z[NC][NZ], x[NC][NZ], pl[NC], ph[NC], q[KEEP ? NC : 1][KEEP ? NZ : 1],
-        dg[KEEP ? NC : 1][KEEP ? NZ : 1];
-    uint32_t code[NC][NZ];
+        dg[KEEP && !FACES ? NC : 1][KEEP && !FACES ? NZ : 1];
+    uint32_t code[FACES ? 1 : NC][FACES ? 1 : NZ];
+    constexpr int FC = FACES ? NC : 1, FZ = FACES ? NZ : 1;
+    T fxl[FC][FZ], fxh[FC][FZ], fyl[FC][FZ], fyh[FC][FZ], fz[FC][FZ + 1];
+    uint32_t wflag = 0;   // FACES, 2 bits a column: p = 0 walls above it in x, y
     int off[NC], gi[NC];  // LDS and grid cell of the column's first plane
     uint32_t cflag = 0;   // 4 bits a column: active, i == 0, i == nx - 1, on a y face
     uint32_t uni = 0;     // columns of one class throughout the wave
@@ -318,12 +345,60 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
         const int oyp = j < ny - 1 ? nx : (py ? -(ny - 1) * nx : 0);
         bool same = act && bz == NZ;
         uint32_t kc0 = 0;
+        if constexpr (FACES) {
+            // densities of solids are +inf: no flow through their faces; the
+            // wall stands for density 0 (p = 0 on its face) or for a solid
+            const GLB T *rho = gp((const T *)(F64 ? (const void *)S.rho64 : (const void *)S.rho32));
+            auto wall = [&](int w) { return (bm >> w) & 1 ? T(0) : (T)INFINITY; };
+            wflag |= ((act && i == nx - 1 && !px && (bm & 2) ? 1u : 0u) |
+                      (act && j == ny - 1 && !py && (bm & 8) ? 2u : 0u)) << (2 * c);
+            const int j1 = py && j == ny - 1 ? 0 : j + 1, i1 = px && i == nx - 1 ? 0 : i + 1;
+#pragma unroll
+            for (int k = 0; k < NZ; ++k) {
+                const bool in = act && k < bz;
+                const int m = in ? gi[c] + k * P : 0, kk = k0 + k;
+                T b[6] = { T(0), T(0), T(0), T(0), T(0), T(0) };
+                if (in) {
+                    const T rc = rho[m];
+                    b[0] = face_beta(rc + (oxm ? rho[m + oxm] : wall(0)));
+                    b[1] = face_beta(rc + (oxp ? rho[m + oxp] : wall(1)));
+                    b[2] = face_beta(rc + (oym ? rho[m + oym] : wall(2)));
+                    b[3] = face_beta(rc + (oyp ? rho[m + oyp] : wall(3)));
+                    b[4] = face_beta(rc + (kk > 0 ? rho[m - P] : wall(4)));
+                    b[5] = face_beta(rc + (kk < nz - 1 ? rho[m + P] : wall(5)));
+                    if (S.ax) {
+                        const GLB double *ax = gp(S.ax) + ((int64_t)kk * ny + j) * (nx + 1);
+                        const GLB double *ay = gp(S.ay) + (int64_t)kk * (ny + 1) * nx + i;
+                        const GLB double *az = gp(S.az) + m;
+                        b[0] *= (T)ax[i];
+                        b[1] *= (T)ax[i1];
+                        b[2] *= (T)ay[(int64_t)j * nx];
+                        b[3] *= (T)ay[(int64_t)j1 * nx];
+                        b[4] *= (T)az[0];
+                        b[5] *= (T)az[P];
+                    }
+                }
+                fxl[c][k] = b[0];
+                fxh[c][k] = b[1];
+                fyl[c][k] = b[2];
+                fyh[c][k] = b[3];
+                if (k == 0) fz[c][0] = b[4];
+                // (above the brick's last plane: that cell's high face stays)
+                fz[c][k + 1] = b[5];
+            }
+        }
 #pragma unroll
         for (int k = 0; k < NZ; ++k) {
             const bool in = act && k < bz;
             const int m = in ? gi[c] + k * P : 0;
-            uint32_t cd = 0x0fffffffu;
             z[c][k] = x[c][k] = T(0);
+            if (in) {
+                z[c][k] = zg[m];
+                x[c][k] = xg[m];
+                if (!first) Lp[off[c] + k * PS] = pg[m];
+            }
+            if constexpr (FACES) continue;
+            uint32_t cd = 0x0fffffffu;
             if (in) {
                 const int kk = k0 + k;
                 const uint32_t kc = gcls[m];
@@ -336,11 +411,8 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
                                         key(kk > 0, -P, 4),    key(kk < nz - 1, P, 5) };
                 if (kc != (uint32_t)kClsSolid)
                     cd = kc | w[0] << 4 | w[1] << 8 | w[2] << 12 | w[3] << 16 | w[4] << 20 | w[5] << 24;
-                z[c][k] = zg[m];
-                x[c][k] = xg[m];
-                if (!first) Lp[off[c] + k * PS] = pg[m];
             }
-            code[c][k] = cd;
+            code[FACES ? 0 : c][FACES ? 0 : k] = cd;
             // one class throughout, the x walls of the row aside
             if (k == 0) kc0 = __builtin_amdgcn_readfirstlane(cd) & 15u;
             uint32_t want = kc0 * 0x1111111u, have = cd;
@@ -348,7 +420,7 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
             if (i == nx - 1 && !px) { want &= ~0xf00u; have &= ~0xf00u; }
             same = same && kc0 < (uint32_t)kMaxFluidClasses && have == want;
         }
-        if (__all(same)) uni |= 1u << c;
+        if (!FACES && __all(same)) uni |= 1u << c;
         // p of the planes below and above the brick
         pl[c] = ph[c] = T(0);
         if (act && !first && zlo) pl[c] = pg[gi[c] - P];
@@ -463,15 +535,44 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
                 pc = zp;
             }
         };
+        // the same with the coefficients of FACES
+        auto column_faces = [&](auto SUM, int c, auto &&each) __attribute__((always_inline)) {
+            constexpr bool kS = decltype(SUM)::value;
+            keep_here(off[c]);
+            keep_here(wflag);
+            const T *a = Lp + off[c];
+            const uint32_t f = wflag >> (2 * c);
+            T zm = pl[c], pc = a[0];
+#pragma unroll
+            for (int k = 0; k < NZ; ++k) {
+                const T *b = a + k * PS;
+                const T zp = k + 1 < NZ ? b[PS] : ph[c];
+                keep_here(fxl[c][k]);
+                keep_here(fyl[c][k]);
+                keep_here(fz[c][k]);
+                // planes past the grid's last one hold no cells
+                const T bzm = k < bz ? fz[c][k] : T(0);
+                const Betas<T> bt = { fxl[c][k], fxh[c][k], fyl[c][k], fyh[c][k], bzm, fz[c][k + 1],
+                                      (f & 1u) != 0, (f & 2u) != 0,
+                                      k0 + k == nz - 1 && (bm & 32) };
+                each(c, k, row_of<T, kS>(bt, pc, b[-1], b[1], b[-RS], b[RS], zm, zp), pc);
+                zm = pc;
+                pc = zp;
+            }
+        };
         using Yes = std::integral_constant<bool, true>;
         using No = std::integral_constant<bool, false>;
         auto first_half = [&](int c, int k, const Row<T> &r, T) __attribute__((always_inline)) {
             sum += (double)r.s;
-            if constexpr (KEEP) { q[c][k] = r.q; dg[c][k] = r.dg; }
+            if constexpr (KEEP) q[c][k] = r.q;
+            // (formed here: not its products kept for later)
+            if constexpr (KEEP && FACES) keep_here(q[c][k]);
+            if constexpr (KEEP && !FACES) dg[c][k] = r.dg;
         };
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            if ((uni >> c) & 1u) column(Yes{}, Yes{}, c, first_half);
+            if constexpr (FACES) column_faces(Yes{}, c, first_half);
+            else if ((uni >> c) & 1u) column(Yes{}, Yes{}, c, first_half);
             else column(No{}, Yes{}, c, first_half);
         }
         double v1[1] = { sum };
@@ -505,10 +606,22 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
             keep_here(gi[c]);
             if constexpr (KEEP) {
 #pragma unroll
-                for (int k = 0; k < NZ; ++k)
-                    second_half(c, k, Row<T>{ q[c][k], dg[c][k], T(0) }, Lp[off[c] + k * PS]);
+                for (int k = 0; k < NZ; ++k) {
+                    T d;
+                    if constexpr (FACES) {
+                        keep_here(fxl[c][k]);
+                        keep_here(fyl[c][k]);
+                        keep_here(fz[c][k]);
+                        d = ((fxl[c][k] + fxh[c][k]) + (fyl[c][k] + fyh[c][k])) +
+                            ((k < bz ? fz[c][k] : T(0)) + fz[c][k + 1]);
+                    } else {
+                        d = dg[c][k];
+                    }
+                    second_half(c, k, Row<T>{ q[c][k], d, T(0) }, Lp[off[c] + k * PS]);
+                }
             } else {
-                if ((uni >> c) & 1u) column(Yes{}, No{}, c, second_half);
+                if constexpr (FACES) column_faces(No{}, c, second_half);
+                else if ((uni >> c) & 1u) column(Yes{}, No{}, c, second_half);
                 else column(No{}, No{}, c, second_half);
             }
         }
@@ -571,7 +684,12 @@ struct Entry {
 template <typename T, int NC, int NZ, bool KEEP>
 Entry entry(int batch = 0)
 {
-    return { { NC, NZ, KEEP, batch }, (const void *)k_resident<T, NC, NZ, KEEP> };
+    return { { NC, NZ, KEEP, false, batch }, (const void *)k_resident<T, NC, NZ, KEEP, false> };
+}
+template <typename T, int NC, int NZ, bool KEEP>
+Entry faces()
+{
+    return { { NC, NZ, KEEP, true, 0 }, (const void *)k_resident<T, NC, NZ, KEEP, true> };
 }
 // Shapes.  FP64 keeps q and the diagonal in registers up to 16 cells a thread,
 // FP32 up to 32 (256 registers a thread with two waves a SIMD); batches take
@@ -584,6 +702,10 @@ const Entry kF64[] = {
     entry<double, 3, 4, true>(),  entry<double, 2, 8, true>(1), entry<double, 4, 4, true>(),
     entry<double, 4, 6, false>(), entry<double, 3, 8, false>(), entry<double, 5, 6, false>(),
     entry<double, 4, 8, false>(1),
+    faces<double, 1, 1, true>(),  faces<double, 1, 2, true>(),  faces<double, 1, 4, true>(),
+    faces<double, 2, 2, true>(),  faces<double, 1, 6, true>(),  faces<double, 2, 4, true>(),
+    faces<double, 1, 8, true>(),  faces<double, 2, 5, true>(),  faces<double, 3, 4, false>(),
+    faces<double, 2, 6, false>(),
 };
 const Entry kF32[] = {
     entry<float, 1, 1, true>(),  entry<float, 1, 2, true>(),  entry<float, 1, 3, true>(),
@@ -592,6 +714,10 @@ const Entry kF32[] = {
     entry<float, 3, 4, true>(),  entry<float, 4, 4, true>(),  entry<float, 2, 8, true>(),
     entry<float, 3, 8, true>(),  entry<float, 4, 6, true>(),  entry<float, 5, 6, true>(),
     entry<float, 4, 8, true>(1), entry<float, 6, 8, false>(1),
+    faces<float, 1, 1, true>(),  faces<float, 1, 2, true>(),  faces<float, 1, 4, true>(),
+    faces<float, 2, 2, true>(),  faces<float, 2, 4, true>(),  faces<float, 1, 8, true>(),
+    faces<float, 3, 4, true>(),  faces<float, 2, 8, true>(),  faces<float, 4, 4, true>(),
+    faces<float, 3, 6, true>(),  faces<float, 5, 4, true>(),  faces<float, 4, 6, false>(),
 };
 }  // namespace
 
