@@ -203,6 +203,8 @@ typedef struct pcg_batch pcg_batch_t; /* opaque, owned by the library */
 
 /*
  * Bytes of device workspace pcg_setup needs for this grid and options.
+ * (48 KiB more, where given, hold the partial sums of shorter tiles, which
+ * some grids run faster with; the result then differs in its rounding.)
  * Returns PCG_EINVAL on bad arguments, PCG_EUNSUPPORTED when
  * nx*ny*nz >= 2^31.
  */

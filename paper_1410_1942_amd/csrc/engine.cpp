@@ -339,22 +339,46 @@ Geometry make_geometry(const pcg_grid_t &g, int prec, int tz_opt, bool batch, in
     return G;
 }
 
-// Planes a tile of a solve with cut-cell fractions: at most one tile a CU.
-// Its two passes read five arrays beside the vectors, and two workgroups a CU
-// run them slower than one after the other: per iteration 192 x 160 x 144
-// FP64 480 tiles (18 planes) 149 us on 512 workgroups, 120 on 256, and 240
-// tiles (36) 113; 128^3 352 tiles 102, 256 79, 192 81; 160 x 140 x 160 440
-// tiles 137, 220 109; 192 x 160 x 144 FP32 360 tiles 126, 240 96, 180 100.
-// Tiles of one height, too: 192 x 160 x 144 FP64 in chunks of 64, 64 and 16
-// planes 150, of 48 124 (its four chunks of 36 would need more partial sums
-// than the plain form's tiles, which the workspace is sized for).
-constexpr int kFracTiles = 256;
+// Tile height of a single solve.  The table's heights were tuned on cubes and
+// boxes of powers of two, whose tiles fill the device evenly; other grids left
+// it mostly idle in the last round of tiles (two workgroups a CU, kRoundTiles
+// at once).  The cost of a cut into c chunks of planes is that of its rounds:
+// a round of t tiles takes (tz + 6) plane steps (start, end and wait of the
+// launch are worth about six) of 1 + t / d, d = 850, or 1600 for the tiles
+// whose step is bound by its chain of waits rather than by what it moves (one
+// cell a thread, four FP32 cells).  Fitted to FP64 250 x 200 x 180 per
+// iteration, chunks: 2 163 us, 3 135, 4 111, 5 (500 tiles) 98, 6 141, 8 132,
+// 10 123, and to the like of FP32 400 x 250 x 250.  The cheapest cut is taken
+// where it is below 95 % of the table's; measured, table against it: FP64 250
+// x 200 x 180 145 -> 98 us, 380 x 300 x 200 302 -> 240, 512 x 330 x 300 513
+// -> 473, 320 x 256 x 128 157 -> 141, 255 x 161 x 199 (one cell a thread) 192
+// -> 116, 333 x 201 x 301 379 -> 316, consecutive cells 150 x 180 x 200 116
+// -> 82, 330 x 220 x 300 304 -> 250, with fractions 192 x 160 x 144 112 -> 90.
+// Below 2^20 cells the table stands: consecutive cells 64^3 22.5 against its
+// 21.9, 33^3 FP32 18.4 against 17.0, 140 x 100 x 60 FP32 28.1 against 26.0.
+// limit: tiles whose partial sums the slot has room for.
+constexpr int kRoundTiles = 512;
+constexpr int64_t kBalanceCells = 1 << 20;
+constexpr int64_t kTileRoom = 2048;   // tiles with room in spare workspace
 
-int frac_tz(const Geometry &G)
+int balanced_tz(const Geometry &G, int prec, int64_t limit)
 {
-    const int64_t chunks = std::min<int64_t>(kFracTiles, G.ntiles) / G.plane_tiles;
-    if (chunks < 1) return G.tz;
-    return (int)((G.nz + chunks - 1) / chunks);
+    if (G.n < kBalanceCells) return G.tz;
+    const bool light = G.tx > 0 && (G.cpt == 1 || prec == PCG_PREC_FP32_IR);
+    const double d = light ? 1600.0 : 850.0;
+    auto cost = [&](int tz) {
+        const int64_t t = (int64_t)G.plane_tiles * ((G.nz + tz - 1) / tz);
+        const int64_t full = t / kRoundTiles, rest = t % kRoundTiles;
+        return (tz + 6) * (full * (1.0 + kRoundTiles / d) + (rest ? 1.0 + rest / d : 0.0));
+    };
+    const int64_t tz_cap = kMaxTileBytes / ((int64_t)G.nx * G.ny * 8) - 2;
+    int best = G.tz;
+    double least = 0.95 * cost(G.tz);
+    for (int64_t c = 1; c <= G.nz && c * G.plane_tiles <= limit; ++c) {
+        const int tz = (int)((G.nz + c - 1) / c);
+        if (tz <= tz_cap && cost(tz) < least) { best = tz; least = cost(tz); }
+    }
+    return best;
 }
 
 // Bytes of the four fraction arrays of a grid (FP64 MAC faces and cells).
@@ -661,8 +685,9 @@ struct SlotHost {
     bool running = false;   // in the slot table
     bool finished = false;  // completion observed on the host
     Geometry geo{};
-    int plain_tz = 0;        // planes a tile without fractions, and its tile count
-    int64_t plain_tiles = 0; // (partial sums are reserved for these)
+    bool balanced = false;   // another tile height than the table's
+    int64_t tile_room = 0;   // tiles that the partial sums have room for
+    size_t spare = 0;        // arena offset of theirs beyond the slot's own (0: none)
     int bcmask = 0;
     int permask = 0;
     bool singular = false;   // no Dirichlet wall reaches the fluid
@@ -885,24 +910,6 @@ struct Engine {
         d.vol = S.has_frac ? S.vol : nullptr;
     }
 
-    // Tile height of a slot, which depends on whether it has fractions (single
-    // solves; a caller's own height stands).
-    void set_tile_height(SlotHost &S)
-    {
-        Geometry &G = S.geo;
-        auto cut = [&](int tz) {
-            G.tz = tz;
-            G.ztiles = (G.nz + tz - 1) / tz;
-            G.ntiles = (int64_t)G.plane_tiles * G.ztiles;
-        };
-        cut(S.plain_tz);
-        if (S.has_frac && !batch_mode() && tz_opt == 0) {
-            const int64_t cap = kMaxTileBytes / ((int64_t)G.nx * G.ny * 8) - 2;
-            const int tz = frac_tz(G);
-            if (tz <= cap) cut(tz);
-        }
-    }
-
     // Cut-cell fractions for a prepared slot that is not running: copy the
     // caller's arrays into the slot's reserved space and validate them on the
     // device (areas in [0, 1], fluid volumes in (0, 1]); all NULL clears.
@@ -917,7 +924,6 @@ struct Engine {
         if (view_id == id) view_id = -1;
         table_dirty = true;
         S.has_frac = false;
-        set_tile_height(S);
         if (!given) return PCG_OK;
         if (!S.ax) return PCG_EINVAL;   // no room reserved (PCG_FRACTIONS not set)
         const size_t nx = S.geo.nx, ny = S.geo.ny, nz = S.geo.nz;
@@ -937,7 +943,6 @@ struct Engine {
         if (e != hipSuccess) return hip_fail(e, "fractions");
         if (*h_bad) return PCG_EDOMAIN;
         S.has_frac = true;
-        set_tile_height(S);
         return PCG_OK;
     }
 
@@ -1003,8 +1008,6 @@ struct Engine {
         SlotHost &S = slots[id];
         S = SlotHost{};
         S.geo = geo;
-        S.plain_tz = geo.tz;
-        S.plain_tiles = geo.ntiles;
         S.bcmask = bm;
         S.permask = per;
         S.h2 = grid_->h * grid_->h;
@@ -1022,7 +1025,22 @@ struct Engine {
         S.dir2 = p; p += align_up(es * n, kAlign);
         if (prec == PCG_PREC_FP32_IR) { S.d32 = (float *)p; p += align_up(4 * n, kAlign); }
         S.partials = (double *)p;
+        S.tile_room = geo.ntiles;
         p += align_up(kMaxPartials * 8 * (size_t)geo.ntiles, kAlign);
+        // a single solve takes the better height (the caller's own launch
+        // shape stands), with more tiles where the workspace has spare bytes
+        if (!batch_mode() && tz_opt == 0 && grid_opt == 0) {
+            size_t spare = 0;
+            if (geo.ntiles < kTileRoom && alloc.alloc(kMaxPartials * 8 * kTileRoom, &spare)) {
+                S.spare = spare;
+                S.partials = (double *)(arena + spare);
+                S.tile_room = kTileRoom;
+            }
+            S.geo.tz = balanced_tz(geo, prec, S.tile_room);
+            S.geo.ztiles = (geo.nz + S.geo.tz - 1) / S.geo.tz;
+            S.geo.ntiles = (int64_t)geo.plane_tiles * S.geo.ztiles;
+            S.balanced = S.geo.tz != geo.tz;
+        }
         S.cls = (uint8_t *)p;
         p += align_up(n, kAlign);
         S.tab64 = (double *)p;
@@ -1044,7 +1062,12 @@ struct Engine {
         }
 
         st = encode_slot(S, rho, mask, flags);
-        if (st) { alloc.release(off, need); S = SlotHost{}; return st; }
+        if (st) {
+            alloc.release(off, need);
+            if (S.spare) alloc.release(S.spare, kMaxPartials * 8 * kTileRoom);
+            S = SlotHost{};
+            return st;
+        }
         S.used = true;
         *slot_out = id;
         return PCG_OK;
@@ -1164,6 +1187,7 @@ struct Engine {
         SlotHost &S = slots[id];
         if (!S.used) return;
         alloc.release(S.off, S.bytes);
+        if (S.spare) alloc.release(S.spare, kMaxPartials * 8 * kTileRoom);
         if (S.running) table_dirty = true;
         if (view_id == id) view_id = -1;
         S = SlotHost{};
@@ -1268,14 +1292,17 @@ struct Engine {
         if (max_slots == 1) {
             int64_t t = 0, n = 0;
             int group = 0;
+            bool balanced = false;
             for (auto &S : slots)
                 if (S.used) {
+                    balanced = S.balanced;
                     t = std::max<int64_t>(t, S.geo.ntiles);
                     n = S.geo.n;
                     group = S.geo.tx > 0 ? S.geo.cpt : 0;
                 }
             if (grid_opt <= 0 && n > 0 && rule_for(n, prec, false, group).grid > 0)
                 g = rule_for(n, prec, false, group).grid;
+            if (balanced) g = std::max(g, kRoundTiles);
             if (t > 0 && t < g) g = (int)t;
         }
         g = std::max(8, (g + 7) / 8 * 8);
@@ -1853,7 +1880,7 @@ int pcg_divergence(pcg_ctx_t *c, const double *u, const double *v, const double 
     if (st) return st;
     const SlotHost &S = c->eng.slots[c->slot];
     // one partial pair per workgroup, in the slot's partial-sum buffer
-    const int64_t room = kMaxPartials * S.plain_tiles / 2;
+    const int64_t room = kMaxPartials * S.tile_room / 2;
     const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>({ project_blocks(S), 4096, room }));
     HIP_TRY(launch_divnorm(ds, 1.0 / std::sqrt(S.h2), u, v, w, S.partials, (int)blocks,
                            c->eng.stream));

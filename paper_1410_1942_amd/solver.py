@@ -61,6 +61,9 @@ def _check(t: Optional[torch.Tensor], shape, dtype, name: str, device=None,
         raise ValueError(f"{name}: must be on {device}, got {t.device}")
 
 
+_SPARE_BYTES = 48 << 10   # 2048 tiles of three doubles
+
+
 def _field_shape(rho: torch.Tensor):
     if not isinstance(rho, torch.Tensor) or rho.dim() != 3:
         raise ValueError("rho: a 3-D [nz, ny, nx] tensor")
@@ -117,6 +120,9 @@ class Solver:
         L.check(lib.pcg_workspace_bytes(ctypes.byref(self.grid),
                                         ctypes.byref(self.opts),
                                         ctypes.byref(nbytes)), "workspace")
+        # spare bytes hold the partial sums of more tiles than the least
+        # workspace has room for
+        nbytes.value += _SPARE_BYTES
         self.workspace = torch.empty(int(nbytes.value), dtype=torch.uint8,
                                      device=rho.device)
         self._stream = _stream_handle(stream)
