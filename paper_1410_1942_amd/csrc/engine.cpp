@@ -119,6 +119,9 @@ struct TileRule {
 };
 
 // Built-in table: the autotuner's choice on gfx950 (package tile_table.json).
+// (Tuned, like the comparisons of tile forms below, when every tile ended with
+// a fence that cost a launch 35 us; on the grids tried again without it, 64^3
+// to 256^3 and 512 x 128 x 128, they stand.)
 std::vector<TileRule> g_rules[2] = {  // single solves: FP64, FP32+IR
     { { 7524, 2, 256 }, { 21283, 2, 256 }, { 60198, 4, 1024 }, { 170267, 4, 768 }, { 481589, 8, 1024 }, { 1362140, 16, 2048 }, { 3852714, 16, 768 }, { 10897121, 64, 512 }, { 30821713, 128, 768 }, { 87176971, 32, 512 }, { INT64_MAX, 256, 512 } },
     { { 7524, 2, 256 }, { 21283, 2, 1024 }, { 60198, 2, 2048 }, { 170267, 4, 768 }, { 481589, 4, 1024 }, { 1362140, 8, 256 }, { 3852714, 16, 256 }, { 10897121, 32, 768 }, { 30821713, 32, 768 }, { 87176971, 16, 512 }, { INT64_MAX, 256, 1024 } },

@@ -327,8 +327,9 @@ struct ClsCoef {
 // wait for it, plane after plane: fractions come in groups, pass A's a plane
 // ahead, and the high faces only where a Dirichlet wall needs them.  192 x 160
 // x 144 FP64 per iteration: six loads a cell and density keys 177 us, groups
-// 163, class keys 151 (all with 64 planes a tile; 124 at 48).  A plane ahead
-// in pass B too: 122 against 113 (36 planes), its registers cost more.
+// 163, class keys 151 (64 planes a tile; 90 with even tiles of 18 and without
+// the fences at a tile's end, 5.3 TB/s).  A plane ahead in pass B too: 122
+// against 113 (36 planes), its registers cost more.
 template <typename T, class KC>
 struct FracCoef : KC {
     static constexpr bool kWallBranch = true;   // saves the loads
@@ -1823,9 +1824,9 @@ __device__ void lds_sweep_cg(const Slot &S, const SlotState &st, int64_t lt, con
     // coefficients the operator row formed there, and the Dirichlet high walls
     // (only waves that hold such a cell form those); the x-/y- neighbours' z'
     // from LDS.  Against forming each face's coefficient a second time here,
-    // per iteration: 512^3 FP32 793 -> 778 us, FP64 1292 -> 1289, 256^3 FP32
-    // 124.0 -> 121.7, densities without classes (320 x 192 x 160 FP64) 206.2
-    // -> 203.1.
+    // per iteration: 512^3 FP32 793 -> 778 us (743 without the fences at a
+    // tile's end), FP64 1292 -> 1289 (1200), 256^3 FP32 124.0 -> 121.7 (95.5),
+    // densities without classes (320 x 192 x 160 FP64) 206.2 -> 203.1 (152).
     const bool wwave = __any(hwx || hwy);
     auto delta = [&](const T *Lz, const T (&zc)[N], const T (&zd)[N], const T (&bx)[N],
                      const T (&by)[N], const T (&bd)[N], const K (&kd)[N],

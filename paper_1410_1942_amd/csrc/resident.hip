@@ -17,20 +17,17 @@
 // (a store that reaches memory, a load that sees it), and for bricks of many
 // cells their LDS reads and arithmetic (40 B and about 60 vector instructions
 // a cell).  A launch per iteration instead waits for memory plane after plane
-// and streams 41 B a cell.  Measured per iteration of a whole solve, launches
-// against this: FP64 32^3 16.4 -> 5.9 us, 64^3 21.7 -> 7.4, 101 x 77 x 59 32.6
-// -> 8.4, 128^3 44.7 -> 15.0, 150 x 141 x 133 98 -> 22, 320 x 128 x 96 90 -> 35;
-// FP32 32^3 16.4 -> 6.1, 64^3 21.7 -> 7.5, 128^3 48.6 -> 12.5, 320 x 128 x 96
-// 65.6 -> 20.1.
+// and streams 41 B a cell.  Measured per iteration of whole solves, launches
+// against this: FP64 33^3 14.6 -> 5.9 us, 64^3 18.7 -> 7.4, 128^3 32 -> 15,
+// 320 x 128 x 96 52 -> 32; FP32 33^3 14.5 -> 6.1, 64^3 18.0 -> 7.5, 128^3 33
+// -> 12.5, 150 x 141 x 250 64 -> 33.
 //
 // Densities without classes and cut cells hold the face coefficients in
 // registers beside z and x (FACES), 16 words a cell FP64, which bounds them
-// to ten or twelve cells a thread.  Per iteration, launches against this:
-// densities FP64 32^3 17.6 -> 5.9 us, 64^3 24.2 -> 7.8, 96^3 44.2 -> 11.3,
-// 110 x 128 x 90 (twelve cells) 58.5 -> 17.8; FP32 32^3 16.2 -> 8.4 (100
-// iterations with their refinements), 128^3 59.0 -> 17.2, 150 x 141 x 133
-// 90 -> 25; cut cells FP64 64^3 32.8 -> 8.2, 96^3 59.6 -> 11.9; FP32 128^3
-// 88 -> 18.
+// to ten or twelve cells a thread.  Launches against this: densities FP64 110
+// x 128 x 90 (twelve cells) 30.7 -> 16.1 us, 109 x 119 x 101 35 -> 17; FP32
+// 125 x 125 x 150 42 -> 15, 150 x 141 x 133 46 -> 22; smaller ones 64^3 7.8,
+// 96^3 11.3 (FP64), cut cells 64^3 8.2, 96^3 11.9.
 //
 // Exchange: a workgroup's sums go out as words of half a double beside a
 // 32-bit tag, the number of the exchange, written and read with relaxed
