@@ -98,15 +98,6 @@ __device__ __forceinline__ double wave_sum63(double v)
     return v;
 }
 
-__device__ __forceinline__ double lane63(double v)
-{
-    typedef int i2 __attribute__((ext_vector_type(2)));
-    i2 h = __builtin_bit_cast(i2, v);
-    h.x = __builtin_amdgcn_readlane(h.x, 63);
-    h.y = __builtin_amdgcn_readlane(h.y, 63);
-    return __builtin_bit_cast(double, h);
-}
-
 __device__ __forceinline__ double recip(double d)
 {
     double y = __builtin_amdgcn_rcp(d);
