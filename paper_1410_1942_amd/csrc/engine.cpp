@@ -1455,10 +1455,26 @@ struct Engine {
     // The same for a context's one solve, a stage a step: the actions before
     // its iterations, up to kResBudget iterations (FP32 + refinement: an inner
     // solve), the actions after them.  The host waits after the last of these
-    // only (and with refinement not before the trips its tolerance needs at
-    // least): a wait and a start cost about 40 us, six iterations of a small
-    // grid.  *wait: whether this step ends with a look at the state.
+    // only (and with refinement not before the trips of queued_trips): a wait
+    // and a start cost about 40 us, six iterations of a small grid.  *wait:
+    // whether this step ends with a look at the state.
     static constexpr int kResBudget = 4096;
+    // Refinement trips queued before the first look: those that the tolerance
+    // needs at least from a zero start, up to kMaxQueuedTrips (1e-14 at the
+    // default 1e-4 a trip takes that many; a trip reduces by less than asked
+    // for where inner_tol is near 1, and the device ends a solve long before
+    // the trips that a tolerance out of reach would name).  One where the
+    // solve may end in its first: a warm start, or a cap of few iterations (a
+    // trip of nothing costs about 40 us too, five iterations).
+    static constexpr int kMaxQueuedTrips = 4;
+    static constexpr int kShortSolve = 256;
+    static int queued_trips(const SlotState &h, bool ir)
+    {
+        if (!ir || h.warm || h.maxit <= kShortSolve) return 1;
+        const double trips = std::ceil(std::log(h.tol) / (0.5 * std::log(h.inner_tol2)));
+        if (!(trips > 1.0)) return 1;
+        return trips < kMaxQueuedTrips ? (int)trips : kMaxQueuedTrips;
+    }
     int resident_stage(bool *wait)
     {
         const bool ir = prec == PCG_PREC_FP32_IR;
@@ -1475,8 +1491,7 @@ struct Engine {
                                     stream));
         } else {
             HIP_TRY(launch_actions((ir ? 2 - !k2only : 1) + (S->singular ? 2 - !k2only : 0)));
-            const double trips = ir ? std::log(h.tol) / (0.5 * std::log(h.inner_tol2)) : 0.0;
-            *wait = S->rwaits > 0 || ++S->rtrips >= trips;
+            *wait = S->rwaits > 0 || ++S->rtrips >= queued_trips(h, ir);
         }
         S->rstage = (S->rstage + 1) % 3;
         if (*wait) {
