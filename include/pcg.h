@@ -501,6 +501,18 @@ int pcg_get_tile_rules(int32_t precision, int32_t table, int32_t cap,
  */
 int pcg_inject_failure(pcg_ctx_t *ctx, int32_t after_steps);
 
+/*
+ * Test hook for solves that iterate on the chip (several workgroups at once,
+ * which exchange their sums): at most `iterations` a launch (0 = the default,
+ * 4096; the answer does not depend on it) and `polls` looks at another
+ * workgroup's sums before an exchange counts as timed out (negative = the
+ * default, a few seconds; 0 = every exchange between workgroups times out).
+ * A solve whose exchange times out, because other work keeps part of the
+ * device, starts again on the tile passes, and the context or batch stays
+ * with them.  PCG_EINVAL for a null context or iterations < 0.
+ */
+int pcg_set_resident_limits(pcg_ctx_t *ctx, int32_t iterations, int32_t polls);
+
 /* ---- allocation-free solve ---------------------------------------------- */
 
 /*

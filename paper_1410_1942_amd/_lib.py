@@ -30,7 +30,7 @@ EXPORTED = [
     "pcg_density_classes", "pcg_project", "pcg_divergence",
     "pcg_solve_ex", "pcg_project_ex", "pcg_rhs", "pcg_update_density",
     "pcg_set_fractions", "pcg_triad_probe", "pcg_inject_failure",
-    "pcg_solve_static", "pcg_tile_form",
+    "pcg_solve_static", "pcg_tile_form", "pcg_set_resident_limits",
 ]
 
 
@@ -117,6 +117,7 @@ def load(path: str = LIB_PATH):
     lib.pcg_update_density.argtypes = [vp, vp, vp, i32]
     lib.pcg_set_fractions.argtypes = [vp, vp, vp, vp, vp]
     lib.pcg_inject_failure.argtypes = [vp, i32]
+    lib.pcg_set_resident_limits.argtypes = [vp, i32, i32]
     lib.pcg_solve_static.argtypes = [P(Grid), vp, vp, P(BC), P(Opts), vp, vp, dbl, i32,
                                      P(Stats), vp]
     for name in EXPORTED:

@@ -51,7 +51,7 @@ __attribute__((weak)) int resident_shapes(int family, ResidentShape *out, int ca
 __attribute__((weak)) hipError_t resident_occupancy(int family, int shape, unsigned lds, int *wgs);
 __attribute__((weak)) hipError_t launch_resident(int family, int shape, int blocks, unsigned lds,
                                                  const Slot *slots, int s0, int s1, int budget,
-                                                 hipStream_t s);
+                                                 int polls, hipStream_t s);
 }  // namespace pcgmi
 
 using namespace pcgmi;
@@ -795,6 +795,12 @@ struct Engine {
         unsigned lds;
     };
     std::vector<ResidentLaunch> rlaunch;
+    // iterations a launch of a single solve takes at most, and looks at
+    // another workgroup's sums before an exchange counts as timed out (some
+    // seconds: only workgroups that the device has no room for reach it)
+    static constexpr int kResBudget = 4096, kResPolls = 1 << 21;
+    int res_budget = kResBudget, res_polls = kResPolls;
+    bool no_resident = false;   // an exchange timed out or a launch was refused
     bool looked = false;    // the last step refreshed the host's states
     int fail_after = 0;     // test hook: the step call that reports a failure
     HostMirror *mirror = nullptr;  // caller-owned host mirrors: no pinned memory,
@@ -1173,7 +1179,7 @@ struct Engine {
         h.warm = (flags & PCG_WARM_START) ? 1 : 0;
         // grids with a resident form, unless each launch is timed
         S.res = S.has_frac || !S.classes ? S.by_face : S.by_class;
-        S.resident = S.res.shape >= 0 && !timing && S.has_frac == frac_space;
+        S.resident = S.res.shape >= 0 && !timing && !no_resident && S.has_frac == frac_space;
         S.rstage = S.rtrips = S.rwaits = 0;
         h.resident = S.resident ? 1 : 0;
         h.fused = S.z2 && !S.resident ? 1 : 0;
@@ -1434,9 +1440,39 @@ struct Engine {
         }
     }
 
+    // A solve whose resident launch could not run beside its own workgroups
+    // (or not at all) starts again on the tile passes, from zero or, warm,
+    // from what is in x: a launch that timed out has left the guess or a
+    // later iterate there, in part one and in part the other at worst.  So do
+    // this engine's later solves: other work holds the device.
+    int leave_resident(int id)
+    {
+        SlotHost &S = slots[id];
+        const SlotState h = h_states[id];
+        const Clock::time_point t0 = S.t0;
+        no_resident = true;
+        S.running = false;
+        const int st = start(id, S.rhs, S.x, h.tol, h.maxit, h.warm ? PCG_WARM_START : 0);
+        S.t0 = t0;
+        return st;
+    }
+
+    // The same for every resident solve, after a launch that was refused.
+    int leave_resident_all()
+    {
+        (void)hipGetLastError();
+        for (int id = 0; id < max_slots; ++id)
+            if (slots[id].used && slots[id].running && slots[id].resident) {
+                const int st = leave_resident(id);
+                if (st) return st;
+            }
+        return PCG_OK;
+    }
+
     // One polling step of the resident solves: the actions they are waiting
-    // for, and check_every iterations.
-    int resident_step(bool others)
+    // for, and check_every iterations.  *left: a launch was refused, and they
+    // have left the resident kernel.
+    int resident_step(bool others, bool *left)
     {
         const bool ir = prec == PCG_PREC_FP32_IR;
         int pre = 0;
@@ -1447,18 +1483,20 @@ struct Engine {
         }
         if (!others) HIP_TRY(launch_actions(pre));   // else the others' launches took them
         for (const ResidentLaunch &q : rlaunch)
-            HIP_TRY(launch_resident(prec, q.shape, q.blocks, q.lds, d_slots, q.s0, q.s1,
-                                    check_every, stream));
+            if (launch_resident(prec, q.shape, q.blocks, q.lds, d_slots, q.s0, q.s1, check_every,
+                                res_polls, stream) != hipSuccess) {
+                *left = true;
+                return leave_resident_all();
+            }
         return PCG_OK;
     }
 
     // The same for a context's one solve, a stage a step: the actions before
-    // its iterations, up to kResBudget iterations (FP32 + refinement: an inner
+    // its iterations, up to res_budget iterations (FP32 + refinement: an inner
     // solve), the actions after them.  The host waits after the last of these
     // only (and with refinement not before the trips of queued_trips): a wait
     // and a start cost about 40 us, six iterations of a small grid.  *wait:
     // whether this step ends with a look at the state.
-    static constexpr int kResBudget = 4096;
     // Refinement trips queued before the first look: those that the tolerance
     // needs at least from a zero start, up to kMaxQueuedTrips (1e-14 at the
     // default 1e-4 a trip takes that many; a trip reduces by less than asked
@@ -1487,8 +1525,9 @@ struct Engine {
             if (S->rtrips == 0) HIP_TRY(launch_actions(actions_before(h.phase, ir, S->singular, !k2only)));
         } else if (S->rstage == 1) {
             const ResidentLaunch &q = rlaunch[0];
-            HIP_TRY(launch_resident(prec, q.shape, q.blocks, q.lds, d_slots, q.s0, q.s1, kResBudget,
-                                    stream));
+            if (launch_resident(prec, q.shape, q.blocks, q.lds, d_slots, q.s0, q.s1, res_budget,
+                                res_polls, stream) != hipSuccess)
+                return leave_resident_all();
         } else {
             HIP_TRY(launch_actions((ir ? 2 - !k2only : 1) + (S->singular ? 2 - !k2only : 0)));
             *wait = S->rwaits > 0 || ++S->rtrips >= queued_trips(h, ir);
@@ -1534,8 +1573,9 @@ struct Engine {
                 st = resident_stage(&wait);
                 if (st || !wait) return st;
             } else if (nresident) {
-                st = resident_step(others);
-                if (st) return st;
+                bool left = false;
+                st = resident_step(others, &left);
+                if (st || left) return st;
             }
         }
         HIP_TRY(hipMemcpyAsync(h_states, d_states, sizeof(SlotState) * max_slots,
@@ -1546,8 +1586,9 @@ struct Engine {
             SlotHost &S = slots[id];
             if (!S.used || !S.running) continue;
             if (h_states[id].rfail) {
-                g_hip_err = "resident kernel: an exchange between workgroups timed out";
-                return PCG_EHIP;
+                st = leave_resident(id);
+                if (st) return st;
+                continue;
             }
             if (h_states[id].phase == PH_DONE) {
                 S.running = false;
@@ -1965,6 +2006,14 @@ int pcg_inject_failure(pcg_ctx_t *c, int32_t after_steps)
 {
     if (!c || after_steps < 0) return PCG_EINVAL;
     c->eng.fail_after = after_steps;
+    return PCG_OK;
+}
+
+int pcg_set_resident_limits(pcg_ctx_t *c, int32_t iterations, int32_t polls)
+{
+    if (!c || iterations < 0) return PCG_EINVAL;
+    c->eng.res_budget = iterations > 0 ? iterations : Engine::kResBudget;
+    c->eng.res_polls = polls >= 0 ? polls : Engine::kResPolls;
     return PCG_OK;
 }
 

@@ -38,6 +38,12 @@
 // faces.  All workgroups add the sums in the same order and so take the same
 // decisions.  A word is rewritten only after an exchange that its readers
 // have all passed.
+//
+// Polling is bounded.  Where not all workgroups come to run beside each other
+// in that time (other work holds compute units of the device for seconds) a
+// workgroup that waits in vain sets SlotState::rfail and all of them end, the
+// solve's later launches at once; the host then starts it again on the tile
+// passes.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -57,10 +63,6 @@ template <typename T>
 __device__ __forceinline__ const GLB T *gp(const T *p) { return (const GLB T *)p; }
 
 typedef unsigned long long u64;
-
-// Polls of one exchange before a workgroup gives up (seconds: only a lost
-// workgroup reaches it).
-constexpr int kSpin = 1 << 21;
 
 template <typename T>
 __device__ __forceinline__ T dev_load(const GLB T *p)
@@ -144,10 +146,10 @@ __device__ __forceinline__ double add_waves(const double *red)
 // Sum NV values over the workgroups of a solve: every thread brings its part
 // and leaves with the total, added in an order fixed by the bricks.  The
 // workgroup's earlier stores have reached memory before its sums go out.
-// False when a workgroup did not answer.
+// False when a workgroup did not answer within `polls` looks.
 template <int NV>
 __device__ __forceinline__ bool all_sum(double (&v)[NV], GLB u64 *area, int G, int g, uint32_t tag,
-                                        double (*red)[4 * kWaves], int *fail)
+                                        int polls, double (*red)[4 * kWaves], int *fail)
 {
     const int t = (int)threadIdx.x, w = t >> 6, lane = t & 63;
     // calls alternate the halves: a wave may still read the last call's
@@ -177,12 +179,12 @@ __device__ __forceinline__ bool all_sum(double (&v)[NV], GLB u64 *area, int G, i
     // value m of brick b: pair b NV + m of words
     for (int e = t; e < G * NV; e += kResThreads) {
         const GLB u64 *src = area + 2 * (size_t)e;
-        u64 lo, hi;
+        u64 lo = 0, hi = 0;
         for (int n = 0;; ++n) {
+            if (n >= polls) { ok = false; break; }
             lo = dev_load(src);
             hi = dev_load(src + 1);
             if ((uint32_t)(lo >> 32) == tag && (uint32_t)(hi >> 32) == tag) break;
-            if (n >= kSpin) { ok = false; break; }
         }
         const double d = __longlong_as_double((long long)((lo & 0xffffffffull) | (hi << 32)));
 #pragma unroll
@@ -266,7 +268,7 @@ __device__ __forceinline__ Row<T> cell_row(uint32_t code, const T *tab, T bu, T 
 // being looked up by class.
 template <typename T, int NC, int NZ, bool KEEP, bool FACES>
 __global__ void __launch_bounds__(kResThreads)
-k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
+k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget, int polls)
 {
     constexpr bool F64 = std::is_same<T, double>::value;
     constexpr int NH = res_halo(NC * NZ);
@@ -282,7 +284,7 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
     const int g = (int)blockIdx.x - S.rblk, G = S.rnby * S.rnbz;
     if (!S.resident || g >= G) return;
     SlotState &st = *S.st;
-    if (st.phase != (F64 ? K1_CG_A : K1_IR_A)) return;
+    if (st.rfail || st.phase != (F64 ? K1_CG_A : K1_IR_A)) return;
 
     const int nx = S.nx, ny = S.ny, nz = S.nz, P = nx * ny, bm = S.bcmask;
     const bool px = (S.permask & 1) && nx > 1, py = (S.permask & 2) && ny > 1;
@@ -564,7 +566,7 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
             else column(No{}, Yes{}, c, first_half);
         }
         double v1[1] = { sum };
-        if (!all_sum<1>(v1, area1, G, g, ++tag, red, &s_fail)) break;
+        if (!all_sum<1>(v1, area1, G, g, ++tag, polls, red, &s_fail)) break;
         pap = v1[0];
         if (!isfinite(pap) || !(pap > 0.0)) { end = (F64 || !isfinite(pap)) ? 2 : 3; break; }
         alpha = rz * recip(pap);
@@ -613,7 +615,7 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget)
                 else column(No{}, No{}, c, second_half);
             }
         }
-        if (!all_sum<2>(v2, area2, G, g, ++tag, red, &s_fail)) break;
+        if (!all_sum<2>(v2, area2, G, g, ++tag, polls, red, &s_fail)) break;
         beta = v2[0] * inv_rz;
         rz = v2[0];
         rr = v2[1];
@@ -728,14 +730,17 @@ hipError_t resident_occupancy(int family, int shape, unsigned lds, int *wgs)
 }
 
 // One launch of the resident kernel of shape `shape` over slots [s0, s1) of
-// the table: `blocks` workgroups, all resident at once, `lds` bytes each.
+// the table: `blocks` workgroups, all resident at once, `lds` bytes each; at
+// most `budget` iterations, and `polls` looks at a word before an exchange
+// counts as timed out.
 hipError_t launch_resident(int family, int shape, int blocks, unsigned lds, const Slot *slots,
-                           int s0, int s1, int budget, hipStream_t s)
+                           int s0, int s1, int budget, int polls, hipStream_t s)
 {
     const void *fn = (family == PCG_PREC_FP64 ? kF64 : kF32)[shape].fn;
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    void *args[] = { (void *)&slots, (void *)&s0, (void *)&s1, (void *)&budget };
+    void *args[] = { (void *)&slots, (void *)&s0, (void *)&s1, (void *)&budget,
+                     (void *)&polls };
     return hipLaunchCooperativeKernel(fn, dim3((unsigned)blocks), dim3(kResThreads), args, lds, s);
 }
 

@@ -241,6 +241,13 @@ class Solver:
         L.check(self.lib.pcg_inject_failure(self._ctx, int(after_steps)),
                 "pcg_inject_failure")
 
+    def set_resident_limits(self, iterations: int = 0, polls: int = -1):
+        """Test hook: iterations a launch on the chip takes at most, and looks
+        at another workgroup's sums before an exchange counts as timed out
+        (pcg_set_resident_limits); no arguments restore the defaults."""
+        L.check(self.lib.pcg_set_resident_limits(self._ctx, int(iterations), int(polls)),
+                "pcg_set_resident_limits")
+
     def set_timing(self, on: bool = True):
         L.check(self.lib.pcg_set_timing(self._ctx, int(on)), "pcg_set_timing")
 

@@ -82,11 +82,68 @@ void refinement_trips()
           "refinement: so is a solve of few iterations");
 }
 
+// A solve whose workgroups do not get to run side by side, or whose launch is
+// refused, ends on the tile passes with the same status and iterations, and
+// so do the later ones of the context and every member of a batch.
+void left_the_chip()
+{
+    for (int prec : { PCG_PREC_FP64, PCG_PREC_FP32_IR })
+        for (int refused : { 0, 1 })
+            for (int maxit : { 1000000, 40 }) {
+                dev = Device();
+                pcg_opts_t o{};
+                o.precision = prec;
+                Context c(33, 31, 29, o);
+                const pcg_stats_t a = c.solve(1e-11, maxit);
+                const int sa = c.status;
+                check(sa == (maxit == 40 ? PCG_MAXIT : PCG_OK) && dev.resident > 0, "on the chip");
+                (refused ? dev.refused : dev.timeouts) = 1;
+                const pcg_stats_t b = c.solve(1e-11, maxit);
+                check(c.status == sa && b.iters == a.iters && b.outer_iters == a.outer_iters,
+                      "left the chip: the tile passes solve it");
+                const pcg_stats_t d = c.solve(1e-11, maxit);
+                check(c.status == sa && d.iters == a.iters && dev.resident == 0 && dev.graphs > 0,
+                      "left the chip: the next solve is theirs too");
+            }
+    for (int refused : { 0, 1 }) {
+        dev = Device();
+        pcg_opts_t o{};
+        o.precision = PCG_PREC_FP32_IR;
+        const pcg_grid_t g = { 17, 19, 21, 1.0 };
+        const size_t n = (size_t)g.nx * g.ny * g.nz;
+        std::vector<double> rho(n, 1.0), rhs(n, 1.0), p(n);
+        std::vector<char> mem((16u << 20) + 256);
+        pcg_bc_t bc{};
+        bc.kind[5] = PCG_BC_DIRICHLET;
+        pcg_batch_t *b = nullptr;
+        pcg_batch_create(&b, (void *)(((uintptr_t)mem.data() + 255) / 256 * 256), 16u << 20, 8, &o, nullptr);
+        int32_t slot[5], active = 1, steps = 0;
+        auto admit = [&](int i) {
+            return pcg_batch_admit(b, &g, rho.data(), nullptr, &bc, rhs.data(), p.data(), 1e-11, 1000000, 0,
+                                   &slot[i]);
+        };
+        bool ok = true;
+        for (int i = 0; i < 4; ++i) ok = ok && admit(i) == PCG_OK;
+        ok = ok && pcg_batch_step(b, 1, &active) == PCG_OK && dev.resident > 0;
+        (refused ? dev.refused : dev.timeouts) = 1;
+        ok = ok && pcg_batch_step(b, 1, &active) == PCG_OK && active == 4;
+        ok = ok && admit(4) == PCG_OK;
+        while (ok && active && steps++ < 100) ok = pcg_batch_step(b, 1, &active) == PCG_OK;
+        for (int i = 0; i < 5; ++i) {
+            pcg_stats_t st;
+            ok = ok && pcg_batch_poll(b, slot[i], &st) == PCG_OK && st.iters == 300 && st.outer_iters == 4;
+        }
+        check(ok && !active, "left the chip: every member of a batch ends");
+        pcg_batch_destroy(b);
+    }
+}
+
 }  // namespace
 
 int main()
 {
     refinement_trips();
+    left_the_chip();
     std::printf("%d failed\n", failures);
     return failures != 0;
 }

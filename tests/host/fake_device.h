@@ -15,6 +15,8 @@ struct Device {
     int iters = 100;          // iterations a solve (FP32 + refinement: a trip) takes
     int trips = 3;            // refinement trips
     int cus = 256;
+    int timeouts = 0;         // resident launches from now on that time out
+    int refused = 0;          // and those that fail to launch
     // counted
     int actions = 0, resident = 0, waits = 0, graphs = 0;
     void count_from_zero() { actions = resident = waits = graphs = 0; }
@@ -185,13 +187,16 @@ hipError_t resident_occupancy(int, int, unsigned, int *wgs)
 }
 
 // The resident kernel: `budget` iterations of the solves in their loop.
-hipError_t launch_resident(int, int, int, unsigned, const Slot *slots, int s0, int s1, int budget, hipStream_t)
+hipError_t launch_resident(int, int, int, unsigned, const Slot *slots, int s0, int s1, int budget, int, hipStream_t)
 {
+    if (dev.refused > 0) { --dev.refused; return hipErrorCooperativeLaunchTooLarge; }
     ++dev.resident;
+    const bool late = dev.timeouts > 0 && dev.timeouts--;
     for (int s = s0; s < s1; ++s) {
         SlotState &st = *slots[s].st;
         const bool ir = st.phase == K1_IR_A;
-        if (!slots[s].resident || (st.phase != K1_CG_A && !ir)) continue;
+        if (!slots[s].resident || st.rfail || (st.phase != K1_CG_A && !ir)) continue;
+        if (late) { st.rfail = 1; continue; }
         for (int n = 0; n < budget && (st.phase == K1_CG_A || st.phase == K1_IR_A); ++n) {
             st.iter += 1;
             st.inner_iter += 1;
