@@ -720,11 +720,20 @@ int resident_shapes(int family, ResidentShape *out, int cap)
     return n;
 }
 
+// Lets a shape's workgroups take up to kResLds bytes of LDS.  The attribute
+// belongs to the process, so every caller sets the same value: one thread's
+// launch never meets a smaller one that another has set for its own grid.
+static hipError_t resident_fn(int family, int shape, const void **fn)
+{
+    *fn = (family == PCG_PREC_FP64 ? kF64 : kF32)[shape].fn;
+    return hipFuncSetAttribute(*fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResLds);
+}
+
 // Workgroups of a shape that a CU holds at once with lds bytes each.
 hipError_t resident_occupancy(int family, int shape, unsigned lds, int *wgs)
 {
-    const void *fn = (family == PCG_PREC_FP64 ? kF64 : kF32)[shape].fn;
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const void *fn = nullptr;
+    const hipError_t e = resident_fn(family, shape, &fn);
     if (e != hipSuccess) return e;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(wgs, fn, kResThreads, lds);
 }
@@ -736,11 +745,10 @@ hipError_t resident_occupancy(int family, int shape, unsigned lds, int *wgs)
 hipError_t launch_resident(int family, int shape, int blocks, unsigned lds, const Slot *slots,
                            int s0, int s1, int budget, int polls, hipStream_t s)
 {
-    const void *fn = (family == PCG_PREC_FP64 ? kF64 : kF32)[shape].fn;
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const void *fn = nullptr;
+    const hipError_t e = resident_fn(family, shape, &fn);
     if (e != hipSuccess) return e;
-    void *args[] = { (void *)&slots, (void *)&s0, (void *)&s1, (void *)&budget,
-                     (void *)&polls };
+    void *args[] = { (void *)&slots, (void *)&s0, (void *)&s1, (void *)&budget, (void *)&polls };
     return hipLaunchCooperativeKernel(fn, dim3((unsigned)blocks), dim3(kResThreads), args, lds, s);
 }
 
