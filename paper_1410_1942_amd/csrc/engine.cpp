@@ -1865,7 +1865,7 @@ int pcg_get_tile_rules(int32_t precision, int32_t table, int32_t cap,
 
 static int project_blocks(const SlotHost &S)
 {
-    return (int)col_tiles((int64_t)S.geo.nx * S.geo.ny, S.geo.nz);
+    return (int)col_blocks((int64_t)S.geo.nx * S.geo.ny, S.geo.nz);
 }
 
 int pcg_project(pcg_ctx_t *c, const double *p, double dt, double *u, double *v,

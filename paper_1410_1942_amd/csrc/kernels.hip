@@ -3214,14 +3214,12 @@ template <class F>
 __device__ __forceinline__ void for_columns(const Slot &S, F &&f)
 {
     const int nx = S.nx, nz = S.nz, P = nx * S.ny;
-    const int zc = col_planes(P, nz), pt = (P + kBlock - 1) / kBlock;
-    const int64_t T = (int64_t)pt * ((nz + zc - 1) / zc);
-    const int G = (int)gridDim.x;
-    for (int64_t t = blockIdx.x; t < T; t += G) {
-        const int q = (int)(t % pt) * kBlock + (int)threadIdx.x, zt = (int)(t / pt);
-        if (q >= P) continue;
-        const int j = q / nx;
-        f(q, q - j * nx, j, zt * zc, min(nz, (zt + 1) * zc));
+    const uint32_t T = (uint32_t)col_tiles(P, nz);
+    for (uint32_t t = blockIdx.x; t < T; t += gridDim.x) {
+        const ColumnSpan c = col_span(t, threadIdx.x, P, nz);
+        if (c.k0 >= c.k1) continue;
+        const int j = (int)((uint32_t)c.q / (uint32_t)nx);
+        f(c.q, c.q - j * nx, j, c.k0, c.k1);
     }
 }
 

@@ -47,14 +47,51 @@ struct ResidentShape {
 // device's streams near each other in memory; a small grid takes fewer and so
 // gives about 2048 tiles.  On 384^3 the projection took 663 us at 1, 610 at 4,
 // 703 at 8 and 725 at 16 planes a tile.
+// A plane of fewer than four tiles would leave much of its last one's lanes
+// without a column: there the columns of all chunks of planes are dealt out in
+// a row (projection of 5 x 5 x 200000 cells 144 -> 80 us, 260 x 1 x 20000 100
+// -> 72), and where a wave takes columns of several chunks at once, with one
+// plane each: its lanes then lie side by side in memory (1 x 1 x 4000000 360
+// us at four planes, 89 at one).
+constexpr bool cols_packed(int64_t plane) { return plane < 4 * kBlock; }
 constexpr int col_planes(int64_t plane, int nz)
 {
+    if (cols_packed(plane)) return plane < 16 ? 1 : 4;
     const int64_t t = (plane + kBlock - 1) / kBlock * nz / 2048;
     return t < 1 ? 1 : t > 4 ? 4 : (int)t;
 }
 constexpr int64_t col_tiles(int64_t plane, int nz)
 {
-    return (plane + kBlock - 1) / kBlock * ((nz + col_planes(plane, nz) - 1) / col_planes(plane, nz));
+    const int64_t zc = col_planes(plane, nz), chunks = (nz + zc - 1) / zc;
+    return cols_packed(plane) ? (plane * chunks + kBlock - 1) / kBlock
+                              : (plane + kBlock - 1) / kBlock * chunks;
+}
+// Workgroups for them: one a tile of four planes; tiles of fewer planes are
+// too little work for one each (projection of 4096 x 4096 x 1 cells 271 us
+// with 65536 workgroups, 246 with 8192, 255 with 4096; 1 x 1 x 4000000 92, 94, 97).
+constexpr int64_t col_blocks(int64_t plane, int nz)
+{
+    const int64_t t = col_tiles(plane, nz);
+    return nz >= 4 && col_planes(plane, nz) == 4 ? t : t < 8192 ? t : 8192;
+}
+// Column q of a plane and planes [k0, k1) of a lane of tile t; none: k1 <= k0.
+struct ColumnSpan {
+    int q, k0, k1;
+};
+constexpr ColumnSpan col_span(uint32_t t, uint32_t lane, int plane, int nz)
+{
+    const uint32_t P = (uint32_t)plane, pt = (P + kBlock - 1) / kBlock;
+    const int zc = col_planes(plane, nz);
+    uint32_t q = t * kBlock + lane, zt = 0;   // columns and tiles: fewer than 2^31
+    if (cols_packed(plane)) {
+        zt = q / P;
+        q -= zt * P;
+    } else {
+        zt = t / pt;
+        q = (t - zt * pt) * kBlock + lane;
+    }
+    const int k0 = (int)zt * zc, k1 = nz - k0 > zc ? k0 + zc : nz;
+    return { (int)q, k0, q < P ? k1 : k0 };
 }
 
 // Density classes: up to kMaxFluidClasses distinct fluid densities get a

@@ -138,10 +138,46 @@ void left_the_chip()
     }
 }
 
+// The columns of the kernels around a solve: every cell in one lane's span of
+// planes, most lanes of a full launch with a column, and launches that the
+// runtime takes (fewer than 2^32 threads) up to the largest grid.
+void columns()
+{
+    bool once = true, busy = true, fits = true;
+    for (int P : { 1, 2, 6, 15, 16, 25, 63, 255, 256, 257, 300, 1000, 1023, 1024, 1025, 1300, 5000 })
+        for (int nz : { 1, 2, 3, 4, 5, 7, 64, 333, 2049 }) {
+            std::vector<int> seen((size_t)P * nz, 0);
+            const int64_t T = col_tiles(P, nz);
+            int64_t with = 0;
+            for (int64_t t = 0; t < T; ++t)
+                for (int l = 0; l < kBlock; ++l) {
+                    const ColumnSpan c = col_span((uint32_t)t, (uint32_t)l, P, nz);
+                    with += c.k1 > c.k0;
+                    for (int k = c.k0; k < c.k1; ++k)
+                        if (c.q < 0 || c.q >= P || k < 0 || k >= nz) once = false;
+                        else ++seen[(size_t)k * P + c.q];
+                }
+            for (int v : seen) once = once && v == 1;
+            if (T > 4) busy = busy && with >= 0.75 * T * kBlock;
+        }
+    for (int64_t P : { 1ll, 3ll, 31ll, 63ll, 1023ll, 1024ll, 65537ll, 178956970ll }) {
+        const int nz = (int)std::min<int64_t>(INT32_MAX, ((int64_t(1) << 31) - 1) / P);
+        const int64_t b = col_blocks(P, nz), T = col_tiles(P, nz);
+        fits = fits && b >= 1 && b <= T && b * kBlock <= 0xffffffffll && T <= INT32_MAX &&
+               (T + b) * kBlock / kBlock < 0x100000000ll;
+        const ColumnSpan c = col_span((uint32_t)(T - 1), 0, (int)P, nz);
+        fits = fits && c.q < P && c.k0 >= 0 && c.k0 < c.k1 && c.k1 <= nz;
+    }
+    check(once, "columns: every cell once");
+    check(busy, "columns: three quarters of the lanes have one");
+    check(fits, "columns: launches of the largest grids");
+}
+
 }  // namespace
 
 int main()
 {
+    columns();
     refinement_trips();
     left_the_chip();
     std::printf("%d failed\n", failures);
