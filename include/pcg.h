@@ -470,6 +470,9 @@ int pcg_batch_destroy(pcg_batch_t *b);
  * Tables consulted when opts.tz (or opts.grid_blocks) is 0: a solve of n
  * cells uses the first rule with n <= max_cells[i]: tile height tz[i] and,
  * for single-solve contexts, grid[i] workgroups (0 = library default).
+ * While a table is the built-in one, its single solves of 2^20 cells and more
+ * may take another height, one that fills the device more evenly; installed
+ * rules that differ from it stand as they are.
  * Rules must be ordered by increasing max_cells, 1 <= n <= 64, tz >= 1.
  * There are four tables per precision: table = 0 for single-solve
  * contexts on tiles of consecutive cells, 1 for batches (any tile form),

@@ -162,15 +162,20 @@ std::vector<TileRule> &rules_of(int prec, int table)
     return t[prec == PCG_PREC_FP32_IR ? 1 : 0];
 }
 
+// Tables whose rules in force are others than the built-in ones.
+bool g_installed[2][4] = {};
+
 // Batches use the batch table whatever their tile form; single solves the
 // table of theirs (group: 0 consecutive cells, 1 narrow, else wide plane
 // tiles).
+int table_of(bool batch, int group)
+{
+    return batch ? kTableBatch : group == 1 ? kTableNarrow : group > 1 ? kTablePlane : kTableSingle;
+}
+
 const TileRule &rule_for(int64_t n, int prec, bool batch, int group)
 {
-    const int table = batch ? kTableBatch
-                      : group == 1 ? kTableNarrow
-                      : group > 1 ? kTablePlane : kTableSingle;
-    const auto &rules = rules_of(prec, table);
+    const auto &rules = rules_of(prec, table_of(batch, group));
     for (const auto &r : rules)
         if (n <= r.max_cells) return r;
     return rules.back();
@@ -1037,8 +1042,11 @@ struct Engine {
         S.tile_room = geo.ntiles;
         p += align_up(kMaxPartials * 8 * (size_t)geo.ntiles, kAlign);
         // a single solve takes the better height (the caller's own launch
-        // shape stands), with more tiles where the workspace has spare bytes
-        if (!batch_mode() && tz_opt == 0 && grid_opt == 0) {
+        // shape and tables stand), with more tiles where the workspace has
+        // spare bytes
+        const int table = table_of(false, geo.tx > 0 ? geo.cpt : 0);
+        if (!batch_mode() && tz_opt == 0 && grid_opt == 0 &&
+            !g_installed[prec == PCG_PREC_FP32_IR][table]) {
             size_t spare = 0;
             if (geo.ntiles < kTileRoom && alloc.alloc(kMaxPartials * 8 * kTileRoom, &spare)) {
                 S.spare = spare;
@@ -1843,6 +1851,18 @@ int pcg_set_tile_rules(int32_t precision, int32_t table, int32_t n,
         rules.push_back({ max_cells[i], tz[i], g });
     }
     rules.back().max_cells = INT64_MAX;   // the last rule covers every size
+    // the tables as built in, from the first call: only this function changes them
+    static const std::vector<std::vector<TileRule>> built_in = [] {
+        std::vector<std::vector<TileRule>> all;
+        for (int t = 0; t < 8; ++t) all.push_back(rules_of(t / 4 ? PCG_PREC_FP32_IR : PCG_PREC_FP64, t % 4));
+        return all;
+    }();
+    const int ir = precision == PCG_PREC_FP32_IR;
+    const auto &own = built_in[4 * ir + table];
+    g_installed[ir][table] = !std::equal(rules.begin(), rules.end(), own.begin(), own.end(),
+                                         [](const TileRule &a, const TileRule &b) {
+                                             return a.max_cells == b.max_cells && a.tz == b.tz && a.grid == b.grid;
+                                         });
     rules_of(precision, table) = rules;
     return PCG_OK;
 }

@@ -173,10 +173,42 @@ void columns()
     check(fits, "columns: launches of the largest grids");
 }
 
+// Tile heights: a table that the caller installed is taken at its word; the
+// built-in one (installed again, too) leaves room for more even heights.
+void tile_rules()
+{
+    dev = Device();
+    for (int prec : { PCG_PREC_FP64, PCG_PREC_FP32_IR })
+        for (int flags : { (int)PCG_FLAT_TILES, (int)PCG_PLANE_TILES, (int)PCG_NARROW_TILES }) {
+            const int table = flags == PCG_FLAT_TILES ? 0 : flags == PCG_PLANE_TILES ? 2 : 3;
+            const int nx = table == 3 ? 131 : 132;
+            pcg_opts_t o{};
+            o.precision = prec;
+            o.flags = flags;
+            auto geometry = [&] {
+                Context c(nx, 90, 97, o, 48 << 10);
+                return c.c->eng.slots[0].geo;
+            };
+            const int table_tz = rule_for((int64_t)nx * 90 * 97, prec, false, table == 0 ? 0 : table == 3 ? 1 : 2).tz;
+            const int before = geometry().tz;
+            check(before != table_tz, "tile rules: the built-in height is replaced");
+            int64_t mc[64];
+            int32_t tz[64], gr[64], n = 0;
+            pcg_get_tile_rules(prec, table, 64, mc, tz, gr, &n);
+            const int64_t all[1] = { INT64_MAX };
+            const int32_t own_tz[1] = { 17 }, own_grid[1] = { 256 };
+            pcg_set_tile_rules(prec, table, 1, all, own_tz, own_grid);
+            check(geometry().tz == 17, "tile rules: an installed height stands");
+            pcg_set_tile_rules(prec, table, n, mc, tz, gr);
+            check(geometry().tz == before, "tile rules: the built-in ones again");
+        }
+}
+
 }  // namespace
 
 int main()
 {
+    tile_rules();
     columns();
     refinement_trips();
     left_the_chip();
