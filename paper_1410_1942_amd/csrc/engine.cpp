@@ -1478,16 +1478,18 @@ struct Engine {
     }
 
     // One polling step of the resident solves: the actions they are waiting
-    // for, and check_every iterations.  *left: a launch was refused, and they
-    // have left the resident kernel.
-    int resident_step(bool others, bool *left)
+    // for, and check_every iterations.  seen: the host has seen their phases
+    // (else a solve may have left its loop since: the actions after that too).
+    // *left: a launch was refused, and they have left the resident kernel.
+    int resident_step(bool others, bool seen, bool *left)
     {
         const bool ir = prec == PCG_PREC_FP32_IR;
         int pre = 0;
         for (int id = 0; id < max_slots; ++id) {
             SlotHost &S = slots[id];
             if (!S.used || !S.running || !S.resident) continue;
-            pre = std::max(pre, actions_before(h_states[id].phase, ir, S.singular, !k2only));
+            const int phase = seen ? h_states[id].phase : ir ? K1_IR_RESID : K1_CHECK64;
+            pre = std::max(pre, actions_before(phase, ir, S.singular, !k2only));
         }
         if (!others) HIP_TRY(launch_actions(pre));   // else the others' launches took them
         for (const ResidentLaunch &q : rlaunch)
@@ -1582,7 +1584,7 @@ struct Engine {
                 if (st || !wait) return st;
             } else if (nresident) {
                 bool left = false;
-                st = resident_step(others, &left);
+                st = resident_step(others, r == 0, &left);
                 if (st || left) return st;
             }
         }

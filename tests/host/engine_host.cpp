@@ -138,6 +138,39 @@ void left_the_chip()
     }
 }
 
+// A step of several replays takes a batch's solves through their trips (and
+// to the checks behind the last), not only to the end of the next one.
+void several_replays()
+{
+    for (int prec : { PCG_PREC_FP64, PCG_PREC_FP32_IR })
+        for (int top : { PCG_BC_DIRICHLET, PCG_BC_NEUMANN })
+            for (int flags : { 0, (int)PCG_TWO_SWEEPS }) {
+                dev = Device();
+                // ten replays, or three trips of five: the first step of
+                // eight ends within a loop
+                dev.iters = prec == PCG_PREC_FP64 ? 300 : 150;
+                pcg_opts_t o{};
+                o.precision = prec;
+                const pcg_grid_t g = { 17, 19, 21, 1.0 };
+                const size_t n = (size_t)g.nx * g.ny * g.nz;
+                std::vector<double> rho(n, 1.0), rhs(n, 1.0), p(n);
+                std::vector<char> mem((16u << 20) + 256);
+                pcg_bc_t bc{};
+                bc.kind[5] = top;
+                pcg_batch_t *b = nullptr;
+                pcg_batch_create(&b, (void *)(((uintptr_t)mem.data() + 255) / 256 * 256), 16u << 20, 8, &o,
+                                 nullptr);
+                int32_t slot, active = 1, steps = 0;
+                bool ok = true;
+                for (int i = 0; i < 4; ++i)
+                    ok = ok && pcg_batch_admit(b, &g, rho.data(), nullptr, &bc, rhs.data(), p.data(), 1e-11,
+                                               1000000, flags, &slot) == PCG_OK;
+                while (ok && active && steps++ < 100) ok = pcg_batch_step(b, 8, &active) == PCG_OK;
+                check(ok && steps <= 2 + (top == PCG_BC_NEUMANN), "several replays a step");
+                pcg_batch_destroy(b);
+            }
+}
+
 // The columns of the kernels around a solve: every cell in one lane's span of
 // planes, most lanes of a full launch with a column, and launches that the
 // runtime takes (fewer than 2^32 threads) up to the largest grid.
@@ -212,6 +245,7 @@ int main()
     columns();
     refinement_trips();
     left_the_chip();
+    several_replays();
     std::printf("%d failed\n", failures);
     return failures != 0;
 }
