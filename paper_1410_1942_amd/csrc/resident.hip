@@ -110,6 +110,11 @@ __device__ __forceinline__ double recip(double d)
 }
 __device__ __forceinline__ float recip(float d) { return __builtin_amdgcn_rcpf(d); }
 
+// Whether recip(b) and its refinement stay within the range of normal numbers;
+// sums of solves scaled near its ends (a source of 1e-150 with densities of
+// 1e-9) do not, and are divided by.
+__device__ __forceinline__ bool recip_range(double b) { return b > 0x1p-1000 && b < 0x1p1000; }
+
 // Face coefficient 2 / (a + b) of two cells' densities, 0 at solids (+inf).
 template <typename T>
 __device__ __forceinline__ T face_beta(T den)
@@ -569,7 +574,7 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget, int polls
         if (!all_sum<1>(v1, area1, G, g, ++tag, polls, red, &s_fail)) break;
         pap = v1[0];
         if (!isfinite(pap) || !(pap > 0.0)) { end = (F64 || !isfinite(pap)) ? 2 : 3; break; }
-        alpha = rz * recip(pap);
+        alpha = !F64 || recip_range(pap) ? rz * recip(pap) : rz / pap;
 
         // x += alpha p, z -= alpha q / diag, the faces of z, r.z and r.r
         const T ta = (T)alpha;
@@ -616,7 +621,7 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget, int polls
             }
         }
         if (!all_sum<2>(v2, area2, G, g, ++tag, polls, red, &s_fail)) break;
-        beta = v2[0] * inv_rz;
+        beta = !F64 || recip_range(rz) ? v2[0] * inv_rz : v2[0] / rz;
         rz = v2[0];
         rr = v2[1];
         ++iter;
