@@ -39,7 +39,8 @@ def build(verbose: bool = False, extra=None) -> str:
         for cmd, code in codes:
             if code:
                 raise subprocess.CalledProcessError(code, cmd)
-        subprocess.run([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", *objs,
+        # no undefined symbols: a lost kernel file fails here, not at run time
+        subprocess.run([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-Wl,-z,defs", *objs,
                         "-o", LIB + ".tmp"], check=True)
     os.replace(LIB + ".tmp", LIB)
     return LIB

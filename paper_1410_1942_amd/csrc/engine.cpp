@@ -21,13 +21,17 @@
 #include "pcg.h"
 #include "pcg_types.h"
 
+// The library has every launcher (its link allows no undefined symbol).  A
+// build of this file alone, for its host code, may do without some of them.
+#ifdef __HIP__
+#define PCG_MAY_LACK
+#else
+#define PCG_MAY_LACK __attribute__((weak))
+#endif
+
 namespace pcgmi {
 hipError_t launch_iter(int family, int which, int mode, int grid,
                        const BatchHeader *hdr, const Slot *slots, hipStream_t s);
-__attribute__((weak)) hipError_t launch_setup(const double *rho, const uint8_t *mask, double *r64,
-                                              float *r32, uint8_t *cls, int64_t n, int *bad,
-                                              unsigned long long *words, double *t64, float *t32,
-                                              hipStream_t s);
 hipError_t launch_copy(const double *src, double *dst, size_t n, hipStream_t s);
 hipError_t launch_pack_mask(const uint8_t *mask, uint32_t *bits, int nx,
                             int words_per_row, int64_t nwords, hipStream_t s);
@@ -45,13 +49,15 @@ hipError_t launch_divnorm(const Slot *slot, double inv_h, const double *u,
                           const double *v, const double *w, double *part, int blocks,
                           hipStream_t st);
 hipError_t static_scratch(void **ptr, size_t *bytes);
-// The resident kernel (resident.hip); weak, so that the host engine also
-// links without its device side (then no solve is resident).
-__attribute__((weak)) int resident_shapes(int family, ResidentShape *out, int cap);
-__attribute__((weak)) hipError_t resident_occupancy(int family, int shape, unsigned lds, int *wgs);
-__attribute__((weak)) hipError_t launch_resident(int family, int shape, int blocks, unsigned lds,
-                                                 const Slot *slots, int s0, int s1, int budget,
-                                                 int polls, hipStream_t s);
+PCG_MAY_LACK hipError_t launch_setup(const double *rho, const uint8_t *mask, double *r64, float *r32,
+                                     uint8_t *cls, int64_t n, int *bad, unsigned long long *words,
+                                     double *t64, float *t32, hipStream_t s);
+// the resident kernel (resident.hip)
+PCG_MAY_LACK int resident_shapes(int family, ResidentShape *out, int cap);
+PCG_MAY_LACK hipError_t resident_occupancy(int family, int shape, unsigned lds, int *wgs);
+PCG_MAY_LACK hipError_t launch_resident(int family, int shape, int blocks, unsigned lds,
+                                        const Slot *slots, int s0, int s1, int budget, int polls,
+                                        hipStream_t s);
 }  // namespace pcgmi
 
 using namespace pcgmi;
@@ -424,6 +430,7 @@ ResidentPlan resident_bricks(const pcg_grid_t &g, int prec, const ResidentShape 
     const int64_t cols = (int64_t)sh.cols * kResThreads;
     if (g.nx > cols) return p;
     p.rbz = sh.planes;
+    if (g.nz > (1 << 20)) return p;            // (far more bricks than any device holds)
     p.rnbz = (g.nz + p.rbz - 1) / p.rbz;
     p.rby = (int)std::min<int64_t>(g.ny, cols / g.nx);
     p.rnby = (g.ny + p.rby - 1) / p.rby;
@@ -896,20 +903,18 @@ struct Engine {
         HIP_TRY(hipMemcpyAsync(d_hdr, h_hdr, sizeof(BatchHeader), hipMemcpyHostToDevice, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         if (!mirror) HIP_TRY(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
-        if (resident_shapes) {
-            int dev = 0, cus = 0, coop = 0;
-            HIP_TRY(hipGetDevice(&dev));
-            HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-            HIP_TRY(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
-            nshapes = coop ? std::min(kMaxShapes, resident_shapes(prec, rshapes, kMaxShapes)) : 0;
-            // one brick a CU for single solves, whose exchanges grow with the
-            // bricks; batches fill what fits
-            for (int i = 0; i < nshapes; ++i) {
-                int wgs = 1;
-                if (is_batch)
-                    HIP_TRY(resident_occupancy(prec, i, kResLds / (rshapes[i].batch > 0 ? rshapes[i].batch : 1), &wgs));
-                rcap[i] = cus * (is_batch ? std::min(wgs, rshapes[i].batch) : 1);
-            }
+        int device = 0, cus = 0, coop = 0;
+        HIP_TRY(hipGetDevice(&device));
+        HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
+        HIP_TRY(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, device));
+        nshapes = coop ? std::min(kMaxShapes, resident_shapes(prec, rshapes, kMaxShapes)) : 0;
+        // one brick a CU for single solves, whose exchanges grow with the
+        // bricks; batches fill what fits
+        for (int i = 0; i < nshapes; ++i) {
+            int wgs = 1;
+            if (is_batch)
+                HIP_TRY(resident_occupancy(prec, i, kResLds / (rshapes[i].batch > 0 ? rshapes[i].batch : 1), &wgs));
+            rcap[i] = cus * (is_batch ? std::min(wgs, rshapes[i].batch) : 1);
         }
         return PCG_OK;
     }
@@ -1133,9 +1138,8 @@ struct Engine {
         for (int r = 0; r <= kMaxFluidClasses; ++r) h_words[r] = ~0ull;
         hipError_t e = hipMemcpyAsync(d_bad, h_bad, bytes, hipMemcpyHostToDevice, stream);
         if (e == hipSuccess)
-            e = launch_setup ? launch_setup(rho, mask, S.rho64, S.rho32, want_classes ? S.cls : nullptr,
-                                            geo.n, d_bad, d_words, S.tab64, S.tab32, stream)
-                             : hipErrorNoDevice;
+            e = launch_setup(rho, mask, S.rho64, S.rho32, want_classes ? S.cls : nullptr, geo.n, d_bad,
+                             d_words, S.tab64, S.tab32, stream);
         if (e == hipSuccess) e = hipMemcpyAsync(h_bad, d_bad, bytes, hipMemcpyDeviceToHost, stream);
         if (e == hipSuccess) e = hipStreamSynchronize(stream);
         if (e != hipSuccess) return hip_fail(e, "encode");

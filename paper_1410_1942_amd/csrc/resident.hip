@@ -51,6 +51,7 @@
 
 #include "pcg_types.h"
 #include "pcg.h"
+#include "resident_shapes.h"
 
 namespace pcgmi {
 
@@ -676,44 +677,12 @@ struct Entry {
     ResidentShape shape;
     const void *fn;
 };
-template <typename T, int NC, int NZ, bool KEEP>
-Entry entry(int batch = 0)
-{
-    return { { NC, NZ, KEEP, false, batch }, (const void *)k_resident<T, NC, NZ, KEEP, false> };
-}
-template <typename T, int NC, int NZ, bool KEEP>
-Entry faces()
-{
-    return { { NC, NZ, KEEP, true, 0 }, (const void *)k_resident<T, NC, NZ, KEEP, true> };
-}
-// Shapes.  FP64 keeps q and the diagonal in registers up to 16 cells a thread,
-// FP32 up to 32 (256 registers a thread with two waves a SIMD); batches take
-// the first shape marked that holds a grid (two workgroups a CU where its
-// registers allow, which hide each other's exchanges).
-const Entry kF64[] = {
-    entry<double, 1, 1, true>(),  entry<double, 1, 2, true>(),  entry<double, 1, 3, true>(),
-    entry<double, 1, 4, true>(),  entry<double, 2, 2, true>(),  entry<double, 1, 6, true>(),
-    entry<double, 2, 4, true>(),  entry<double, 1, 8, true>(1), entry<double, 2, 6, true>(),
-    entry<double, 3, 4, true>(),  entry<double, 2, 8, true>(1), entry<double, 4, 4, true>(),
-    entry<double, 4, 6, false>(), entry<double, 3, 8, false>(), entry<double, 5, 6, false>(),
-    entry<double, 4, 8, false>(1),
-    faces<double, 1, 1, true>(),  faces<double, 1, 2, true>(),  faces<double, 1, 4, true>(),
-    faces<double, 2, 2, true>(),  faces<double, 1, 6, true>(),  faces<double, 2, 4, true>(),
-    faces<double, 1, 8, true>(),  faces<double, 2, 5, true>(),  faces<double, 3, 4, false>(),
-    faces<double, 2, 6, false>(),
-};
-const Entry kF32[] = {
-    entry<float, 1, 1, true>(),  entry<float, 1, 2, true>(),  entry<float, 1, 3, true>(),
-    entry<float, 1, 4, true>(),  entry<float, 2, 2, true>(),  entry<float, 1, 6, true>(),
-    entry<float, 2, 4, true>(),  entry<float, 1, 8, true>(2), entry<float, 2, 6, true>(),
-    entry<float, 3, 4, true>(),  entry<float, 4, 4, true>(),  entry<float, 2, 8, true>(),
-    entry<float, 3, 8, true>(),  entry<float, 4, 6, true>(),  entry<float, 5, 6, true>(),
-    entry<float, 4, 8, true>(1), entry<float, 6, 8, false>(1),
-    faces<float, 1, 1, true>(),  faces<float, 1, 2, true>(),  faces<float, 1, 4, true>(),
-    faces<float, 2, 2, true>(),  faces<float, 2, 4, true>(),  faces<float, 1, 8, true>(),
-    faces<float, 3, 4, true>(),  faces<float, 2, 8, true>(),  faces<float, 4, 4, true>(),
-    faces<float, 3, 6, true>(),  faces<float, 5, 4, true>(),  faces<float, 4, 6, false>(),
-};
+#define PCG_ENTRY64(c, p, keep, faces, batch) \
+    { { c, p, keep, faces, batch }, (const void *)k_resident<double, c, p, keep, faces> },
+#define PCG_ENTRY32(c, p, keep, faces, batch) \
+    { { c, p, keep, faces, batch }, (const void *)k_resident<float, c, p, keep, faces> },
+const Entry kF64[] = { PCG_RESIDENT_FP64(PCG_ENTRY64) };
+const Entry kF32[] = { PCG_RESIDENT_FP32(PCG_ENTRY32) };
 }  // namespace
 
 int resident_shapes(int family, ResidentShape *out, int cap)

@@ -237,10 +237,70 @@ void tile_rules()
         }
 }
 
+// The resident plan: every cell in one brick, no brick without cells, and
+// each bound that the kernel relies on (threads, LDS, rows beside a brick, the
+// reciprocal that divides by the row length, exchange words, workgroups).
+void bricks()
+{
+    dev = Device();
+    bool cover = true, bounds = true, some = false, none = true, exact = true;
+    std::vector<ResidentShape> shapes(64);
+    for (int prec : { PCG_PREC_FP64, PCG_PREC_FP32_IR }) {
+        const int ns = resident_shapes(prec, shapes.data(), 64);
+        const size_t es = prec == PCG_PREC_FP32_IR ? 4 : 8;
+        for (const bool batch : { false, true }) {
+            std::vector<int> cap;
+            for (int i = 0; i < ns; ++i) cap.push_back(dev.cus * (batch ? shapes[i].batch : 1));
+            for (const bool faces : { false, true })
+                for (int nx : { 1, 2, 3, 24, 33, 97, 128, 255, 320, 511, 512, 513, 1000, 1536, 2560, 3071, 3072, 3073 })
+                    for (int ny : { 1, 2, 3, 7, 29, 64, 101, 128, 500 })
+                        for (int nz : { 1, 2, 5, 8, 9, 45, 96, 150, 2000 }) {
+                            const pcg_grid_t g = { nx, ny, nz, 1.0 };
+                            const ResidentPlan p =
+                                resident_plan(g, prec, pcg_opts_t{}, batch, faces, shapes.data(), cap.data(), ns);
+                            if (p.shape < 0) continue;
+                            some = true;
+                            const ResidentShape &sh = shapes[p.shape];
+                            std::vector<int> seen((size_t)ny * nz, 0);
+                            for (int b = 0; b < p.bricks(); ++b) {
+                                const int j0 = b % p.rnby * p.rby, k0 = b / p.rnby * sh.planes;
+                                const int by = std::min(p.rby, ny - j0), bz = std::min(sh.planes, nz - k0);
+                                cover = cover && by >= 1 && bz >= 1;
+                                for (int k = k0; k < k0 + bz; ++k)
+                                    for (int j = j0; j < j0 + by; ++j) ++seen[(size_t)k * ny + j];
+                            }
+                            for (int v : seen) cover = cover && v == 1;
+                            const int halo = res_halo(sh.cols * sh.planes) * kResThreads;
+                            const size_t row = nx + 2, plane = (p.rby + 2) * row;
+                            // the last row beside a brick, its cell's x + 1 neighbour
+                            const size_t last = (sh.planes - 1) * plane + (p.rby + 1) * row + nx + 1;
+                            bounds = bounds && p.rbz == sh.planes && sh.faces == faces &&
+                                     (int64_t)nx * p.rby <= (int64_t)sh.cols * kResThreads &&
+                                     (last + 1) * es <= p.lds && p.lds <= kResLds / (batch ? sh.batch : 1) &&
+                                     2 * sh.planes * nx <= halo && halo <= 4096 && nx <= 4096 &&
+                                     (size_t)p.bricks() * kResWords * 8 <= es * nx * ny * nz &&
+                                     p.bricks() <= cap[p.shape];
+                        }
+            for (const pcg_grid_t g : { pcg_grid_t{ 1, 1, INT32_MAX, 1.0 }, pcg_grid_t{ 3072, 1, 699050, 1.0 },
+                                        pcg_grid_t{ 1, 178956970, 12, 1.0 }, pcg_grid_t{ 512, 512, 512, 1.0 } })
+                none = none && resident_plan(g, prec, pcg_opts_t{}, batch, false, shapes.data(), cap.data(), ns).shape < 0;
+        }
+    }
+    for (uint32_t nx = 2; nx <= 4096; ++nx) {
+        const uint32_t inv = ((1u << 24) + nx - 1u) / nx;
+        for (uint32_t m = 0; m < 4096; ++m) exact = exact && (uint32_t)(((uint64_t)(m << 8) * inv) >> 32) == m / nx;
+    }
+    check(some && cover, "bricks: every cell in one");
+    check(bounds, "bricks: within the kernel's bounds");
+    check(none, "bricks: grids too large have none");
+    check(exact, "bricks: the row of a value beside one");
+}
+
 }  // namespace
 
 int main()
 {
+    bricks();
     tile_rules();
     columns();
     refinement_trips();

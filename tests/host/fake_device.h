@@ -11,6 +11,8 @@
 #include <cstring>
 #include <vector>
 
+#include "resident_shapes.h"
+
 struct Device {
     int iters = 100;          // iterations a solve (FP32 + refinement: a trip) takes
     int trips = 3;            // refinement trips
@@ -172,11 +174,13 @@ hipError_t launch_divnorm(const Slot *, double, const double *, const double *, 
 }
 hipError_t static_scratch(void **, size_t *) { return hipErrorNoDevice; }
 
-int resident_shapes(int, ResidentShape *out, int cap)
+#define PCG_SHAPE(c, p, keep, faces, batch) { c, p, keep, faces, batch },
+int resident_shapes(int family, ResidentShape *out, int cap)
 {
-    static const ResidentShape s[] = { { 1, 4, true, false, 1 }, { 4, 8, false, false, 1 }, { 2, 4, true, true, 0 } };
+    static const std::vector<ResidentShape> s[2] = { { PCG_RESIDENT_FP64(PCG_SHAPE) },
+                                                     { PCG_RESIDENT_FP32(PCG_SHAPE) } };
     int n = 0;
-    for (const ResidentShape &r : s)
+    for (const ResidentShape &r : s[family == PCG_PREC_FP32_IR])
         if (n < cap) out[n++] = r;
     return n;
 }
