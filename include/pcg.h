@@ -159,6 +159,20 @@ enum {
 };
 
 /*
+ * Where a solve iterates.  A grid that fits on the chip (by default: up to 4.2
+ * million cells FP64 and 6.3 million FP32_IR with density classes, about 1.3
+ * and 3 million without or with cut-cell fractions, in batches with classes
+ * only) keeps its vectors there, and one launch runs whole stretches of
+ * iterations (pcg_resident_form); set-up, residuals and updates, and all
+ * iterations of other grids, are passes over tiles.  A tile form asked for
+ * (PCG_FLAT_TILES, PCG_PLANE_TILES, PCG_TWO_SWEEPS, PCG_NARROW_TILES), tz or
+ * grid_blocks given, and a timed solve (pcg_set_timing) stay with the tile
+ * passes, and so does a context with PCG_FRACTIONS until fractions are set.
+ * Iterating on the chip takes all of a launch's workgroups at once.  Where
+ * other work keeps part of the device for seconds, or the runtime refuses the
+ * launch, the solve starts again on the tile passes (from zero, or from what p
+ * holds when it was a warm start), and its context or batch stays with them.
+ *
  * Options.  Zero-initialised fields take the defaults in brackets.
  *   precision   PCG_PREC_FP64 [default] or PCG_PREC_FP32_IR: FP32 stencil
  *               and vectors inside, FP64 residual, dot products, alpha/beta
@@ -168,7 +182,7 @@ enum {
  *               iterations have ended)
  *   flags       PCG_WARM_START | PCG_SKIP_CONNECTIVITY_CHECK |
  *               PCG_NO_DENSITY_CLASSES | PCG_FRACTIONS | PCG_FLAT_TILES |
- *               PCG_PLANE_TILES | PCG_TWO_SWEEPS
+ *               PCG_PLANE_TILES | PCG_TWO_SWEEPS | PCG_NARROW_TILES
  *   inner_maxit FP32_IR: cap on inner iterations per refinement trip [none]
  *   inner_tol   FP32_IR: relative reduction asked of each inner solve, never
  *               more than the last refinement trip needs [1e-4]
@@ -271,18 +285,26 @@ int pcg_check_connectivity(const uint8_t *host_mask, const pcg_grid_t *grid,
 /*
  * Number of density classes the context codes its field with (1..14), or 0
  * when it reads a density per cell (more distinct densities than classes,
- * or PCG_NO_DENSITY_CLASSES).
+ * or PCG_NO_DENSITY_CLASSES) and while fractions are set.
  */
 int pcg_density_classes(const pcg_ctx_t *ctx, int32_t *nclasses);
 
 /*
- * Tile form of a context: *tx, *ty = columns and rows of its 2-D plane tiles
+ * Tile form of a context (of its set-up, residual and update passes only
+ * where it iterates on the chip): *tx, *ty = columns and rows of its 2-D plane tiles
  * (128 x 4 FP64, 256 x 4 FP32, 64 x 4 narrow tiles), or 0, 0 when its tiles are runs of
  * consecutive cells; *sweeps = passes over the grid per iteration (1: the
  * one-sweep iteration on plane tiles, else 2).  PCG_EINVAL for null
  * arguments.
  */
 int pcg_tile_form(const pcg_ctx_t *ctx, int32_t *tx, int32_t *ty, int32_t *sweeps);
+
+/*
+ * How the context's next solve iterates: *workgroups = those it keeps its
+ * vectors in on the chip, *cells = most cells a thread of them, or 0, 0 when it
+ * iterates by passes over tiles.  PCG_EINVAL for null arguments.
+ */
+int pcg_resident_form(const pcg_ctx_t *ctx, int32_t *workgroups, int32_t *cells);
 
 /*
  * Velocity projection (Section 2.1: u* = u - dt (1/rho) grad P on the MAC
@@ -354,8 +376,7 @@ int pcg_rhs(pcg_ctx_t *ctx, double dt, const double *au, const double *av,
  * The arrays are copied into the workspace (set up with PCG_FRACTIONS, else
  * PCG_EINVAL) and validated on the device (PCG_EDOMAIN when out of range, and
  * the context then has no fractions).  All four NULL returns the context to
- * the binary hull.  While fractions are set the density is read per cell
- * (no density classes).  Blocks until done.
+ * the binary hull.  Blocks until done.
  */
 int pcg_set_fractions(pcg_ctx_t *ctx, const double *ax, const double *ay, const double *az,
                       const double *vol);
@@ -396,12 +417,13 @@ const char *pcg_last_hip_error(void);
 
 /*
  * A batch keeps several independent solves resident on the device and
- * advances all of them together: every launch covers the tiles of every
- * active solve, and each solve's iterations are captured once in a hipGraph
- * and replayed.  Solves may be admitted and released between steps
+ * advances all of them together.  Members that fit on the chip iterate there,
+ * as many a launch as the device holds at once; the others by passes over
+ * tiles, whose launches cover every such solve and are captured once in a
+ * hipGraph and replayed.  Solves may be admitted and released between steps
  * (continuous batching).  A solve's arithmetic depends only on its own
  * grid, tile shape and data, so its result is bitwise the same alone or in
- * any mix.
+ * any mix (unless one could not stay on the chip, see above).
  *
  *   arena       device buffer owned by the caller; admission succeeds only
  *               while the sum of the resident solves' footprints fits in it
@@ -432,8 +454,8 @@ int pcg_batch_admit(pcg_batch_t *b, const pcg_grid_t *grid, const double *rho,
                     int32_t *slot);
 
 /*
- * Run `replays` captured graphs of check_every iterations each over every
- * active solve, then refresh the host mirror of every solve's status.
+ * Run `replays` times check_every iterations of every active solve, then
+ * refresh the host mirror of every solve's status.
  * Blocks until the work is done.  *active_out (may be NULL) receives the
  * number of solves still running.
  */
@@ -542,8 +564,9 @@ int pcg_solve_static(const pcg_grid_t *grid, const double *rho, const uint8_t *s
 /* ---- measurement helpers ---------------------------------------------- */
 
 /*
- * Kernel timing of pcg_solve.  After pcg_set_timing(ctx, 1) the solve
- * launches its two iteration kernels directly (not through the captured
+ * Kernel timing of pcg_solve by passes over tiles.  After pcg_set_timing(ctx,
+ * 1) the solve, also one that would iterate on the chip, launches its two
+ * iteration kernels directly (not through the captured
  * graph) with a hipEvent recorded on the context's stream around each
  * launch; pcg_last_timing then gives the average duration (ms) of the first
  * (direction update + p.Ap) and second (operator apply + vector update +

@@ -736,8 +736,8 @@ struct SlotHost {
 
 // Coefficient mode of a slot, as the kernels derive it from its description
 // (kernel template argument MODE): 0 per-cell density, 1 density classes,
-// 2 per-cell density with cut-cell fractions, 3 classes and 4 per-cell
-// density on 2-D plane tiles.
+// 2 cut-cell fractions (over either), 3 classes and 4 per-cell density on 2-D
+// plane tiles.
 constexpr int kModes = 5;
 int slot_mode(const SlotHost &S)
 {
@@ -1163,6 +1163,16 @@ struct Engine {
         return encode_slot(S, rho, mask, flags);
     }
 
+    // The resident form that a solve of the slot takes: that of its coefficients,
+    // unless each launch is timed.  A context with room for fractions takes it
+    // once they are set; the binary hull on such a context stays on its tiles,
+    // as does a batch member without classes: neither has been measured.
+    ResidentPlan resident_form(const SlotHost &S) const
+    {
+        if (timing || no_resident || S.has_frac != frac_space) return ResidentPlan{};
+        return S.has_frac || !S.classes ? S.by_face : S.by_class;
+    }
+
     // Start a solve on a prepared slot.
     int start(int id, const double *rhs, double *x, double tol, int maxit, int flags)
     {
@@ -1189,9 +1199,8 @@ struct Engine {
         h.inner_maxit = inner_maxit > 0 ? inner_maxit : INT32_MAX;
         h.inner_tol2 = inner_tol * inner_tol;
         h.warm = (flags & PCG_WARM_START) ? 1 : 0;
-        // grids with a resident form, unless each launch is timed
-        S.res = S.has_frac || !S.classes ? S.by_face : S.by_class;
-        S.resident = S.res.shape >= 0 && !timing && !no_resident && S.has_frac == frac_space;
+        S.res = resident_form(S);
+        S.resident = S.res.shape >= 0;
         S.rstage = S.rtrips = S.rwaits = 0;
         h.resident = S.resident ? 1 : 0;
         h.fused = S.z2 && !S.resident ? 1 : 0;
@@ -1998,6 +2007,16 @@ int pcg_tile_form(const pcg_ctx_t *c, int32_t *tx, int32_t *ty, int32_t *sweeps)
     *tx = S.geo.tx;
     *ty = S.geo.ty;
     *sweeps = S.z2 ? 1 : 2;
+    return PCG_OK;
+}
+
+int pcg_resident_form(const pcg_ctx_t *c, int32_t *workgroups, int32_t *cells)
+{
+    if (!c || !workgroups || !cells) return PCG_EINVAL;
+    const ResidentPlan p = c->eng.resident_form(c->eng.slots[c->slot]);
+    const ResidentShape *sh = p.shape >= 0 ? &c->eng.rshapes[p.shape] : nullptr;
+    *workgroups = sh ? p.bricks() : 0;
+    *cells = sh ? sh->cols * sh->planes : 0;
     return PCG_OK;
 }
 

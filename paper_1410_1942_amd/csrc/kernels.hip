@@ -2645,7 +2645,7 @@ __device__ void advance(SlotState &st, int phase, const double (&tot)[3])
 // workgroups per CU use).  K1 and K2 come in three coefficient modes
 // (density, classes, cut cells), each serving only the slots of its mode.
 // Coefficient mode of a slot: 0 per-cell density, 1 density classes,
-// 2 per-cell density with free-slip cut cells (area/volume fractions);
+// 2 free-slip cut cells (area/volume fractions) with either as keys;
 // 3 classes and 4 per-cell density on 2-D plane tiles (LDS-staged pass B).
 __device__ __forceinline__ int slot_mode(const Slot &S)
 {

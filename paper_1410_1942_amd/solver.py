@@ -184,6 +184,15 @@ class Solver:
                                        ctypes.byref(sw)), "pcg_tile_form")
         return tx.value, ty.value, sw.value
 
+    def resident_form(self):
+        """(workgroups, cells a thread) that the next solve keeps its vectors
+        in on the chip, or (0, 0) when it iterates by passes over tiles
+        (pcg_resident_form)."""
+        g, c = ctypes.c_int32(), ctypes.c_int32()
+        L.check(self.lib.pcg_resident_form(self._ctx, ctypes.byref(g), ctypes.byref(c)),
+                "pcg_resident_form")
+        return g.value, c.value
+
     def set_fractions(self, ax=None, ay=None, az=None, vol=None):
         """Free-slip cut-cell fractions (pcg_set_fractions): MAC face area
         fractions ax[nz,ny,nx+1], ay[nz,ny+1,nx], az[nz+1,ny,nx] and cell

@@ -97,8 +97,17 @@ void left_the_chip()
                 const pcg_stats_t a = c.solve(1e-11, maxit);
                 const int sa = c.status;
                 check(sa == (maxit == 40 ? PCG_MAXIT : PCG_OK) && dev.resident > 0, "on the chip");
+                int32_t wgs = -1, cells = -1;
+                check(pcg_resident_form(c.c, &wgs, &cells) == PCG_OK && wgs > 1 && wgs <= dev.cus && cells > 0,
+                      "resident form: reported");
+                pcg_set_timing(c.c, 1);
+                check(pcg_resident_form(c.c, &wgs, &cells) == PCG_OK && wgs == 0 && cells == 0,
+                      "resident form: not for timed solves");
+                pcg_set_timing(c.c, 0);
                 (refused ? dev.refused : dev.timeouts) = 1;
                 const pcg_stats_t b = c.solve(1e-11, maxit);
+                check(pcg_resident_form(c.c, &wgs, &cells) == PCG_OK && wgs == 0 && cells == 0,
+                      "resident form: none after leaving the chip");
                 check(c.status == sa && b.iters == a.iters && b.outer_iters == a.outer_iters,
                       "left the chip: the tile passes solve it");
                 const pcg_stats_t d = c.solve(1e-11, maxit);
