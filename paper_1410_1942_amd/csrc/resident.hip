@@ -49,19 +49,13 @@
 #include <stdint.h>
 #include <type_traits>
 
-#include "pcg_types.h"
+#include "device_common.h"
 #include "pcg.h"
 #include "resident_shapes.h"
 
 namespace pcgmi {
 
 namespace {
-
-#define GLB __attribute__((address_space(1)))
-template <typename T>
-__device__ __forceinline__ GLB T *gp(T *p) { return (GLB T *)p; }
-template <typename T>
-__device__ __forceinline__ const GLB T *gp(const T *p) { return (const GLB T *)p; }
 
 typedef unsigned long long u64;
 
@@ -101,38 +95,10 @@ __device__ __forceinline__ double wave_sum63(double v)
     return v;
 }
 
-__device__ __forceinline__ double recip(double d)
-{
-    double y = __builtin_amdgcn_rcp(d);
-    double e = fma(-d, y, 1.0);
-    y = fma(y, e, y);
-    e = fma(-d, y, 1.0);
-    return fma(y, e, y);
-}
-__device__ __forceinline__ float recip(float d) { return __builtin_amdgcn_rcpf(d); }
-
 // Whether recip(b) and its refinement stay within the range of normal numbers;
 // sums of solves scaled near its ends (a source of 1e-150 with densities of
 // 1e-9) do not, and are divided by.
 __device__ __forceinline__ bool recip_range(double b) { return b > 0x1p-1000 && b < 0x1p1000; }
-
-// Face coefficient 2 / (a + b) of two cells' densities, 0 at solids (+inf).
-template <typename T>
-__device__ __forceinline__ T face_beta(T den)
-{
-    return den < (T)INFINITY ? T(2) * recip(den) : T(0);
-}
-
-__device__ __forceinline__ void *dir_buf(const Slot &S, int b)
-{
-    return b == 0 ? S.dir0 : (b == 1 ? S.dir1 : S.dir2);
-}
-
-__device__ double pow2_scale(double norm)
-{
-    if (!(norm > 0.0) || !isfinite(norm)) return 1.0;
-    return ldexp(1.0, -ilogb(norm));
-}
 
 // Holds the compiler to the value in a register: what is derived from it in
 // the iteration loop (coefficient addresses, lane masks) is formed there
@@ -356,12 +322,12 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget, int polls
                 T b[6] = { T(0), T(0), T(0), T(0), T(0), T(0) };
                 if (in) {
                     const T rc = rho[m];
-                    b[0] = face_beta(rc + (oxm ? rho[m + oxm] : wall(0)));
-                    b[1] = face_beta(rc + (oxp ? rho[m + oxp] : wall(1)));
-                    b[2] = face_beta(rc + (oym ? rho[m + oym] : wall(2)));
-                    b[3] = face_beta(rc + (oyp ? rho[m + oyp] : wall(3)));
-                    b[4] = face_beta(rc + (kk > 0 ? rho[m - P] : wall(4)));
-                    b[5] = face_beta(rc + (kk < nz - 1 ? rho[m + P] : wall(5)));
+                    b[0] = fb(rc + (oxm ? rho[m + oxm] : wall(0)));
+                    b[1] = fb(rc + (oxp ? rho[m + oxp] : wall(1)));
+                    b[2] = fb(rc + (oym ? rho[m + oym] : wall(2)));
+                    b[3] = fb(rc + (oyp ? rho[m + oyp] : wall(3)));
+                    b[4] = fb(rc + (kk > 0 ? rho[m - P] : wall(4)));
+                    b[5] = fb(rc + (kk < nz - 1 ? rho[m + P] : wall(5)));
                     if (S.ax) {
                         const GLB double *ax = gp(S.ax) + ((int64_t)kk * ny + j) * (nx + 1);
                         const GLB double *ay = gp(S.ay) + (int64_t)kk * (ny + 1) * nx + i;
