@@ -169,9 +169,11 @@ enum {
  * grid_blocks given, and a timed solve (pcg_set_timing) stay with the tile
  * passes, and so does a context with PCG_FRACTIONS until fractions are set.
  * Iterating on the chip takes all of a launch's workgroups at once.  Where
- * other work keeps part of the device for seconds, or the runtime refuses the
- * launch, the solve starts again on the tile passes (from zero, or from what p
- * holds when it was a warm start), and its context or batch stays with them.
+ * other work keeps part of the device too long for that, or the runtime refuses
+ * the launch (it lets one process at a time launch so on a device), the solve
+ * starts again on the tile passes (from zero, or from what p holds when it was
+ * a warm start), and its context or batch stays with them; so do those created
+ * in the ten seconds after a refusal.
  *
  * Options.  Zero-initialised fields take the defaults in brackets.
  *   precision   PCG_PREC_FP64 [default] or PCG_PREC_FP32_IR: FP32 stencil

@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -114,6 +115,21 @@ using Clock = std::chrono::steady_clock;
 double ms_since(Clock::time_point t0)
 {
     return std::chrono::duration<double, std::milli>(Clock::now() - t0).count();
+}
+
+// When the runtime last refused a resident launch, by device (0: never).  It
+// lets one process at a time launch cooperatively on a device, as long as that
+// process lives, and takes 40 ms to say no to another (a solve of 37 x 29 x 23
+// cells 42 ms instead of 2.9): contexts and batches created within ten seconds
+// of a refusal do not ask.
+constexpr int kMaxDevices = 64;
+constexpr std::chrono::seconds kRefusalHolds{10};
+std::atomic<int64_t> g_refused[kMaxDevices] = {};
+
+bool lately_refused(int device)
+{
+    const int64_t t = g_refused[device % kMaxDevices].load(std::memory_order_relaxed);
+    return t != 0 && Clock::now().time_since_epoch() - Clock::duration(t) < kRefusalHolds;
 }
 
 // ---- tile shape table (autotuned values can be installed at run time) ----
@@ -813,6 +829,7 @@ struct Engine {
     static constexpr int kResBudget = 4096, kResPolls = 1 << 21;
     int res_budget = kResBudget, res_polls = kResPolls;
     bool no_resident = false;   // an exchange timed out or a launch was refused
+    int device = 0;
     bool looked = false;    // the last step refreshed the host's states
     int fail_after = 0;     // test hook: the step call that reports a failure
     HostMirror *mirror = nullptr;  // caller-owned host mirrors: no pinned memory,
@@ -903,8 +920,9 @@ struct Engine {
         HIP_TRY(hipMemcpyAsync(d_hdr, h_hdr, sizeof(BatchHeader), hipMemcpyHostToDevice, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         if (!mirror) HIP_TRY(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
-        int device = 0, cus = 0, coop = 0;
+        int cus = 0, coop = 0;
         HIP_TRY(hipGetDevice(&device));
+        no_resident = lately_refused(device);
         HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
         HIP_TRY(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, device));
         nshapes = coop ? std::min(kMaxShapes, resident_shapes(prec, rshapes, kMaxShapes)) : 0;
@@ -1482,6 +1500,8 @@ struct Engine {
     int leave_resident_all()
     {
         (void)hipGetLastError();
+        g_refused[device % kMaxDevices].store(Clock::now().time_since_epoch().count(),
+                                              std::memory_order_relaxed);
         for (int id = 0; id < max_slots; ++id)
             if (slots[id].used && slots[id].running && slots[id].resident) {
                 const int st = leave_resident(id);

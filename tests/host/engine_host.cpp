@@ -15,6 +15,12 @@ void check(bool ok, const char *what)
     failures += !ok;
 }
 
+void fresh_device()
+{
+    dev = Device();
+    g_refused[0] = 0;
+}
+
 // A context of one density on an n^3 grid with p = 0 on top.
 struct Context {
     std::vector<double> rho, rhs, p;
@@ -53,7 +59,7 @@ struct Context {
 // may end there.
 void refinement_trips()
 {
-    dev = Device();
+    fresh_device();
     pcg_opts_t o{};
     o.precision = PCG_PREC_FP32_IR;
     {
@@ -90,7 +96,7 @@ void left_the_chip()
     for (int prec : { PCG_PREC_FP64, PCG_PREC_FP32_IR })
         for (int refused : { 0, 1 })
             for (int maxit : { 1000000, 40 }) {
-                dev = Device();
+                fresh_device();
                 pcg_opts_t o{};
                 o.precision = prec;
                 Context c(33, 31, 29, o);
@@ -114,8 +120,20 @@ void left_the_chip()
                 check(c.status == sa && d.iters == a.iters && dev.resident == 0 && dev.graphs > 0,
                       "left the chip: the next solve is theirs too");
             }
+    // contexts created soon after a refusal do not ask again, later ones do
+    for (int ago : { 0, 9, 11 }) {
+        fresh_device();
+        Context a(33, 31, 29, pcg_opts_t{});
+        dev.refused = 1;
+        a.solve(1e-8, 1000000);
+        g_refused[0] -= std::chrono::duration_cast<Clock::duration>(std::chrono::seconds(ago)).count();
+        Context b(33, 31, 29, pcg_opts_t{});
+        b.solve(1e-8, 1000000);
+        check(a.status == PCG_OK && b.status == PCG_OK && (dev.resident > 0) == (ago > 10),
+              "left the chip: contexts created soon after a refusal");
+    }
     for (int refused : { 0, 1 }) {
-        dev = Device();
+        fresh_device();
         pcg_opts_t o{};
         o.precision = PCG_PREC_FP32_IR;
         const pcg_grid_t g = { 17, 19, 21, 1.0 };
@@ -154,7 +172,7 @@ void several_replays()
     for (int prec : { PCG_PREC_FP64, PCG_PREC_FP32_IR })
         for (int top : { PCG_BC_DIRICHLET, PCG_BC_NEUMANN })
             for (int flags : { 0, (int)PCG_TWO_SWEEPS }) {
-                dev = Device();
+                fresh_device();
                 // ten replays, or three trips of five: the first step of
                 // eight ends within a loop
                 dev.iters = prec == PCG_PREC_FP64 ? 300 : 150;
@@ -219,7 +237,7 @@ void columns()
 // built-in one (installed again, too) leaves room for more even heights.
 void tile_rules()
 {
-    dev = Device();
+    fresh_device();
     for (int prec : { PCG_PREC_FP64, PCG_PREC_FP32_IR })
         for (int flags : { (int)PCG_FLAT_TILES, (int)PCG_PLANE_TILES, (int)PCG_NARROW_TILES }) {
             const int table = flags == PCG_FLAT_TILES ? 0 : flags == PCG_PLANE_TILES ? 2 : 3;
@@ -251,7 +269,7 @@ void tile_rules()
 // reciprocal that divides by the row length, exchange words, workgroups).
 void bricks()
 {
-    dev = Device();
+    fresh_device();
     bool cover = true, bounds = true, some = false, none = true, exact = true;
     std::vector<ResidentShape> shapes(64);
     for (int prec : { PCG_PREC_FP64, PCG_PREC_FP32_IR }) {
