@@ -897,6 +897,7 @@ struct Engine {
         d_bad = (int *)(arena + off);
         alloc.reset(hb, bytes);
         slots.assign(nslots, SlotHost{});
+        rlaunch.reserve(nslots);
         stream = (hipStream_t)hip_stream;
         if (hm) {
             mirror = hm;
@@ -1249,18 +1250,14 @@ struct Engine {
         int ns = 0;
         int m = 0;
         bool all_fused = true;
-        // resident solves first, by shape: a launch takes a run of the table
-        std::vector<int> order;
-        for (int id = 0; id < max_slots; ++id)
-            if (slots[id].used && slots[id].running) order.push_back(id);
-        std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-            auto key = [&](int id) { return slots[id].resident ? slots[id].res.shape : kMaxShapes; };
-            return key(a) < key(b);
-        });
         rlaunch.clear();
         int nres = 0;
-        for (int id : order) {
+        // resident solves first, by shape: a launch takes a run of the table
+        // (a step allocates nothing: rlaunch has room for every slot)
+        for (int entry = 0; entry < (kMaxShapes + 1) * max_slots; ++entry) {
+            const int shape = entry / max_slots, id = entry % max_slots;
             SlotHost &S = slots[id];
+            if (!S.used || !S.running || shape != (S.resident ? S.res.shape : kMaxShapes)) continue;
             Slot &d = h_slots[ns++];
             std::memset(&d, 0, sizeof(Slot));
             d.nx = S.geo.nx; d.ny = S.geo.ny; d.nz = S.geo.nz;

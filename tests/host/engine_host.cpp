@@ -4,6 +4,23 @@
 
 #include "fake_device.h"
 
+// Heap allocations so far (no exception may cross the C interface, and a
+// polling step makes none).
+static long allocations = 0;
+void *operator new(size_t n)
+{
+    ++allocations;
+    if (void *p = std::malloc(n ? n : 1)) return p;
+    throw std::bad_alloc();
+}
+void *operator new(size_t n, const std::nothrow_t &) noexcept
+{
+    ++allocations;
+    return std::malloc(n ? n : 1);
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+
 namespace {
 
 int failures = 0;
@@ -192,7 +209,10 @@ void several_replays()
                 for (int i = 0; i < 4; ++i)
                     ok = ok && pcg_batch_admit(b, &g, rho.data(), nullptr, &bc, rhs.data(), p.data(), 1e-11,
                                                1000000, flags, &slot) == PCG_OK;
+                recorded.reserve(4096);   // (the stand-in's own list)
+                const long before = allocations;
                 while (ok && active && steps++ < 100) ok = pcg_batch_step(b, 8, &active) == PCG_OK;
+                check(allocations == before, "a polling step allocates nothing");
                 check(ok && steps <= 2 + (top == PCG_BC_NEUMANN), "several replays a step");
                 pcg_batch_destroy(b);
             }
