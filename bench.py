@@ -773,7 +773,7 @@ def kernel_sha():
     import hashlib
     import re
     h = hashlib.sha256()
-    for f in ("kernels.hip", "pcg_types.h"):
+    for f in ("kernels.hip", "device_common.h", "pcg_types.h"):
         src = open(os.path.join(ROOT, "paper_1410_1942_amd", "csrc", f)).read()
         src = re.sub(r"/\*.*?\*/", "", src, flags=re.S)
         src = re.sub(r"//[^\n]*", "", src)
