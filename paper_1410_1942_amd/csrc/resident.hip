@@ -15,8 +15,11 @@
 //
 // What bounds it: the two exchanges, about 1.5 us each across the eight XCDs
 // (a store that reaches memory, a load that sees it), and for bricks of many
-// cells their LDS reads and arithmetic (40 B and about 60 vector instructions
-// a cell).  A launch per iteration instead waits for memory plane after plane
+// cells their LDS accesses and arithmetic.  Counted a cell and iteration: 20
+// LDS and 123 vector instructions at 320 x 128 x 96 FP64 (30 cells a thread,
+// the row formed twice; 16 and 106 where one density fills the grid), 23 and
+// 187 at 101 x 77 x 59 FP32 (four cells); of the wave cycles 21 and 16 % issue
+// vector instructions, 58 and 68 % wait.  A launch per iteration instead waits for memory plane after plane
 // and streams 41 B a cell.  Measured per iteration of whole solves, launches
 // against this: FP64 33^3 14.6 -> 5.9 us, 64^3 18.7 -> 7.4, 128^3 32 -> 15,
 // 320 x 128 x 96 52 -> 32; FP32 33^3 14.5 -> 6.1, 64^3 18.0 -> 7.5, 128^3 33
