@@ -169,11 +169,11 @@ enum {
  * grid_blocks given, and a timed solve (pcg_set_timing) stay with the tile
  * passes, and so does a context with PCG_FRACTIONS until fractions are set.
  * Iterating on the chip takes all of a launch's workgroups at once.  Where
- * other work keeps part of the device too long for that, or the runtime refuses
+ * other work keeps part of the device for 0.3 s, or the runtime refuses
  * the launch (it lets one process at a time launch so on a device), the solve
  * starts again on the tile passes (from zero, or from what p holds when it was
  * a warm start), and its context or batch stays with them; so do those created
- * in the ten seconds after a refusal.
+ * in the next ten seconds.
  *
  * Options.  Zero-initialised fields take the defaults in brackets.
  *   precision   PCG_PREC_FP64 [default] or PCG_PREC_FP32_IR: FP32 stencil
@@ -533,7 +533,7 @@ int pcg_inject_failure(pcg_ctx_t *ctx, int32_t after_steps);
  * which exchange their sums): at most `iterations` a launch (0 = the default,
  * 4096; the answer does not depend on it) and `polls` looks at another
  * workgroup's sums before an exchange counts as timed out (negative = the
- * default, a few seconds; 0 = every exchange between workgroups times out).
+ * default, about 0.3 s; 0 = every exchange between workgroups times out).
  * A solve whose exchange times out, because other work keeps part of the
  * device, starts again on the tile passes, and the context or batch stays
  * with them.  PCG_EINVAL for a null context or iterations < 0.

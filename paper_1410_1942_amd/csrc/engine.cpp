@@ -117,19 +117,26 @@ double ms_since(Clock::time_point t0)
     return std::chrono::duration<double, std::milli>(Clock::now() - t0).count();
 }
 
-// When the runtime last refused a resident launch, by device (0: never).  It
-// lets one process at a time launch cooperatively on a device, as long as that
-// process lives, and takes 40 ms to say no to another (a solve of 37 x 29 x 23
-// cells 42 ms instead of 2.9): contexts and batches created within ten seconds
-// of a refusal do not ask.
+// When a solve last found the chip taken, by device (0: never): its launch was
+// refused or its exchange timed out.  The runtime lets one process at a time
+// launch cooperatively on a device, as long as that process lives, and takes
+// 40 ms to say no to another (a solve of 37 x 29 x 23 cells 42 ms instead of
+// 2.9); a kernel of another stream that holds a compute unit costs 0.3 s of
+// polls (320 x 128 x 96: 361 ms instead of 61 on the tile passes).  Contexts
+// and batches created in the ten seconds after do not try.
 constexpr int kMaxDevices = 64;
-constexpr std::chrono::seconds kRefusalHolds{10};
-std::atomic<int64_t> g_refused[kMaxDevices] = {};
+constexpr std::chrono::seconds kTakenHolds{10};
+std::atomic<int64_t> g_taken[kMaxDevices] = {};
 
-bool lately_refused(int device)
+bool lately_taken(int device)
 {
-    const int64_t t = g_refused[device % kMaxDevices].load(std::memory_order_relaxed);
-    return t != 0 && Clock::now().time_since_epoch() - Clock::duration(t) < kRefusalHolds;
+    const int64_t t = g_taken[device % kMaxDevices].load(std::memory_order_relaxed);
+    return t != 0 && Clock::now().time_since_epoch() - Clock::duration(t) < kTakenHolds;
+}
+
+void note_taken(int device)
+{
+    g_taken[device % kMaxDevices].store(Clock::now().time_since_epoch().count(), std::memory_order_relaxed);
 }
 
 // ---- tile shape table (autotuned values can be installed at run time) ----
@@ -824,10 +831,11 @@ struct Engine {
     };
     std::vector<ResidentLaunch> rlaunch;
     // iterations a launch of a single solve takes at most, and looks at
-    // another workgroup's sums before an exchange counts as timed out (some
-    // seconds: only workgroups that the device has no room for reach it)
+    // another workgroup's sums before an exchange counts as timed out (0.3 s:
+    // only workgroups that the device has no room for reach it)
     static constexpr int kResBudget = 4096, kResPolls = 1 << 21;
     int res_budget = kResBudget, res_polls = kResPolls;
+    bool polls_given = false;   // by the test hook
     bool no_resident = false;   // an exchange timed out or a launch was refused
     int device = 0;
     bool looked = false;    // the last step refreshed the host's states
@@ -923,7 +931,7 @@ struct Engine {
         if (!mirror) HIP_TRY(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
         int cus = 0, coop = 0;
         HIP_TRY(hipGetDevice(&device));
-        no_resident = lately_refused(device);
+        no_resident = lately_taken(device);
         HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
         HIP_TRY(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, device));
         nshapes = coop ? std::min(kMaxShapes, resident_shapes(prec, rshapes, kMaxShapes)) : 0;
@@ -1497,8 +1505,7 @@ struct Engine {
     int leave_resident_all()
     {
         (void)hipGetLastError();
-        g_refused[device % kMaxDevices].store(Clock::now().time_since_epoch().count(),
-                                              std::memory_order_relaxed);
+        note_taken(device);
         for (int id = 0; id < max_slots; ++id)
             if (slots[id].used && slots[id].running && slots[id].resident) {
                 const int st = leave_resident(id);
@@ -1626,6 +1633,7 @@ struct Engine {
             SlotHost &S = slots[id];
             if (!S.used || !S.running) continue;
             if (h_states[id].rfail) {
+                if (!polls_given) note_taken(device);
                 st = leave_resident(id);
                 if (st) return st;
                 continue;
@@ -2076,6 +2084,7 @@ int pcg_set_resident_limits(pcg_ctx_t *c, int32_t iterations, int32_t polls)
     if (!c || iterations < 0) return PCG_EINVAL;
     c->eng.res_budget = iterations > 0 ? iterations : Engine::kResBudget;
     c->eng.res_polls = polls >= 0 ? polls : Engine::kResPolls;
+    c->eng.polls_given = polls >= 0;
     return PCG_OK;
 }
 

@@ -43,7 +43,7 @@
 // have all passed.
 //
 // Polling is bounded.  Where not all workgroups come to run beside each other
-// in that time (other work holds compute units of the device for seconds) a
+// in that time (other work holds compute units of the device for 0.3 s) a
 // workgroup that waits in vain sets SlotState::rfail and all of them end, the
 // solve's later launches at once; the host then starts it again on the tile
 // passes.

@@ -35,7 +35,7 @@ void check(bool ok, const char *what)
 void fresh_device()
 {
     dev = Device();
-    g_refused[0] = 0;
+    g_taken[0] = 0;
 }
 
 // A context of one density on an n^3 grid with p = 0 on top.
@@ -137,17 +137,21 @@ void left_the_chip()
                 check(c.status == sa && d.iters == a.iters && dev.resident == 0 && dev.graphs > 0,
                       "left the chip: the next solve is theirs too");
             }
-    // contexts created soon after a refusal do not ask again, later ones do
+    // contexts created soon after do not try, later ones do (nor do time-outs
+    // that the test hook asked for count)
+    for (int kind : { 0, 1, 2 })
     for (int ago : { 0, 9, 11 }) {
         fresh_device();
         Context a(33, 31, 29, pcg_opts_t{});
-        dev.refused = 1;
+        if (kind == 2) pcg_set_resident_limits(a.c, 0, 0);
+        (kind == 0 ? dev.refused : dev.timeouts) = 1;
         a.solve(1e-8, 1000000);
-        g_refused[0] -= std::chrono::duration_cast<Clock::duration>(std::chrono::seconds(ago)).count();
+        check((g_taken[0] != 0) == (kind < 2), "left the chip: noted for the device");
+        if (kind < 2) g_taken[0] -= std::chrono::duration_cast<Clock::duration>(std::chrono::seconds(ago)).count();
         Context b(33, 31, 29, pcg_opts_t{});
         b.solve(1e-8, 1000000);
-        check(a.status == PCG_OK && b.status == PCG_OK && (dev.resident > 0) == (ago > 10),
-              "left the chip: contexts created soon after a refusal");
+        check(a.status == PCG_OK && b.status == PCG_OK && (dev.resident > 0) == (ago > 10 || kind == 2),
+              "left the chip: contexts created soon after");
     }
     for (int refused : { 0, 1 }) {
         fresh_device();

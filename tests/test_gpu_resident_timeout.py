@@ -83,6 +83,30 @@ def test_timeout(orc, F, shape, bc, kind, precision, polls):
     close(got, 1e-8)
 
 
+def test_device_held_by_another_stream(F):
+    """A kernel on another stream holds a compute unit for a second; the bricks of
+    this grid need all of them."""
+    import torch
+    print("case resident, device held", flush=True)
+    case = _make(F, (320, 128, 96), TANK, "classes")
+    rhs = _t(case.rhs)
+    mine, other = torch.cuda.Stream(), torch.cuda.Stream()
+    tiles = _solver(case, 0, grid_blocks=512)
+    want = tiles.solve(rhs)[0].clone()
+    tiles.close()
+    s = _solver(case, 0, stream=mine)
+    assert s.resident_form()[0] == 256
+    s.set_resident_limits(polls=1 << 21)     # the default, not counted against later contexts
+    torch.cuda.synchronize()
+    with torch.cuda.stream(other):
+        torch.cuda._sleep(2_400_000_000)     # about a second
+    p, st = s.solve(rhs, tol=1e-8)
+    torch.cuda.synchronize()
+    s.close()
+    assert st["status"] == 0
+    assert float((p - want).abs().max()) <= 1e-6 * float(want.abs().max())
+
+
 @pytest.mark.parametrize("precision", [0, 1], ids=["fp64", "ir"])
 def test_one_workgroup_exchanges_nothing(F, precision):
     import torch
