@@ -1262,10 +1262,15 @@ struct Engine {
         int nres = 0;
         // resident solves first, by shape: a launch takes a run of the table
         // (a step allocates nothing: rlaunch has room for every slot)
+        auto shape_of = [](const SlotHost &S) { return S.resident ? S.res.shape : kMaxShapes; };
+        uint64_t shapes = 0;
+        for (const SlotHost &S : slots)
+            if (S.used && S.running) shapes |= 1ull << shape_of(S);
         for (int entry = 0; entry < (kMaxShapes + 1) * max_slots; ++entry) {
             const int shape = entry / max_slots, id = entry % max_slots;
+            if (!(shapes >> shape & 1)) { entry += max_slots - 1; continue; }
             SlotHost &S = slots[id];
-            if (!S.used || !S.running || shape != (S.resident ? S.res.shape : kMaxShapes)) continue;
+            if (!S.used || !S.running || shape != shape_of(S)) continue;
             Slot &d = h_slots[ns++];
             std::memset(&d, 0, sizeof(Slot));
             d.nx = S.geo.nx; d.ny = S.geo.ny; d.nz = S.geo.nz;

@@ -98,10 +98,24 @@ __device__ __forceinline__ double wave_sum63(double v)
     return v;
 }
 
-// Whether recip(b) and its refinement stay within the range of normal numbers;
-// sums of solves scaled near its ends (a source of 1e-150 with densities of
-// 1e-9) do not, and are divided by.
-__device__ __forceinline__ bool recip_range(double b) { return b > 0x1p-1000 && b < 0x1p1000; }
+// a / b by a refined reciprocal.  SCALED: b by its exponent first, and a by the
+// same power of two (which is exact), since the sums of solves scaled near the
+// ends of the number range (a source of 1e-150 with densities of 1e-9) have no
+// reciprocal within it.
+template <bool SCALED>
+struct Divisor {
+    double y;
+    int e;
+    __device__ __forceinline__ explicit Divisor(double b)
+        : e(SCALED ? -__builtin_amdgcn_frexp_exp(b) : 0)
+    {
+        y = recip(SCALED ? __builtin_amdgcn_ldexp(b, e) : b);
+    }
+    __device__ __forceinline__ double under(double a) const
+    {
+        return (SCALED ? __builtin_amdgcn_ldexp(a, e) : a) * y;
+    }
+};
 
 // Holds the compiler to the value in a register: what is derived from it in
 // the iteration loop (coefficient addresses, lane masks) is formed there
@@ -544,12 +558,12 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget, int polls
         if (!all_sum<1>(v1, area1, G, g, ++tag, polls, red, &s_fail)) break;
         pap = v1[0];
         if (!isfinite(pap) || !(pap > 0.0)) { end = (F64 || !isfinite(pap)) ? 2 : 3; break; }
-        alpha = !F64 || recip_range(pap) ? rz * recip(pap) : rz / pap;
+        alpha = Divisor<F64>(pap).under(rz);
 
         // x += alpha p, z -= alpha q / diag, the faces of z, r.z and r.r
         const T ta = (T)alpha;
         keep_here(cflag);
-        const double inv_rz = recip(rz);   // ready before the sums are
+        const Divisor<F64> by_rz(rz);   // ready before the sums are
         double v2[2] = { 0.0, 0.0 };
         auto second_half = [&](int c, int k, const Row<T> &r, T pc) __attribute__((always_inline)) {
             const T inv = r.dg > T(0) ? recip(r.dg) : T(0);   // hull rows keep z = 0
@@ -591,7 +605,7 @@ k_resident(const Slot *__restrict__ slots, int s0, int s1, int budget, int polls
             }
         }
         if (!all_sum<2>(v2, area2, G, g, ++tag, polls, red, &s_fail)) break;
-        beta = !F64 || recip_range(rz) ? v2[0] * inv_rz : v2[0] / rz;
+        beta = by_rz.under(v2[0]);
         rz = v2[0];
         rr = v2[1];
         ++iter;
