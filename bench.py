@@ -382,7 +382,7 @@ def main():
         log(f"  {cpu_val:.4f} Gcell-iter/s on {oracle.threads()} threads")
 
     if not args.no_side:
-        # the 32^3 parity case: launch-bound on the GPU; the oracle's full
+        # the 32^3 parity case: on the chip, bound by its exchanges; the oracle's full
         # solve of it timed on the host beside it
         c1 = F.config1(32, keep_velocity=False)
         out["flat32"] = bench_single(c1, args.tol, dev, "32^3 flat two-phase tank, FP64")

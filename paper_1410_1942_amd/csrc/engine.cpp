@@ -4,7 +4,8 @@
 // One Engine drives any number of resident solves ("slots").  Device memory
 // comes from a caller-owned arena: a fixed head (batch header, slot table,
 // slot states, error flag) followed by one block per slot carved by a
-// first-fit allocator.  The iteration is captured once as a hipGraph of
+// first-fit allocator.  Solves that fit on the chip iterate in launches of the
+// resident kernel.  The others' iteration is captured once as a hipGraph of
 // check_every x [K1, K2] launches that read the slot table from device
 // memory, so slots can join and leave between replays without re-capture.
 #include <hip/hip_runtime.h>
@@ -1122,10 +1123,10 @@ struct Engine {
         return PCG_OK;
     }
 
-    // Check connectivity (unless skipped), encode and validate the densities,
-    // then (unless switched off) run the chained class rounds; one host round
-    // trip reads both results.  Overwrites the slot's coefficients: on any
-    // error the slot is left not ready.
+    // Check connectivity (unless skipped), then encode, validate and (unless
+    // switched off) class the densities in one pass and one host round trip.
+    // Overwrites the slot's coefficients: on any error the slot is left not
+    // ready.
     int encode_slot(SlotHost &S, const double *rho, const uint8_t *mask, int flags)
     {
         S.ready = false;

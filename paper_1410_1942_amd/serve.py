@@ -5,7 +5,7 @@ at given times.  The loop admits waiting requests first-in first-out while
 the batch's arena has room for their footprint and a slot is free
 (``pcg_batch_admit`` refuses with PCG_EBUSY otherwise), with a bounded
 bypass: requests behind a head that does not fit may go first, a limited
-number of times per head (``AdmissionQueue``).  It replays the captured
+number of times per head (``AdmissionQueue``).  It advances the
 iterations of every resident solve together (``pcg_batch_step``), and
 retires finished solves as soon as their status turns final, recording the
 latency from arrival to completion.  The pressure of each request stays a
